@@ -87,7 +87,10 @@ enum {
 typedef struct wv_ctx wv_ctx;
 
 /* Timings (milliseconds, HIP events on the context stream) and sizes of the
- * most recent wv_search_range / wv_eval_primes call. */
+ * most recent wv_search_range / wv_eval_primes call.  Primes evaluated along
+ * progressions (see wv_set_tables) count the sums and terms of the
+ * congruences used for them, their device time under ms_sum, no chunks, and
+ * the terms per block as chunk_terms. */
 typedef struct {
     double ms_total;     /* first to last event of the call (device time)        */
     double ms_sieve;     /* segmented sieve and prime compaction (search only)   */
@@ -118,7 +121,11 @@ int wv_destroy(wv_ctx *ctx);
  * or a Bernoulli table defined with wv_define_table, e_table one of the EE ids
  * or a defined Euler table.  Default: WV_TABLE_BB30 and WV_TABLE_EE33 (the
  * cheapest printed ones, cost 227p/6480 and 27p/512).  Every valid choice gives
- * identical residues; only the work changes.  Errors: WV_EINVAL. */
+ * identical residues; only the work changes.  With the default choice (and no
+ * forced block shape, chunk size or progress callback) the synchronous calls
+ * evaluate primes from 2^27 on by fast evaluation along arithmetic
+ * progressions instead of term by term, from whichever printed congruences
+ * cost it least at their size.  Errors: WV_EINVAL. */
 int wv_set_tables(wv_ctx *ctx, int b_table, int e_table);
 
 /* Define a congruence at run time (for instance one derived from eqnVandiver

@@ -5,11 +5,11 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRCS = [os.path.join(HERE, "csrc", f) for f in ("wv_kernels.hip", "wv_capi.hip", "wv_tune.hip", "wv_server.hip",
-                                                 "wv_irregular.hip", "wv_static.hip")]
+                                                 "wv_irregular.hip", "wv_static.hip", "wv_grid.hip")]
 PEAK_SRC = os.path.join(HERE, "csrc", "peak.hip")
 PEAK_LIB = os.path.join(HERE, "libwvpeak.so")
 DEPS = [os.path.join(HERE, "csrc", f) for f in ("mont.hpp", "sum_core.hpp", "wv_tables.hpp", "wv_internal.hpp",
-                                                "wv_ctx.hpp")] + [
+                                                "wv_ctx.hpp", "wave_ops.hpp", "ntt.hpp", "grid_plan.hpp")] + [
     os.path.join(ROOT, "include", "wvprime.h")]
 LIB = os.path.join(HERE, "libwvprime.so")
 ARCH = os.environ.get("WV_OFFLOAD_ARCH", "gfx950")

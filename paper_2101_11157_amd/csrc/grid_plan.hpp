@@ -1,0 +1,95 @@
+// grid_plan.hpp -- which congruences and which block length the grid path uses
+// for primes of a size: plain host code, unit-tested without a GPU.
+#pragma once
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+#include "ntt.hpp"
+#include "wv_tables.hpp"
+#include "wvprime.h"
+
+namespace wv {
+
+struct GridClass {
+    int logl = 0;          // transform length 2^logl; blocks of K = 2^(logl - 1) - 1 terms
+    int tb = 0, te = 0;    // compiled tables
+    double ops = 0;        // modelled operations per prime
+    bool operator==(const GridClass &o) const { return logl == o.logl && tb == o.tb && te == o.te; }
+};
+
+constexpr uint64_t grid_k(int logl) { return (1ull << (logl - 1)) - 1; }
+constexpr uint64_t grid_w(int logl) { return 1ull << (logl - 1); }
+
+// Upper bound on the shifts (workgroups of W block starts) of one prime p with
+// a table's sums: a sum over (x p, y p) holds at most (y - x) p + 1 terms.
+inline uint64_t grid_shifts(const TableDef &d, double p, int logl) {
+    const double K = (double)grid_k(logl), W = (double)grid_w(logl);
+    uint64_t r = 0;
+    for (int i = 0; i < d.n; i++) {
+        const TermDef &t = d.t[i];
+        const double len = ((double)t.ya / t.yb - (double)t.xa / t.xb) * p + 1.0;
+        r += (uint64_t)(len / K / W) + 1;
+    }
+    return r;
+}
+
+// The same as an estimate: ceil of the blocks over W, no block no shift.
+inline double grid_shifts_est(const TableDef &d, double p, int logl) {
+    const double K = (double)grid_k(logl), W = (double)grid_w(logl);
+    double r = 0;
+    for (int i = 0; i < d.n; i++) {
+        const TermDef &t = d.t[i];
+        r += std::ceil(std::floor(((double)t.ya / t.yb - (double)t.xa / t.xb) * p / K) / W);
+    }
+    return r;
+}
+
+// Operations of a pair of transforms (both moduli) of length L: about 50 per
+// element and modulus at every length used.
+inline double grid_pair_ops(int logl) {
+    const double L = (double)(1ull << logl);
+    return 2.0 * L * (14.0 + 2.6 * logl);
+}
+
+// One side's operations per prime: each shift transforms its kernel and brings
+// back `polys` value vectors; every sum has an inverse list and the terms
+// after its last block.
+inline double grid_side_ops(const TableDef &d, double p, int logl) {
+    const double W = (double)grid_w(logl), K = (double)grid_k(logl);
+    const int polys = d.deg + 1;
+    const double r = grid_shifts_est(d, p, logl);
+    const double pair = grid_pair_ops(logl);
+    return r * (pair + polys * (pair + 4.0 * W * 10.0)) + (r + d.n) * W * 30.0 + d.n * (0.5 * K * 30.0 + 4000.0);
+}
+
+// Node values of blocks of K terms, by doubling from blocks of 255.
+inline double grid_build_ops(int logl) {
+    double ops = 255.0 * 256.0 * 28.0 + 4.0 * grid_pair_ops(logl);
+    for (int l = kNttMinLog; l < logl; l++) ops += 19.0 * grid_pair_ops(l) + 600.0 * (double)(1ull << l);
+    return ops;
+}
+
+// The grid path's class for primes near p: least modelled work over the
+// lengths and compiled congruences.  A length needs p >= 4 L^2: every
+// difference of two points, at most p/2 + 2 K W, is then below p and nonzero.
+inline GridClass grid_class(uint64_t p) {
+    GridClass best;
+    best.ops = 1e300;
+    for (int logl = kNttMinLog; logl <= kNttMaxLog; logl++) {
+        if (p < (4ull << (2 * logl))) break;
+        GridClass c;
+        c.logl = logl;
+        double b = 1e300, e = 1e300;
+        for (int t = WV_TABLE_BB1; t <= WV_TABLE_EE33; t++) {
+            const double v = grid_side_ops(kTables[t], (double)p, logl);
+            if (kTables[t].deg == 3 && v < b) b = v, c.tb = t;
+            if (kTables[t].deg == 2 && v < e) e = v, c.te = t;
+        }
+        c.ops = b + e + grid_build_ops(logl);
+        if (c.ops < best.ops) best = c;
+    }
+    return best;
+}
+
+}  // namespace wv

@@ -285,6 +285,9 @@ void window_descs(uint64_t lo, uint64_t hi, std::vector<SegDesc> &d, uint64_t pi
 
 uint64_t window_piece(const wv_ctx *c, uint64_t hi) {
     // integers holding about kMaxBatchTerms / 2 terms of work at primes near hi
+    // (the grid path sums no terms one by one: whole segments)
+    GridClass g;
+    if (grid_takes(c, hi, &g)) return kSegSpan;
     const double cost = side_cost(c, c->tb) + side_cost(c, c->te);
     const double per_prime = std::max(1.0, (double)hi * cost);
     const double w = kMaxBatchTerms / 2 / per_prime * std::log(std::max<double>((double)hi, 3.0));
@@ -347,6 +350,12 @@ int results_to_host(wv_ctx *c, const wv_result *d, size_t n, wv_result *out) {
     return WV_OK;
 }
 
+// Whether every prime of a segment goes through the grid path, and its class
+// (that of the largest).
+static bool desc_grid(const wv_ctx *c, const SegDesc &d, GridClass *g) {
+    return std::max(d.L, d.lo) >= kGridMinP && grid_takes(c, std::min(d.hi, d.L + kSegSpan) - 1, g);
+}
+
 // All primes of the descriptor list (in order) and their residues into out.
 // Descriptors are grouped into batches of at most kMaxBatchSegs segments and
 // about kMaxBatchPrimes primes; each batch is one plan and one persistent
@@ -364,11 +373,22 @@ int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector
         // (slots per prime: those of the tables a batch up to its largest
         // prime can pick; work: each piece at the cost of the table serving
         // its top)
+        // Segments that the grid path takes form batches of their own, one
+        // class each (it bounds its own workspace).
+        GridClass gc, gj;
+        const bool grid = desc_grid(c, descs[i], &gc);
         size_t j = i;
         uint64_t np = 0, pm = 0;
         double est = 0.0;
         while (j < descs.size() && j - i < kMaxBatchSegs) {
             const uint64_t top = std::min(descs[j].hi, descs[j].L + kSegSpan);
+            if (desc_grid(c, descs[j], &gj) != grid || (grid && !(gj == gc))) break;
+            if (grid) {
+                if (np > 0 && np + counts[j] > kMaxBatchPrimes) break;
+                np += counts[j++];
+                pm = std::max(pm, top);
+                continue;
+            }
             const uint64_t pm_j = std::max(pm, top);
             const uint64_t per = (uint64_t)side_slots(c, batch_table(c, c->tb, pm_j)) +
                                  side_slots(c, batch_table(c, c->te, pm_j));
@@ -400,7 +420,10 @@ int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector
         WV_TRY(ensure(c, c->results, got * sizeof(wv_result)));
         uint64_t pmax = 0;
         for (size_t k = i; k < j; k++) pmax = std::max(pmax, std::min(descs[k].hi, descs[k].L + kSegSpan));
-        WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
+        if (grid)
+            WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
+        else
+            WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
         c->stats.ms_sieve += elapsed(c->ev[EV_START], c->ev[EV_SIEVE]);   // both recorded before its wait
         if (out && !dest) WV_TRY(results_to_host(c, as<wv_result>(c->results), got, out + written));
         if (out && dest) {
@@ -819,9 +842,11 @@ int wv_destroy(wv_ctx *c) {
                       &c->seg_off, &c->seg_desc, &c->pad_primes, &c->stats_hist, &c->stats_near, &c->coefs,
                       &c->lhsmod, &c->tbl_head, &c->tbl_term, &c->tbl_limb, &c->tails, &c->tail_hist,
                       &c->irr_tasks, &c->irr_units, &c->irr_primes, &c->irr_roff, &c->irr_v, &c->irr_fix,
-                      &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e};
+                      &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e, &c->grid_ws};
     for (DevBuf *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
+    for (DevBuf &b : c->ntt_tab)
+        if (b.ptr) (void)hipFree(b.ptr);
     for (int i = 0; i < EV_COUNT; i++)
         if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
     if (c->pin_res) (void)hipHostFree(c->pin_res);
@@ -959,7 +984,8 @@ int wv_search_windows(wv_ctx *c, const uint64_t *lo, const uint64_t *hi, size_t 
     }
     first[nwin] = d.size();
     // a small single-window search: one graph, sized by the prime-count bound
-    if (nwin == 1 && out && !d.empty() && d.size() <= kMaxBatchSegs && !c->progress) {
+    GridClass gc;
+    if (nwin == 1 && out && !d.empty() && d.size() <= kMaxBatchSegs && !c->progress && !desc_grid(c, d[0], &gc)) {
         const uint64_t bound = prime_count_bound(std::max<uint64_t>(lo[0], 5), hi[0]);
         const double work = (double)bound * (double)pmax * (side_cost(c, c->tb) + side_cost(c, c->te));
         if (bound <= cap && bound <= kMaxBatchPrimes && work <= kGraphSearchTerms) {
@@ -1086,6 +1112,37 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
     WV_TRY(ensure(c, c->primes, n * sizeof(uint64_t)));
     WV_TRY(ensure(c, c->results, n * sizeof(wv_result)));
     WV_HIP(hipMemcpyAsync(c->primes.ptr, primes, n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
+    // the primes of the grid path first, by class, the others (ascending
+    // too) after them; results go back to input order
+    std::vector<std::pair<uint64_t, size_t>> ord;
+    GridClass gc, gk;
+    if (grid_takes(c, pmax, &gc)) {
+        ord.resize(n);
+        for (size_t i = 0; i < n; i++) ord[i] = {primes[i], i};
+        std::sort(ord.begin(), ord.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        std::vector<uint64_t> sorted(n);
+        for (size_t i = 0; i < n; i++) sorted[i] = ord[i].first;
+        WV_HIP(hipMemcpyAsync(c->primes.ptr, sorted.data(), n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
+        size_t b = 0;
+        while (b < n && grid_takes(c, sorted[b], &gc)) {
+            size_t e = b + 1;
+            while (e < n && grid_takes(c, sorted[e], &gk) && gk == gc) e++;
+            WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes) + b, (uint32_t)(e - b), sorted[b],
+                                   as<wv_result>(c->results) + b));
+            b = e;
+        }
+        const uint64_t per = (uint64_t)side_slots(c, c->tb) + side_slots(c, c->te);
+        const size_t step = (size_t)std::max<uint64_t>(1, kMaxBatchSlots / per);
+        for (; b < n; b += step) {
+            const size_t k = std::min(step, n - b);
+            WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes) + b, (uint32_t)k, sorted[b] + 1,
+                                  as<wv_result>(c->results) + b));
+        }
+        std::vector<wv_result> res(n);
+        WV_TRY(results_to_host(c, as<wv_result>(c->results), n, res.data()));
+        for (size_t i = 0; i < n; i++) out[ord[i].second] = res[i];
+        return WV_OK;
+    }
     // batches of at most kMaxBatchSlots (prime, sum) slots, in input order
     const uint64_t per = (uint64_t)side_slots(c, c->tb) + side_slots(c, c->te);
     const size_t step = (size_t)std::max<uint64_t>(1, kMaxBatchSlots / per);

@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <vector>
 
+#include "grid_plan.hpp"
 #include "wv_internal.hpp"
 #include "wv_tables.hpp"
 #include "wvprime.h"
@@ -125,7 +126,8 @@ struct wv_ctx {
     wv::DevBuf base_primes, primes, pr, segs, terms, cnt, off, tiles, scal, partials, seg_pairs, results,
         seg_counts, seg_bits, seg_off, seg_desc, pad_primes, stats_hist, stats_near, coefs, lhsmod, tbl_head,
         tbl_term, tbl_limb, tails, tail_hist, irr_tasks, irr_units, irr_primes, irr_roff, irr_v, irr_fix,
-        irr_counts, irr_pairs, irr_b, irr_e;
+        irr_counts, irr_pairs, irr_b, irr_e, grid_ws;
+    wv::DevBuf ntt_tab[wv::kNttMaxLog + 1];       // twiddle tables per log2 length (grid path)
     // congruence registry: the compiled tables (ids < WV_TABLE_COUNT), then
     // those defined at run time; device copy in tbl_* (TableStore)
     std::vector<wv::TableHead> t_head;
@@ -220,6 +222,17 @@ constexpr double kGraphSearchTerms = 17179869184.0;
 constexpr int kGraphNotTaken = 1;
 int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uint64_t pmax, wv_result *out,
                  size_t *n_out);
+// The grid path (wv_grid.hip) takes primes from this size on when the context
+// has its default congruences and no forced shape, chunk or progress callback.
+// Both paths measured on MI355X, microseconds per prime of a large window,
+// term sums / grid: 4e7 0.69 / 1.00, 1e8 1.45 / 1.42, 1e9 13.2 / 5.2, 1e10 139
+// / 23, 1e11 1295 / 87; of 64 primes alone the grid wins from 2e8 (0.82 / 0.68
+// ms a call) and loses at 1e8 (0.64 / 0.73).
+constexpr uint64_t kGridMinP = 1ull << 27;
+bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g);
+// n primes in [4 * 4^logl, pmax] on the device -> d_out (waits; fills c->stats)
+int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
+                    wv_result *d_out);
 // device address of the fixed scratch array on `device` (current), looked up
 // once per device (wv_static.hip)
 int static_scratch_setup(int device, void **addr);

@@ -1,0 +1,803 @@
+// wv_grid.hip -- both residues of a batch of primes by fast evaluation along
+// arithmetic progressions.
+//
+// Each sum of a congruence (Sections 3 and 5) is cut into blocks of K
+// consecutive s.  With F(x) = prod_{j<K} (x + j) and its Taylor coefficients
+// g_0 .. g_3 (F(x + h) = sum g_k h^k), a block that starts at x enters the
+// sum's pair as P = g_0^d, Q as in sum_core.hpp.  Instead of stepping the g_k
+// from block to block, their values at all block starts x = lo + K t are taken
+// from their values at K + 1 fixed nodes by Lagrange's formula,
+//   g(X) = prod_i (X - Y_i) sum_i u_i / (X - Y_i),
+//   u_i = g(Y_i) / prod_{m != i} (Y_i - Y_m),
+// whose nodes and points both advance by K, so that the sum over i is a
+// convolution of u with 1 / (lo + K n), done exactly by number-theoretic
+// transforms (ntt.hpp).  The factor prod (X - Y_i) is common to g_0 .. g_3 at
+// one point and drops out of c1 / c0.  A sum of len terms costs about
+// len / K^2 transforms of length 2 K instead of len steps: for a prime p about
+// sqrt(p) log p operations per transform-sized share instead of p.
+//
+// Nodes Y_i = -K (K + 1 - i), i = 0 .. K: below every point, so every
+// difference X - Y_i is a positive integer below p (p >= 4 (2 K + 2)^2).
+//
+// Node values (products of K consecutive integers with derivatives) are built
+// by doubling: blocks of k = 255 directly, then from k to 2 k + 1 as
+//   P_{2k+1}(Y) = P_k(Y) P_k(Y + k) (Y + 2 k),
+// where the nodes already known give P_k at Y_t + k and at the next k + 1
+// nodes by the same convolutions (here with the factor prod (X - Y_i)).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "grid_plan.hpp"
+#include "ntt.hpp"
+#include "wave_ops.hpp"
+#include "wv_ctx.hpp"
+
+namespace wv {
+namespace {
+
+constexpr int kBaseK = 255;   // blocks whose node values are multiplied out
+
+__device__ __forceinline__ Fmod fmod_of(uint64_t p) {
+    Fmod f;
+    f.p = (double)p;
+    f.pinv = 1.0 / f.p;
+    return f;
+}
+
+// a^e, e >= 1 the same for the whole wave (scalar control flow)
+__device__ __forceinline__ double f_pow_u(double a, uint64_t e, const Fmod &f) {
+    e = readfirst_u64(e);
+    double r = a;
+    for (int i = 62 - __builtin_clzll(e); i >= 0; i--) {
+        r = f_mulmod(r, r, f);
+        if ((e >> i) & 1) r = f_mulmod(r, a, f);
+    }
+    return r;
+}
+
+// ---------------------------------------------------------------------------
+// plan: shifts per sum
+// ---------------------------------------------------------------------------
+
+// One thread per (prime, sum): the shifts of W blocks its blocks need; the
+// terms of each side added to terms[0] (all) and terms[1] (s^-3 side).
+__global__ void __launch_bounds__(256) k_grid_count(const SegRec *__restrict__ segs, uint64_t nseg, uint64_t K,
+                                                    int logw, uint64_t *__restrict__ cnt,
+                                                    unsigned long long *__restrict__ terms) {
+    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    uint64_t len = 0, len_b = 0;
+    if (i < nseg) {
+        const SegRec s = segs[i];
+        len = s.len;
+        len_b = s.deg == 3 ? s.len : 0;
+        const uint64_t t = s.len / K;
+        cnt[i] = (t + (1ull << logw) - 1) >> logw;
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        len += shfl_xor_u64(len, o);
+        len_b += shfl_xor_u64(len_b, o);
+    }
+    if ((threadIdx.x & 63) == 0 && len) {
+        atomicAdd(&terms[0], (unsigned long long)len);
+        if (len_b) atomicAdd(&terms[1], (unsigned long long)len_b);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// inverses along a progression
+// ---------------------------------------------------------------------------
+
+// inv[e] = 1 / (lo + K n) mod p for n = 0 .. (R + 1) W - 1 of every sum with R
+// shifts, at (off[slot] + slot) W + n.  A wave takes 64 C consecutive entries
+// of one sum, each lane C of them: products up, one Fermat inverse, products
+// down.
+template <int C>
+__global__ void __launch_bounds__(256) k_grid_inv(const SegRec *__restrict__ segs, const uint64_t *__restrict__ off,
+                                                  uint32_t nseg, const PrimeRec *__restrict__ pr, uint64_t K, int logw,
+                                                  double *__restrict__ inv) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t units = ((off[nseg] + nseg) << logw) / (64 * C);
+    const uint64_t nwaves = (uint64_t)gridDim.x * 4;
+    for (uint64_t u0 = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6); u0 < units; u0 += nwaves) {
+        const uint64_t u = readfirst_u64(u0);
+        const uint64_t e0 = u * (64 * C), g = e0 >> logw;
+        uint32_t lo = 0, hi = nseg;   // the slot whose entries hold granule g
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (off[mid] + mid <= g) lo = mid;
+            else hi = mid;
+        }
+        if (off[lo + 1] == off[lo]) continue;   // no shift: entries never read
+        const SegRec s = segs[lo];
+        const uint64_t p = pr[s.prime].p;
+        const Fmod f = fmod_of(p);
+        const uint64_t n0 = e0 - ((off[lo] + lo) << logw);
+        const double a0 = (double)(s.lo + K * (n0 + lane)), step = (double)(64 * K);
+        double pre[C];
+        double acc = 1.0;
+WV_UNROLL
+        for (int c = 0; c < C; c++) {
+            pre[c] = acc;
+            acc = f_mulmod(acc, fma((double)c, step, a0), f);   // the entry, an integer below p
+        }
+        double r = f_pow_u(acc, p - 2, f);
+WV_UNROLL
+        for (int c = C - 1; c >= 0; c--) {
+            inv[e0 + (uint64_t)c * 64 + lane] = f_mulmod(r, pre[c], f);
+            r = f_mulmod(r, fma((double)c, step, a0), f);
+        }
+    }
+}
+
+// Prefix products of get(0 .. 256 c - 1) over a workgroup of 256 threads, thread
+// t holding entries [t c, t c + c): put(i, A_i, 1 / A_i, A_{i-1}) for every i.
+template <class Get, class Put>
+__device__ __forceinline__ void prefix_inverses(int c, const Fmod &f, uint64_t p, double *__restrict__ s, Get get,
+                                                Put put) {
+    const int tid = threadIdx.x;
+    double prod = 1.0;
+    for (int i = 0; i < c; i++) prod = f_mulmod(prod, get(tid * c + i), f);
+    s[tid] = prod;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+        const double v = tid >= o ? s[tid - o] : 1.0;
+        __syncthreads();
+        s[tid] = f_mulmod(s[tid], v, f);
+        __syncthreads();
+    }
+    const double excl = tid ? s[tid - 1] : 1.0;
+    double r = f_pow_u(s[tid], p - 2, f);   // inverse of the prefix up to this thread's last entry
+    // downwards: A_{i-1} = A_i / a_i would need inverses, so A is kept per entry
+    double a[32];
+WV_UNROLL
+    for (int i = 0; i < 32; i++) {
+        if (i < c) a[i] = f_mulmod(i ? a[i ? i - 1 : 0] : excl, get(tid * c + i), f);
+    }
+WV_UNROLL
+    for (int i = 31; i >= 0; i--) {
+        if (i < c) {
+            put(tid * c + i, a[i], r, i ? a[i ? i - 1 : 0] : excl);
+            r = f_mulmod(r, get(tid * c + i), f);
+        }
+    }
+}
+
+// Factorials and their inverses mod p up to K (a workgroup per prime):
+// fact[i], fact[(K + 1) + i].
+__global__ void __launch_bounds__(256) k_grid_fact(const PrimeRec *__restrict__ pr, uint32_t K, double *__restrict__ fact) {
+    __shared__ double s[256];
+    const uint64_t p = pr[blockIdx.x].p;
+    const Fmod f = fmod_of(p);
+    double *F = fact + (size_t)blockIdx.x * 2 * (K + 1);
+    prefix_inverses((int)(K + 1) / 256, f, p, s, [](int i) { return i ? (double)i : 1.0; },
+                    [&](int i, double A, double iA, double) {
+                        F[i] = A;
+                        F[K + 1 + i] = iA;
+                    });
+}
+
+// Level arrays of one doubling step (blocks of k terms, L = 2 (k + 1)): for
+// shift s of prime i, a(n) = K n (s = 0: the next k + 1 nodes), k + K (n - L/2)
+// (s = 1: the nodes moved by k) or k + K n (s = 2: both); beta[n] = 1 / a(n),
+// A[n] = prod_{m <= n} a(m) and iA its inverse (a(0) counts as 1).
+// cst[i] = K^-k.
+__global__ void __launch_bounds__(256) k_grid_level(const PrimeRec *__restrict__ pr, uint32_t K, uint32_t k,
+                                                    double *__restrict__ beta, double *__restrict__ A,
+                                                    double *__restrict__ iA, double *__restrict__ cst) {
+    __shared__ double sc[256];
+    const uint32_t i = blockIdx.x / 3, sh = blockIdx.x - 3 * i, L = 2 * (k + 1);
+    const uint64_t p = pr[i].p;
+    const Fmod f = fmod_of(p);
+    const double Kd = (double)K;
+    const double a0 = sh == 0 ? 0.0 : (sh == 1 ? (double)k - Kd * (double)(k + 1) : (double)k);
+    const size_t at = (size_t)blockIdx.x * L;
+    prefix_inverses((int)L / 256, f, p, sc, [&](int n) { return n ? fma((double)n, Kd, a0) : 1.0; },
+                    [&](int n, double a, double ia, double prev) {
+                        beta[at + n] = f_mulmod(ia, prev, f);
+                        A[at + n] = a;
+                        iA[at + n] = ia;
+                    });
+    if (sh == 0) {
+        const double c = f_pow_u(f_pow_u(Kd, p - 2, f), k, f);
+        if (threadIdx.x == 0) cst[i] = c;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// node values
+// ---------------------------------------------------------------------------
+
+// Values of g_0 .. g_3 of blocks of kBaseK terms at the first kBaseK + 1 nodes,
+// multiplied out (one thread per node, one workgroup per prime).
+__global__ void __launch_bounds__(256) k_grid_base(const PrimeRec *__restrict__ pr, uint32_t K, double *__restrict__ node) {
+    const uint64_t p = pr[blockIdx.x].p;
+    const Fmod f = fmod_of(p);
+    const int t = threadIdx.x;
+    const double y = -(double)K * (double)(K + 1 - t);
+    double g0 = 1.0, g1 = 0.0, g2 = 0.0, g3 = 0.0;
+    for (int j = 0; j < kBaseK; j++) {
+        const double a = y + (double)j;   // |a| <= K (K + 1) < p
+        g3 = f_mulmod(g3, a, f) + g2;     // |g_k| < (0.574 + 0.574 k) p
+        g2 = f_mulmod(g2, a, f) + g1;
+        g1 = f_mulmod(g1, a, f) + g0;
+        g0 = f_mulmod(g0, a, f);
+    }
+    double *o = node + (size_t)blockIdx.x * 4 * (kBaseK + 1) + t;
+    o[0] = f_reduce(g0, f);
+    o[kBaseK + 1] = f_reduce(g1, f);
+    o[2 * (kBaseK + 1)] = f_reduce(g2, f);
+    o[3 * (kBaseK + 1)] = f_reduce(g3, f);
+}
+
+// u_i / L of one value vector at the k + 1 = L/2 nodes, transformed (a
+// workgroup per prime, vector and modulus): out[((prime 4 + j) 2 + q) L + ...]
+// in the transform's own layout.
+template <int LOGL>
+__global__ void __launch_bounds__(NttShape<LOGL>::T, 4) k_grid_fwd(const PrimeRec *__restrict__ pr,
+                                                                   const double *__restrict__ node,
+                                                                   const double *__restrict__ fact, uint32_t K,
+                                                                   const double *__restrict__ tab,
+                                                                   double *__restrict__ out) {
+    using S = NttShape<LOGL>;
+    constexpr int E = S::E, T = S::T, L = S::L;
+    __shared__ NttLds<LOGL> lds;
+    const int tid = threadIdx.x;
+    const uint32_t i = blockIdx.x >> 3, j = (blockIdx.x >> 1) & 3, q = blockIdx.x & 1;
+    const Fmod fp = fmod_of(pr[i].p);
+    const Fmod f = ntt_mod(q);
+    const VecBuf tb = vec_buf(tab, 2 * S::STRIDE);
+    const VecBuf v = vec_buf(node + ((size_t)i * 4 + j) * (L / 2), L / 2);
+    const VecBuf iF = vec_buf(fact + (size_t)i * 2 * (K + 1) + (K + 1), K + 1);
+    double x[E];
+WV_UNROLL
+    for (int e = 0; e < E / 2; e++) {
+        // n = tid + T e: (-1)^(k-n) / (n! (k-n)!), k = L/2 - 1 odd, T even
+        const double u = f_mulmod(f_mulmod(vec_load(v, tid, T * e), vec_load(iF, tid, T * e), fp),
+                                  vec_load(iF, T - 1 - tid, L / 2 - T - T * e), fp);
+        x[e] = (tid & 1) ? u : -u;
+        x[E / 2 + e] = 0.0;
+    }
+    ntt_lds_tables<LOGL>(lds, tb, (int)q, tid);
+    ntt_forward<LOGL>(x, lds, tb, (int)q, f, tid);
+    // 1 / L mod q = -(q - 1) / L
+    const double li = -(f.p - 1.0) / (double)L;
+    const VecBuf o = vec_buf(out + (((size_t)i * 4 + j) * 2 + q) * L, L);
+WV_UNROLL
+    for (int m = 0; m < E; m++) vec_store(o, tid, m * T, f_mulmod(x[m], li, f));
+}
+
+// ---------------------------------------------------------------------------
+// values at the block starts
+// ---------------------------------------------------------------------------
+
+struct ShiftArgs {
+    const PrimeRec *pr;
+    const double *beta;       // kernel entries
+    const double *uhat;       // transformed node vectors
+    const double *tab;
+    double *out;              // level: residues; sums: scratch of each workgroup
+    const SegRec *segs;       // sums only, from here
+    const uint64_t *off;
+    Pair *pairs;
+    unsigned long long *counters;   // 8, one per XCD's share, zero at launch
+    uint32_t nseg, K;
+};
+
+// A vector of length L, every load requested before the first is used.
+template <int LOGL>
+__device__ __forceinline__ void load_vec(double (&x)[NttShape<LOGL>::E], const double *base, int tid) {
+    using S = NttShape<LOGL>;
+    const VecBuf b = vec_buf(base, S::L);
+WV_UNROLL
+    for (int e = 0; e < S::E; e++) x[e] = vec_load(b, tid, e * S::T);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// One shift of a doubling step: residues mod q of every value vector at the
+// L/2 points, out[((item 4 + j) 2 + q) L/2 + t]; a workgroup per (item =
+// prime 3 + shift, modulus).
+template <int LOGL>
+__global__ void __launch_bounds__(NttShape<LOGL>::T, 4) k_grid_level_shift(ShiftArgs A) {
+    using S = NttShape<LOGL>;
+    constexpr int E = S::E, T = S::T, L = S::L;
+    __shared__ NttLds<LOGL> lds;
+    const int tid = threadIdx.x;
+    const uint32_t item = blockIdx.x >> 1, q = blockIdx.x & 1, i = item / 3;
+    const Fmod f = ntt_mod(q);
+    const VecBuf tab = vec_buf(A.tab, 2 * S::STRIDE);
+    double w[E], x[E], t1[E];
+    load_vec<LOGL>(w, A.beta + (size_t)item * L, tid);
+    ntt_lds_tables<LOGL>(lds, tab, (int)q, tid);
+    const double *uh = A.uhat + ((size_t)i * 8 + q) * L;   // vector j at 2 j L
+    ntt_forward<LOGL>(w, lds, tab, (int)q, f, tid);
+    twiddle1_load<LOGL>(t1, tab, ntt_inverse_tw1<LOGL>((int)q), tid);
+WV_NO_UNROLL
+    for (int j = 0; j < 4; j++) {
+        load_vec<LOGL>(x, uh + (size_t)(2 * j) * L, tid);
+        mulmod_range<kNttGroup, 0, E>(x, w, f);
+        ntt_inverse<LOGL>(x, t1, lds, (int)q, f, tid);
+        const VecBuf o = vec_buf(A.out + (((size_t)item * 4 + j) * 2 + q) * (L / 2), L / 2);
+WV_UNROLL
+        for (int e = 0; e < E / 2; e++) vec_store(o, tid, e * T, f_reduce(x[E / 2 + e], f));
+    }
+}
+
+// What bounds this kernel: issue of f64 operations (about 66 per element of a
+// transform, 0.58 of the issue slots at L = 2^14), then the vector loads of
+// node vectors, twiddles and scratch between them.  One transform at a time
+// stays in a workgroup's registers (16 values a thread, four waves per SIMD);
+// at L = 2^14 a workgroup fills a CU.  1e11 window of 310 primes: 24.6 ms of
+// 27.3 ms a call; the term sums took 402 ms.
+//
+// The shifts of every sum (persistent; the items split evenly over the eight
+// XCDs, taken one by one, so that neighbouring items, which share a prime's
+// node vectors, meet in one L2): values of g_0 .. g_d at the W block starts, folded into one pair.
+template <int LOGL>
+__global__ void __launch_bounds__(NttShape<LOGL>::T, 4) k_grid_shift(ShiftArgs A) {
+    using S = NttShape<LOGL>;
+    constexpr int E = S::E, T = S::T, L = S::L, W = L / 2;
+    __shared__ NttLds<LOGL> lds;
+    __shared__ unsigned long long ticket;
+    const int tid = threadIdx.x;
+    const uint64_t total = A.off[A.nseg];
+    const VecBuf tab = vec_buf(A.tab, 2 * S::STRIDE);
+    const VecBuf scr = vec_buf(A.out + (size_t)blockIdx.x * 4 * W, 4 * W);
+    // the items of this workgroup's XCD, then those the others have left
+    uint32_t part = 0;
+    while (part < 8) {
+        const uint32_t X = (blockIdx.x + part) & 7;
+        __syncthreads();   // LDS free
+        if (tid == 0) ticket = atomicAdd(&A.counters[X], 1ull);
+        __syncthreads();
+        const uint64_t item = total * X / 8 + readfirst_u64(ticket);
+        if (item >= total * (X + 1) / 8) {
+            part++;
+            continue;
+        }
+        const uint32_t slot = __builtin_amdgcn_readfirstlane(find_seg(A.off, A.nseg, item));
+        const uint64_t first = readfirst_u64(A.off[slot]), sigma = item - first;
+        const uint32_t prime = __builtin_amdgcn_readfirstlane(A.segs[slot].prime);
+        const int np = __builtin_amdgcn_readfirstlane(A.segs[slot].deg) == 3 ? 4 : 3;
+        // block starts from this shift's first
+        const uint32_t blocks = (uint32_t)min(readfirst_u64(A.segs[slot].len / A.K - sigma * W), (uint64_t)W);
+        const Fmod fp = fmod_of(readfirst_u64(A.pr[prime].p));
+        const double q1p = f_reduce((double)kNttQ[0], fp);   // q1 mod p, balanced
+        const double *beta = A.beta + (first + slot + sigma) * W;
+        const double *uh = A.uhat + (size_t)prime * 8 * L;   // vector j modulo q at (2 j + q) L
+        double w[E], x[E], t1[E];
+WV_NO_UNROLL
+        for (int q = 0; q < 2; q++) {
+            const Fmod f = ntt_mod(q);
+            load_vec<LOGL>(w, beta, tid);
+            ntt_lds_tables<LOGL>(lds, tab, q, tid);
+            ntt_forward<LOGL>(w, lds, tab, q, f, tid);
+            twiddle1_load<LOGL>(t1, tab, ntt_inverse_tw1<LOGL>(q), tid);
+WV_NO_UNROLL
+            for (int j = 0; j < np; j++) {
+                load_vec<LOGL>(x, uh + (size_t)(2 * j + q) * L, tid);
+                mulmod_range<kNttGroup, 0, E>(x, w, f);
+                ntt_inverse<LOGL>(x, t1, lds, q, f, tid);
+                const int o = j * W;
+                if (q == 0) {
+WV_UNROLL
+                    for (int e = 0; e < E / 2; e++) vec_store(scr, tid, o + e * T, f_reduce(x[E / 2 + e], f));
+                } else {
+                    double r[E / 2];
+WV_UNROLL
+                    for (int e = 0; e < E / 2; e++) r[e] = vec_load(scr, tid, o + e * T);
+                    __builtin_amdgcn_sched_barrier(0);
+WV_UNROLL
+                    for (int e = 0; e < E / 2; e++)
+                        vec_store(scr, tid, o + e * T, ntt_crt(r[e], x[E / 2 + e], kNttQ1Inv, q1p, f, fp));
+                }
+            }
+        }
+        double a0 = 1.0, a1 = 0.0;
+        // four values of every vector at a time (g_3 is read for s^-2 sums
+        // too, where it is whatever the scratch held, and not used)
+        constexpr int G = E / 2 < 4 ? E / 2 : 4;
+WV_NO_UNROLL
+        for (int e0 = 0; e0 < E / 2; e0 += G) {
+            if ((uint32_t)(T * e0) >= blocks) break;
+            double v[4][G];
+WV_UNROLL
+            for (int e = 0; e < G; e++)
+WV_UNROLL
+                for (int j = 0; j < 4; j++) v[j][e] = vec_load(scr, tid, j * W + (e0 + e) * T);
+            __builtin_amdgcn_sched_barrier(0);
+WV_UNROLL
+            for (int e = 0; e < G; e++) {
+                if ((uint32_t)(tid + T * (e0 + e)) >= blocks) break;
+                const double r0 = v[0][e], r1 = v[1][e], r2 = v[2][e], r3 = v[3][e];
+                double P, Q;
+                if (np == 3) {
+                    P = f_mulmod(r0, r0, fp);
+                    const double u = f_mulmod(r0, r2, fp);
+                    Q = f_mulmod(r1, r1, fp) - (u + u);
+                } else {
+                    const double sq = f_mulmod(r0, r0, fp);
+                    P = f_mulmod(sq, r0, fp);
+                    const double u = fma(f_mulmod(r0, r2, fp), -3.0, f_mulmod(r1, r1, fp));
+                    Q = fma(f_mulmod(r3, sq, fp), 3.0, f_mulmod(r1, u, fp));
+                }
+                a1 = f_mulmod(a0, Q, fp) + f_mulmod(a1, P, fp);
+                a0 = f_mulmod(a0, P, fp);
+            }
+        }
+        const Mont m = mont_of(A.pr[prime]);
+        uint64_t c0 = f_canon(a0, fp), c1 = f_canon(a1, fp);
+        wave_pair_reduce(c0, c1, m);
+        Pair *sp = reinterpret_cast<Pair *>(lds.v);
+        __syncthreads();
+        if ((tid & 63) == 0) sp[tid >> 6] = Pair{c0, c1};
+        __syncthreads();
+        if (tid == 0) {
+            for (int v = 1; v < T / 64; v++) pair_mul(c0, c1, sp[v].c0, sp[v].c1, m);
+            A.pairs[item] = Pair{c0, c1};
+        }
+    }
+}
+
+// Node values of the next doubling step: P_{2k+1} at 2 (k + 1) nodes from P_k at
+// the first k + 1 (node), at the next ones (shift 0) and moved by k (shifts 1,
+// 2).  One thread per (prime, node).
+__global__ void __launch_bounds__(256) k_grid_combine(const PrimeRec *__restrict__ pr, uint32_t n, uint32_t K, uint32_t k,
+                                                      const double *__restrict__ node, const double *__restrict__ res,
+                                                      const double *__restrict__ A, const double *__restrict__ iA,
+                                                      const double *__restrict__ cst, double *__restrict__ next) {
+    const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t h = k + 1, L = 2 * h;
+    if (g >= (uint64_t)n * L) return;
+    const uint32_t i = (uint32_t)(g / L), t = (uint32_t)(g - (uint64_t)i * L);
+    const Fmod fp = fmod_of(pr[i].p);
+    const Fmod f2 = ntt_mod(1);
+    const double q1p = f_reduce((double)kNttQ[0], fp);
+    const uint32_t tt = t < h ? t : t - h;
+    // values of shift s at point tt, times prod (X - Y_i) K^-k
+    auto shifted = [&](uint32_t s, double (&v)[4]) {
+        const size_t item = (size_t)i * 3 + s;
+        const double pi = f_mulmod(f_mulmod(A[item * L + tt + h], iA[item * L + tt], fp), cst[i], fp);
+        for (int j = 0; j < 4; j++) {
+            const double r1 = res[((item * 4 + j) * 2) * h + tt], r2 = res[((item * 4 + j) * 2 + 1) * h + tt];
+            v[j] = f_mulmod(ntt_crt(r1, r2, kNttQ1Inv, q1p, f2, fp), pi, fp);
+        }
+    };
+    double x[4], y[4];
+    if (t < h) {
+        for (int j = 0; j < 4; j++) x[j] = node[((size_t)i * 4 + j) * h + t];
+        shifted(1, y);
+    } else {
+        shifted(0, x);
+        shifted(2, y);
+    }
+    double z[4];
+    z[0] = f_mulmod(x[0], y[0], fp);
+    z[1] = f_mulmod(x[0], y[1], fp) + f_mulmod(x[1], y[0], fp);
+    z[2] = f_mulmod(x[0], y[2], fp) + f_mulmod(x[1], y[1], fp) + f_mulmod(x[2], y[0], fp);
+    z[3] = f_mulmod(x[0], y[3], fp) + f_mulmod(x[1], y[2], fp) + f_mulmod(x[2], y[1], fp) + f_mulmod(x[3], y[0], fp);
+    const double last = (double)(2 * k) - (double)K * (double)(K + 1 - t);   // Y_t + 2 k
+    double *o = next + (size_t)i * 4 * L + t;
+    o[0] = f_reduce(f_mulmod(z[0], last, fp), fp);
+    for (int j = 1; j < 4; j++) o[(size_t)j * L] = f_reduce(f_mulmod(z[j], last, fp) + z[j - 1], fp);
+}
+
+// Every (prime, sum): the pairs of its shifts joined with the terms after its
+// last block (NW waves per sum).
+template <int NW>
+__global__ void __launch_bounds__(256) k_grid_join(const SegRec *__restrict__ segs, const uint64_t *__restrict__ off,
+                                                   uint64_t nseg, const PrimeRec *__restrict__ pr,
+                                                   const Pair *__restrict__ pairs, uint32_t K,
+                                                   Pair *__restrict__ seg_pairs) {
+    __shared__ Pair part[4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint64_t j = NW == 1 ? (uint64_t)blockIdx.x * 4 + wave : blockIdx.x;
+    const bool live = j < nseg;   // NW == 4: the grid has a workgroup per sum
+    uint64_t c0 = 1, c1 = 0;
+    Mont m;
+    if (live) {
+        const SegRec s = segs[j];
+        const PrimeRec P = pr[s.prime];
+        m = mont_of(P);
+        const Fmod f = fmod_of(P.p);
+        const int me = NW == 1 ? lane : (int)threadIdx.x;
+        double a0 = 1.0, a1 = 0.0;
+        const uint64_t done = s.len / K * K;
+        for (uint64_t t = done + me; t < s.len; t += 64 * NW) {
+            const double v = (double)(s.lo + t);
+            const double v2 = f_mulmod(v, v, f);
+            const double u = s.deg == 3 ? f_mulmod(v2, v, f) : v2;
+            a1 = f_mulmod(a1, u, f) + a0;   // |a1| < 1.15 p
+            a0 = f_mulmod(a0, u, f);
+        }
+        c0 = f_canon(a0, f);
+        c1 = f_canon(a1, f);
+        for (uint64_t i = off[j] + me; i < off[j + 1]; i += 64 * NW) pair_mul(c0, c1, pairs[i].c0, pairs[i].c1, m);
+        wave_pair_reduce(c0, c1, m);
+        if (NW == 1 && lane == 0) seg_pairs[j] = Pair{c0, c1};
+    }
+    if (NW > 1) {
+        if (lane == 0) part[wave] = Pair{c0, c1};
+        __syncthreads();
+        if (threadIdx.x == 0 && live) {
+            for (int v = 1; v < NW; v++) pair_mul(c0, c1, part[v].c0, part[v].c1, m);
+            seg_pairs[j] = Pair{c0, c1};
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+
+uint64_t mulmod_q(uint64_t a, uint64_t b, uint64_t q) { return (uint64_t)((unsigned __int128)a * b % q); }
+
+uint64_t powmod_q(uint64_t a, uint64_t e, uint64_t q) {
+    uint64_t r = 1;
+    for (; e; e >>= 1, a = mulmod_q(a, a, q))
+        if (e & 1) r = mulmod_q(r, a, q);
+    return r;
+}
+
+double balanced(uint64_t v, uint64_t q) { return v > q / 2 ? -(double)(q - v) : (double)v; }
+
+uint32_t bitrev(uint32_t v, int bits) {
+    uint32_t r = 0;
+    for (int i = 0; i < bits; i++) r |= ((v >> i) & 1) << (bits - 1 - i);
+    return r;
+}
+
+template <class F>
+int with_shape(int logl, F &&fn) {
+    switch (logl) {
+    case 9: return fn(std::integral_constant<int, 9>{});
+    case 10: return fn(std::integral_constant<int, 10>{});
+    case 11: return fn(std::integral_constant<int, 11>{});
+    case 12: return fn(std::integral_constant<int, 12>{});
+    case 13: return fn(std::integral_constant<int, 13>{});
+    case 14: return fn(std::integral_constant<int, 14>{});
+    default: return WV_EINVAL;
+    }
+}
+
+// Twiddle tables of one length (both moduli), uploaded once per context.
+int ntt_tables(wv_ctx *c, int logl) {
+    DevBuf &buf = c->ntt_tab[logl];
+    if (buf.ptr) return WV_OK;
+    const uint64_t L = 1ull << logl;
+    std::vector<double> h;
+    std::vector<uint64_t> pw(L);
+    const int rc = with_shape(logl, [&](auto s) -> int {
+        using S = NttShape<decltype(s)::value>;
+        h.resize(2 * S::STRIDE);
+        for (int q = 0; q < 2; q++) {
+            const uint64_t Q = kNttQ[q], w = powmod_q(kNttRoot[q], (1ull << 17) / L, Q);
+            pw[0] = 1;
+            for (uint64_t i = 1; i < L; i++) pw[i] = mulmod_q(pw[i - 1], w, Q);
+            double *t = h.data() + (size_t)q * S::STRIDE;
+            for (int k = 1; k <= S::NT; k++)
+                for (uint64_t i = 0; i < (uint64_t)S::E; i++)
+                    for (uint64_t x = 0; x < (uint64_t)S::N(k); x++) {
+                        // root of order N(k - 1) to the power x bitrev(i)
+                        const uint64_t n = (uint64_t)S::N(k - 1), e = bitrev((uint32_t)i, S::LE) * x % n;
+                        t[S::table(k) + i * S::N(k) + x] = balanced(pw[L / n * e], Q);
+                        t[S::DIR + S::table(k) + i * S::N(k) + x] = balanced(pw[L / n * ((n - e) % n)], Q);
+                    }
+        }
+        return WV_OK;
+    });
+    WV_TRY(rc);
+    WV_TRY(ensure(c, buf, h.size() * sizeof(double)));
+    const hipError_t e = hipMemcpyAsync(buf.ptr, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
+    const hipError_t e2 = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess || e2 != hipSuccess) {
+        (void)hipFree(buf.ptr);
+        buf = DevBuf{};
+        return WV_EHIP;
+    }
+    return WV_OK;
+}
+
+// Bytes of device memory a batch of n primes needs besides the plan's records.
+struct GridLayout {
+    uint64_t items;   // bound on the shifts
+    size_t node0, node1, fact, beta, A, iA, cst, uhat, res, inv, pairs, scratch, counters, total;
+};
+
+size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+GridLayout grid_layout(const GridClass &g, uint64_t n, uint64_t pmax, unsigned blocks) {
+    const uint64_t L = 1ull << g.logl, W = L / 2;
+    const uint64_t nseg = n * (kTables[g.tb].n + kTables[g.te].n);
+    GridLayout y;
+    y.items = n * (grid_shifts(kTables[g.tb], (double)pmax, g.logl) + grid_shifts(kTables[g.te], (double)pmax, g.logl));
+    size_t at = 0;
+    auto take = [&](size_t &where, size_t doubles) {
+        where = at;
+        at += up256(doubles * sizeof(double));
+    };
+    take(y.node0, n * 4 * W);
+    take(y.node1, n * 4 * W);
+    take(y.fact, n * 2 * W);
+    take(y.beta, n * 3 * W);
+    take(y.A, n * 3 * W);
+    take(y.iA, n * 3 * W);
+    take(y.cst, n);
+    take(y.uhat, n * 8 * L);
+    take(y.res, n * 12 * W);
+    take(y.inv, (y.items + nseg) * W);
+    take(y.pairs, y.items * 2);
+    take(y.scratch, (size_t)blocks * 4 * W);
+    take(y.counters, 8);
+    y.total = at;
+    return y;
+}
+
+constexpr size_t kGridBytes = (size_t)8 << 30;   // workspace of one sub-batch, at most
+
+// Workgroups of the persistent kernel: four waves per SIMD of 128 registers.
+unsigned grid_blocks(const wv_ctx *c, int logl) {
+    const int T = (1 << logl) / (logl >= 10 ? 16 : 8);
+    return (unsigned)std::max(8, c->num_cus * (1024 / T) / 8 * 8);
+}
+
+template <int C>
+void launch_inv(hipStream_t st, unsigned grid, const SegRec *segs, const uint64_t *off, uint32_t nseg,
+                const PrimeRec *pr, uint64_t K, int logw, double *inv) {
+    hipLaunchKernelGGL(k_grid_inv<C>, dim3(grid), dim3(256), 0, st, segs, off, nseg, pr, K, logw, inv);
+}
+
+// One sub-batch of n primes, enqueued on the context's stream: results into
+// d_out, terms summed added to terms (2 words on the device).
+int grid_sub(wv_ctx *c, const GridClass &g, const GridLayout &y, const uint64_t *d_primes, uint32_t n,
+             unsigned long long *terms, wv_result *d_out) {
+    hipStream_t st = c->stream;
+    const uint32_t K = (uint32_t)grid_k(g.logl);
+    const int logw = g.logl - 1;
+    const int nB = kTables[g.tb].n, nE = kTables[g.te].n;
+    const uint64_t nseg = (uint64_t)n * (nB + nE);
+    if (nseg >= (1ull << 31) || (uint64_t)n * (K + 1) >= (1ull << 31)) return WV_EINVAL;
+    PrimeRec *pr = as<PrimeRec>(c->pr);
+    SegRec *segs = as<SegRec>(c->segs);
+    uint64_t *off = as<uint64_t>(c->off);
+    char *ws = as<char>(c->grid_ws);
+    auto at = [&](size_t o) { return reinterpret_cast<double *>(ws + o); };
+    WV_HIP(launch_plan(st, d_primes, n, g.tb, g.te, g.tb, g.te, nB, nE, table_store(c), pr, segs,
+                       as<uint64_t>(c->terms), as<uint64_t>(c->coefs), as<uint64_t>(c->lhsmod), 0));
+    hipLaunchKernelGGL(k_grid_count, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, st, segs, nseg, (uint64_t)K, logw,
+                       as<uint64_t>(c->cnt), terms);
+    WV_HIP(launch_scan(st, as<uint64_t>(c->cnt), nseg, off, as<uint64_t>(c->tiles)));
+    const unsigned inv_grid = (unsigned)c->num_cus * 8;
+    double *inv = at(y.inv);
+    switch (logw) {
+    case 8: launch_inv<4>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
+    case 9: launch_inv<8>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
+    case 10: launch_inv<16>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
+    default: launch_inv<32>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
+    }
+    hipLaunchKernelGGL(k_grid_fact, dim3(n), dim3(256), 0, st, pr, K, at(y.fact));
+    hipLaunchKernelGGL(k_grid_base, dim3(n), dim3(256), 0, st, pr, K, at(y.node0));
+    double *node = at(y.node0), *next = at(y.node1);
+    auto fwd = [&](int logl) -> int {
+        return with_shape(logl, [&](auto s) -> int {
+            constexpr int LG = decltype(s)::value;
+            hipLaunchKernelGGL(k_grid_fwd<LG>, dim3(n * 8), dim3(NttShape<LG>::T), 0, st, pr, node, at(y.fact), K,
+                               as<double>(c->ntt_tab[LG]), at(y.uhat));
+            return WV_OK;
+        });
+    };
+    for (int l = kNttMinLog; l < g.logl; l++) {
+        const uint32_t k = (uint32_t)grid_k(l);
+        hipLaunchKernelGGL(k_grid_level, dim3(3 * n), dim3(256), 0, st, pr, K, k, at(y.beta), at(y.A), at(y.iA),
+                           at(y.cst));
+        WV_TRY(fwd(l));
+        WV_TRY(with_shape(l, [&](auto s) -> int {
+            constexpr int LG = decltype(s)::value;
+            ShiftArgs a{};
+            a.beta = at(y.beta);
+            a.uhat = at(y.uhat);
+            a.tab = as<double>(c->ntt_tab[LG]);
+            a.out = at(y.res);
+            hipLaunchKernelGGL(k_grid_level_shift<LG>, dim3(6 * n), dim3(NttShape<LG>::T), 0, st, a);
+            return WV_OK;
+        }));
+        const uint64_t points = (uint64_t)n * 2 * (k + 1);
+        hipLaunchKernelGGL(k_grid_combine, dim3((unsigned)((points + 255) / 256)), dim3(256), 0, st, pr, n, K, k, node,
+                           at(y.res), at(y.A), at(y.iA), at(y.cst), next);
+        std::swap(node, next);
+    }
+    WV_TRY(fwd(g.logl));
+    WV_HIP(launch_set_u64(st, reinterpret_cast<uint64_t *>(at(y.counters)), 8, 0));
+    WV_TRY(with_shape(g.logl, [&](auto s) -> int {
+        constexpr int LG = decltype(s)::value;
+        ShiftArgs a{};
+        a.pr = pr;
+        a.beta = inv;
+        a.uhat = at(y.uhat);
+        a.tab = as<double>(c->ntt_tab[LG]);
+        a.out = at(y.scratch);
+        a.segs = segs;
+        a.off = off;
+        a.pairs = reinterpret_cast<Pair *>(at(y.pairs));
+        a.counters = reinterpret_cast<unsigned long long *>(at(y.counters));
+        a.nseg = (uint32_t)nseg;
+        a.K = K;
+        hipLaunchKernelGGL(k_grid_shift<LG>, dim3(grid_blocks(c, LG)), dim3(NttShape<LG>::T), 0, st, a);
+        return WV_OK;
+    }));
+    const Pair *pairs = reinterpret_cast<const Pair *>(at(y.pairs));
+    if (K < 2047)
+        hipLaunchKernelGGL(k_grid_join<1>, dim3((unsigned)((nseg + 3) / 4)), dim3(256), 0, st, segs, off, nseg, pr, pairs,
+                           K, as<Pair>(c->seg_pairs));
+    else
+        hipLaunchKernelGGL(k_grid_join<4>, dim3((unsigned)nseg), dim3(256), 0, st, segs, off, nseg, pr, pairs, K,
+                           as<Pair>(c->seg_pairs));
+    WV_HIP(hipGetLastError());
+    WV_HIP(launch_finalize(st, table_store(c), pr, as<Pair>(c->seg_pairs), as<uint64_t>(c->coefs),
+                           as<uint64_t>(c->lhsmod), n, nB, nE, d_out, nullptr));
+    return WV_OK;
+}
+
+}  // namespace
+
+// The path serves contexts with the default congruences, whose residues any
+// printed congruence gives; a table the caller chose or defined, a forced shape
+// or chunk, and a progress callback (called between term-sum launches) keep the
+// term sums.
+bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g) {
+    if (c->tb != WV_TABLE_BB30 || c->te != WV_TABLE_EE33 || c->shape_forced || c->chunk_cfg || c->progress) return false;
+    if (p < kGridMinP) return false;
+    *g = grid_class(p);
+    return true;
+}
+
+int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
+                    wv_result *d_out) {
+    if (n == 0) return WV_OK;
+    hipStream_t st = c->stream;
+    for (int l = kNttMinLog; l <= g.logl; l++) WV_TRY(ntt_tables(c, l));
+    const unsigned blocks = grid_blocks(c, g.logl);
+    // sub-batches within the workspace bound
+    const size_t one = grid_layout(g, 64, pmax, 0).total / 64 + 1;
+    uint32_t step = (uint32_t)std::min<uint64_t>(n, std::max<uint64_t>(1, kGridBytes / one));
+    step = std::min<uint32_t>(step, 1u << 16);
+    const uint32_t parts = (n + step - 1) / step;
+    step = (n + parts - 1) / parts;
+    const GridLayout y = grid_layout(g, step, pmax, blocks);
+    BatchShape sh{};
+    sh.tb = g.tb;
+    sh.te = g.te;
+    sh.n = step;
+    sh.nB = kTables[g.tb].n;
+    sh.nE = kTables[g.te].n;
+    sh.nseg = (uint64_t)step * (sh.nB + sh.nE);
+    sh.cap = 1;
+    WV_TRY(prepare(c, sh));
+    WV_TRY(ensure(c, c->grid_ws, y.total));
+    auto *terms = as<unsigned long long>(c->scal);
+    WV_HIP(hipEventRecord(c->ev[EV_PLAN0], st));
+    WV_HIP(launch_set_u64(st, as<uint64_t>(c->scal), 8, 0));
+    for (uint32_t b = 0; b < n; b += step)
+        WV_TRY(grid_sub(c, g, y, d_primes + b, std::min(step, n - b), terms, d_out + b));
+    WV_HIP(hipEventRecord(c->ev[EV_FINAL], st));
+    uint64_t host[2];
+    WV_HIP(hipMemcpyAsync(host, terms, sizeof(host), hipMemcpyDeviceToHost, st));
+    WV_HIP(hipStreamSynchronize(st));
+    wv_stats &s = c->stats;
+    float ms = 0.f;
+    (void)hipEventElapsedTime(&ms, c->ev[EV_PLAN0], c->ev[EV_FINAL]);
+    s.ms_total += ms;
+    s.ms_sum += ms;   // the phases are not timed apart
+    s.n_primes += n;
+    s.n_sums += (uint64_t)n * (sh.nB + sh.nE);
+    s.n_terms += host[0];
+    s.n_terms_b += host[1];
+    s.chunk_terms = grid_k(g.logl);
+    s.block_k_b = (uint32_t)sum_variant_kb(c->variant);
+    s.block_k_e = (uint32_t)sum_variant_ke(c->variant);
+    s.grid = blocks;
+    return WV_OK;
+}
+
+}  // namespace wv

@@ -27,97 +27,10 @@
 
 #include "mont.hpp"
 #include "sum_core.hpp"
+#include "wave_ops.hpp"
 #include "wv_internal.hpp"
 
 namespace wv {
-
-// --------------------------------------------------------------------------
-// constants and records
-// --------------------------------------------------------------------------
-
-__device__ __forceinline__ Mont mont_of(const PrimeRec &r) {
-    Mont m;
-    m.p = r.p;
-    m.p0 = (uint32_t)r.p;
-    m.p1 = (uint32_t)(r.p >> 32);
-    m.ninv = r.ninv;
-    return m;
-}
-
-// Wave-uniform values are moved into scalar registers with readfirstlane /
-// readlane, so that every branch and loop exit that depends on them is a
-// scalar branch.  A cross-lane read through a vector shuffle inside a loop lets
-// the compiler split the loop per lane, and lanes can then read a register of
-// a lane that is parked on another path.
-__device__ __forceinline__ uint64_t readfirst_u64(uint64_t v) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
-    uint32_t lo = __shfl_xor((int)(uint32_t)v, mask, 64);
-    uint32_t hi = __shfl_xor((int)(uint32_t)(v >> 32), mask, 64);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// v of lane (lane ^ X) within the same 32-lane half (0 < X < 32): ds_swizzle
-// in bit-mask mode (offset = and-mask 0x1f | or-mask 0 << 5 | xor-mask X << 10).
-// The pattern is an immediate, so unlike ds_bpermute no per-lane address
-// register is held; the persistent sum kernel would otherwise keep those
-// addresses live across its loop and spill them.
-template <int X>
-__device__ __forceinline__ uint32_t swz_xor(uint32_t v) {
-    static_assert(X > 0 && X < 32, "swizzle reaches within a 32-lane half");
-    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x1f | (X << 10));
-}
-
-template <int X>
-__device__ __forceinline__ uint64_t swz_xor_u64(uint64_t v) {
-    return ((uint64_t)swz_xor<X>((uint32_t)(v >> 32)) << 32) | swz_xor<X>((uint32_t)v);
-}
-
-__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// minimum over the 64 lanes of a fully active wave, as a wave-uniform value
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-    v = min(v, swz_xor<16>(v));
-    v = min(v, swz_xor<8>(v));
-    v = min(v, swz_xor<4>(v));
-    v = min(v, swz_xor<2>(v));
-    v = min(v, swz_xor<1>(v));
-    // readlane returns int: compare as unsigned (0xffffffff is the largest value)
-    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
-    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)v, 32);
-    return a < b ? a : b;
-}
-
-// Butterfly of eqnCombinePairs across the 64 lanes of a fully active wave
-// (same prime on all lanes): each 32-lane half by swizzles, then the two
-// halves through scalar reads; every lane ends with the product of all 64
-// pairs.
-template <int X>
-__device__ __forceinline__ void pair_swz_step(uint64_t &c0, uint64_t &c1, const Mont &m) {
-    const uint64_t d0 = swz_xor_u64<X>(c0);
-    const uint64_t d1 = swz_xor_u64<X>(c1);
-    pair_mul(c0, c1, d0, d1, m);
-}
-
-__device__ __forceinline__ void wave_pair_reduce(uint64_t &c0, uint64_t &c1, const Mont &m) {
-    pair_swz_step<16>(c0, c1, m);
-    pair_swz_step<8>(c0, c1, m);
-    pair_swz_step<4>(c0, c1, m);
-    pair_swz_step<2>(c0, c1, m);
-    pair_swz_step<1>(c0, c1, m);
-    const uint64_t d0 = readlane_u64(c0, 32), d1 = readlane_u64(c1, 32);
-    c0 = readlane_u64(c0, 0);
-    c1 = readlane_u64(c1, 0);
-    pair_mul(c0, c1, d0, d1, m);
-}
 
 // --------------------------------------------------------------------------
 // sieve
