@@ -397,7 +397,8 @@ int wv_eval_sums(wv_ctx *ctx, const uint64_t *primes, size_t n, uint64_t *out_b,
 typedef struct wv_server wv_server;
 
 typedef struct {
-    uint64_t step_terms;   /* terms of work per step (0: 2^38, ~45 ms at p ~ 1e11) */
+    uint64_t step_terms;   /* terms of work per step (0: 2^38, or for primes evaluated along
+                              progressions as much as takes the same time, ~45 ms) */
     uint32_t max_primes;   /* prime slots of the device pool (0: 65536, or fewer so that the pool
                               holds at most 2^30 (prime, sum) slots, at least 1024 primes) */
     uint32_t reserved;

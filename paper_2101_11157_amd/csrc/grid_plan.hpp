@@ -70,10 +70,10 @@ inline double grid_build_ops(int logl) {
     return ops;
 }
 
-// The grid path's class for primes near p: least modelled work over the
-// lengths and compiled congruences.  A length needs p >= 4 L^2: every
+// The least modelled work over the lengths and compiled congruences for primes
+// near p.  A length needs p >= 4 L^2: every
 // difference of two points, at most p/2 + 2 K W, is then below p and nonzero.
-inline GridClass grid_class(uint64_t p) {
+inline GridClass grid_search(uint64_t p) {
     GridClass best;
     best.ops = 1e300;
     for (int logl = kNttMinLog; logl <= kNttMaxLog; logl++) {
@@ -90,6 +90,38 @@ inline GridClass grid_class(uint64_t p) {
         if (c.ops < best.ops) best = c;
     }
     return best;
+}
+
+// The grid path's class for p: that of the least prime of its sixteenth of an
+// octave (so primes of one size share a class), searched once per process.
+inline const GridClass &grid_class(uint64_t p) {
+    struct Table {
+        GridClass c[16 * 41];
+        Table() {
+            for (int i = 0; i < 16 * 41; i++) c[i] = grid_search((uint64_t)std::ceil(std::exp2(i / 16.0)));
+        }
+    };
+    static const Table t;
+    int i = std::min((int)(std::log2((double)p) * 16.0), 16 * 41 - 1);
+    while (i > 0 && p < (uint64_t)std::ceil(std::exp2(i / 16.0))) i--;   // rounding of the logarithm
+    return t.c[i];
+}
+
+// Operations per prime near p in class g.
+inline double grid_ops(uint64_t p, const GridClass &g) {
+    return grid_side_ops(kTables[g.tb], (double)p, g.logl) + grid_side_ops(kTables[g.te], (double)p, g.logl) +
+           grid_build_ops(g.logl);
+}
+
+// Whether n primes near p join a batch of class g (of larger primes) instead
+// of running in their own: the work that g adds has to stay below what the
+// kernels of one more batch take whatever it holds (about 0.35 ms of the GPU,
+// measured for one prime; the path runs at about 1.7e13 operations/s).
+constexpr double kGridRate = 1.7e13, kGridBatchS = 3.5e-4;
+inline bool grid_joins(uint64_t p, double n, const GridClass &g) {
+    if (p < (4ull << (2 * g.logl))) return false;
+    const GridClass &own = grid_class(p);
+    return own == g || (grid_ops(p, g) - own.ops) * n < kGridBatchS * kGridRate;
 }
 
 }  // namespace wv

@@ -842,9 +842,10 @@ int wv_destroy(wv_ctx *c) {
                       &c->seg_off, &c->seg_desc, &c->pad_primes, &c->stats_hist, &c->stats_near, &c->coefs,
                       &c->lhsmod, &c->tbl_head, &c->tbl_term, &c->tbl_limb, &c->tails, &c->tail_hist,
                       &c->irr_tasks, &c->irr_units, &c->irr_primes, &c->irr_roff, &c->irr_v, &c->irr_fix,
-                      &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e, &c->grid_ws};
+                      &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e};
     for (DevBuf *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
+    grid_free(c->grid);
     for (DevBuf &b : c->ntt_tab)
         if (b.ptr) (void)hipFree(b.ptr);
     for (int i = 0; i < EV_COUNT; i++)
@@ -1125,8 +1126,14 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
         WV_HIP(hipMemcpyAsync(c->primes.ptr, sorted.data(), n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
         size_t b = 0;
         while (b < n && grid_takes(c, sorted[b], &gc)) {
-            size_t e = b + 1;
-            while (e < n && grid_takes(c, sorted[e], &gk) && gk == gc) e++;
+            // runs of smaller classes join while that is the cheaper way
+            size_t e = b;
+            while (e < n && grid_takes(c, sorted[e], &gk)) {
+                size_t r = e + 1;
+                while (r < n && sorted[r] >= kGridMinP && grid_class(sorted[r]) == gk) r++;
+                if (!grid_joins(sorted[e], (double)(r - e), gc)) break;
+                e = r;
+            }
             WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes) + b, (uint32_t)(e - b), sorted[b],
                                    as<wv_result>(c->results) + b));
             b = e;

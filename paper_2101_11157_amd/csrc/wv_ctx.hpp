@@ -92,6 +92,12 @@ struct GraphEntry {
     int tbl_b = -1, tbl_e = -1;   // search graphs: the batch's table choice
 };
 
+// Device buffers of one grid-path batch: the plan's records and a workspace.
+// Each stream that runs such batches has its own.
+struct GridWork {
+    DevBuf pr, segs, terms, cnt, off, tiles, seg_pairs, coefs, lhsmod, ws;
+};
+
 // Per-batch consumer of device results that never go to the host: residue
 // histograms accumulated on the device, near misses gathered per batch.
 struct StatsSink {
@@ -126,7 +132,8 @@ struct wv_ctx {
     wv::DevBuf base_primes, primes, pr, segs, terms, cnt, off, tiles, scal, partials, seg_pairs, results,
         seg_counts, seg_bits, seg_off, seg_desc, pad_primes, stats_hist, stats_near, coefs, lhsmod, tbl_head,
         tbl_term, tbl_limb, tails, tail_hist, irr_tasks, irr_units, irr_primes, irr_roff, irr_v, irr_fix,
-        irr_counts, irr_pairs, irr_b, irr_e, grid_ws;
+        irr_counts, irr_pairs, irr_b, irr_e;
+    wv::GridWork grid;                             // grid path's records and workspace
     wv::DevBuf ntt_tab[wv::kNttMaxLog + 1];       // twiddle tables per log2 length (grid path)
     // congruence registry: the compiled tables (ids < WV_TABLE_COUNT), then
     // those defined at run time; device copy in tbl_* (TableStore)
@@ -229,10 +236,23 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
 // / 23, 1e11 1295 / 87; of 64 primes alone the grid wins from 2e8 (0.82 / 0.68
 // ms a call) and loses at 1e8 (0.64 / 0.73).
 constexpr uint64_t kGridMinP = 1ull << 27;
+bool grid_allowed(const wv_ctx *c, int tb, int te);   // with these tables configured
 bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g);
-// n primes in [4 * 4^logl, pmax] on the device -> d_out (waits; fills c->stats)
+// n primes in [4 * 4^logl, pmax] on the device -> d_out, enqueued on st with
+// buffers b; the terms covered are added to terms[0] (all) and terms[1] (s^-3)
+int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const uint64_t *d_primes, uint32_t n,
+                 uint64_t pmax, unsigned long long *terms, wv_result *d_out);
+void grid_free(GridWork &b);
+// the same on the context's stream, waited for; fills c->stats
 int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
                     wv_result *d_out);
+// server: pool primes of a step's spans (i0: first pool slot) to out[q0 ..],
+// their results back, and the results of finished requests
+hipError_t launch_pool_gather(hipStream_t st, const StepSpan *sp, uint32_t nsp, uint32_t n, const uint64_t *plist,
+                              uint64_t *out);
+hipError_t launch_pool_scatter(hipStream_t st, const StepSpan *sp, uint32_t nsp, uint32_t n, const wv_result *res,
+                               wv_result *pool);
+hipError_t launch_pool_results(hipStream_t st, const FinReq *fr, uint32_t nfr, const wv_result *pool, wv_result *out);
 // device address of the fixed scratch array on `device` (current), looked up
 // once per device (wv_static.hip)
 int static_scratch_setup(int device, void **addr);

@@ -648,26 +648,25 @@ void launch_inv(hipStream_t st, unsigned grid, const SegRec *segs, const uint64_
     hipLaunchKernelGGL(k_grid_inv<C>, dim3(grid), dim3(256), 0, st, segs, off, nseg, pr, K, logw, inv);
 }
 
-// One sub-batch of n primes, enqueued on the context's stream: results into
-// d_out, terms summed added to terms (2 words on the device).
-int grid_sub(wv_ctx *c, const GridClass &g, const GridLayout &y, const uint64_t *d_primes, uint32_t n,
-             unsigned long long *terms, wv_result *d_out) {
-    hipStream_t st = c->stream;
+// One sub-batch of n primes, enqueued on st: results into d_out, terms summed
+// added to terms (2 words on the device).
+int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const GridLayout &y, const uint64_t *d_primes,
+             uint32_t n, unsigned long long *terms, wv_result *d_out) {
     const uint32_t K = (uint32_t)grid_k(g.logl);
     const int logw = g.logl - 1;
     const int nB = kTables[g.tb].n, nE = kTables[g.te].n;
     const uint64_t nseg = (uint64_t)n * (nB + nE);
     if (nseg >= (1ull << 31) || (uint64_t)n * (K + 1) >= (1ull << 31)) return WV_EINVAL;
-    PrimeRec *pr = as<PrimeRec>(c->pr);
-    SegRec *segs = as<SegRec>(c->segs);
-    uint64_t *off = as<uint64_t>(c->off);
-    char *ws = as<char>(c->grid_ws);
+    PrimeRec *pr = as<PrimeRec>(b.pr);
+    SegRec *segs = as<SegRec>(b.segs);
+    uint64_t *off = as<uint64_t>(b.off);
+    char *ws = as<char>(b.ws);
     auto at = [&](size_t o) { return reinterpret_cast<double *>(ws + o); };
     WV_HIP(launch_plan(st, d_primes, n, g.tb, g.te, g.tb, g.te, nB, nE, table_store(c), pr, segs,
-                       as<uint64_t>(c->terms), as<uint64_t>(c->coefs), as<uint64_t>(c->lhsmod), 0));
+                       as<uint64_t>(b.terms), as<uint64_t>(b.coefs), as<uint64_t>(b.lhsmod), 0));
     hipLaunchKernelGGL(k_grid_count, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, st, segs, nseg, (uint64_t)K, logw,
-                       as<uint64_t>(c->cnt), terms);
-    WV_HIP(launch_scan(st, as<uint64_t>(c->cnt), nseg, off, as<uint64_t>(c->tiles)));
+                       as<uint64_t>(b.cnt), terms);
+    WV_HIP(launch_scan(st, as<uint64_t>(b.cnt), nseg, off, as<uint64_t>(b.tiles)));
     const unsigned inv_grid = (unsigned)c->num_cus * 8;
     double *inv = at(y.inv);
     switch (logw) {
@@ -729,13 +728,13 @@ int grid_sub(wv_ctx *c, const GridClass &g, const GridLayout &y, const uint64_t 
     const Pair *pairs = reinterpret_cast<const Pair *>(at(y.pairs));
     if (K < 2047)
         hipLaunchKernelGGL(k_grid_join<1>, dim3((unsigned)((nseg + 3) / 4)), dim3(256), 0, st, segs, off, nseg, pr, pairs,
-                           K, as<Pair>(c->seg_pairs));
+                           K, as<Pair>(b.seg_pairs));
     else
         hipLaunchKernelGGL(k_grid_join<4>, dim3((unsigned)nseg), dim3(256), 0, st, segs, off, nseg, pr, pairs, K,
-                           as<Pair>(c->seg_pairs));
+                           as<Pair>(b.seg_pairs));
     WV_HIP(hipGetLastError());
-    WV_HIP(launch_finalize(st, table_store(c), pr, as<Pair>(c->seg_pairs), as<uint64_t>(c->coefs),
-                           as<uint64_t>(c->lhsmod), n, nB, nE, d_out, nullptr));
+    WV_HIP(launch_finalize(st, table_store(c), pr, as<Pair>(b.seg_pairs), as<uint64_t>(b.coefs),
+                           as<uint64_t>(b.lhsmod), n, nB, nE, d_out, nullptr));
     return WV_OK;
 }
 
@@ -745,17 +744,19 @@ int grid_sub(wv_ctx *c, const GridClass &g, const GridLayout &y, const uint64_t 
 // printed congruence gives; a table the caller chose or defined, a forced shape
 // or chunk, and a progress callback (called between term-sum launches) keep the
 // term sums.
+bool grid_allowed(const wv_ctx *c, int tb, int te) {
+    return tb == WV_TABLE_BB30 && te == WV_TABLE_EE33 && !c->shape_forced && !c->chunk_cfg && !c->progress;
+}
+
 bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g) {
-    if (c->tb != WV_TABLE_BB30 || c->te != WV_TABLE_EE33 || c->shape_forced || c->chunk_cfg || c->progress) return false;
-    if (p < kGridMinP) return false;
+    if (p < kGridMinP || !grid_allowed(c, c->tb, c->te)) return false;
     *g = grid_class(p);
     return true;
 }
 
-int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
-                    wv_result *d_out) {
+int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const uint64_t *d_primes, uint32_t n,
+                 uint64_t pmax, unsigned long long *terms, wv_result *d_out) {
     if (n == 0) return WV_OK;
-    hipStream_t st = c->stream;
     for (int l = kNttMinLog; l <= g.logl; l++) WV_TRY(ntt_tables(c, l));
     const unsigned blocks = grid_blocks(c, g.logl);
     // sub-batches within the workspace bound
@@ -765,21 +766,36 @@ int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uin
     const uint32_t parts = (n + step - 1) / step;
     step = (n + parts - 1) / parts;
     const GridLayout y = grid_layout(g, step, pmax, blocks);
-    BatchShape sh{};
-    sh.tb = g.tb;
-    sh.te = g.te;
-    sh.n = step;
-    sh.nB = kTables[g.tb].n;
-    sh.nE = kTables[g.te].n;
-    sh.nseg = (uint64_t)step * (sh.nB + sh.nE);
-    sh.cap = 1;
-    WV_TRY(prepare(c, sh));
-    WV_TRY(ensure(c, c->grid_ws, y.total));
+    const uint64_t nseg = (uint64_t)step * (kTables[g.tb].n + kTables[g.te].n);
+    WV_TRY(ensure(c, b.pr, step * sizeof(PrimeRec)));
+    WV_TRY(ensure(c, b.segs, nseg * sizeof(SegRec)));
+    WV_TRY(ensure(c, b.terms, nseg * sizeof(uint64_t)));
+    WV_TRY(ensure(c, b.cnt, nseg * sizeof(uint64_t)));
+    WV_TRY(ensure(c, b.off, (nseg + 1) * sizeof(uint64_t)));
+    WV_TRY(ensure(c, b.tiles, ((nseg + kScanTile - 1) / kScanTile + 1) * sizeof(uint64_t)));
+    WV_TRY(ensure(c, b.seg_pairs, nseg * sizeof(Pair)));
+    WV_TRY(ensure(c, b.coefs, nseg * sizeof(uint64_t)));
+    WV_TRY(ensure(c, b.lhsmod, 2 * (size_t)step * sizeof(uint64_t)));
+    WV_TRY(ensure(c, b.ws, y.total));
+    for (uint32_t i = 0; i < n; i += step)
+        WV_TRY(grid_sub(c, b, st, g, y, d_primes + i, std::min(step, n - i), terms, d_out + i));
+    return WV_OK;
+}
+
+void grid_free(GridWork &b) {
+    DevBuf *bufs[] = {&b.pr, &b.segs, &b.terms, &b.cnt, &b.off, &b.tiles, &b.seg_pairs, &b.coefs, &b.lhsmod, &b.ws};
+    for (DevBuf *x : bufs)
+        if (x->ptr) (void)hipFree(x->ptr);
+}
+
+int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
+                    wv_result *d_out) {
+    if (n == 0) return WV_OK;
+    hipStream_t st = c->stream;
     auto *terms = as<unsigned long long>(c->scal);
     WV_HIP(hipEventRecord(c->ev[EV_PLAN0], st));
     WV_HIP(launch_set_u64(st, as<uint64_t>(c->scal), 8, 0));
-    for (uint32_t b = 0; b < n; b += step)
-        WV_TRY(grid_sub(c, g, y, d_primes + b, std::min(step, n - b), terms, d_out + b));
+    WV_TRY(grid_enqueue(c, c->grid, st, g, d_primes, n, pmax, terms, d_out));
     WV_HIP(hipEventRecord(c->ev[EV_FINAL], st));
     uint64_t host[2];
     WV_HIP(hipMemcpyAsync(host, terms, sizeof(host), hipMemcpyDeviceToHost, st));
@@ -790,14 +806,70 @@ int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uin
     s.ms_total += ms;
     s.ms_sum += ms;   // the phases are not timed apart
     s.n_primes += n;
-    s.n_sums += (uint64_t)n * (sh.nB + sh.nE);
+    s.n_sums += (uint64_t)n * (kTables[g.tb].n + kTables[g.te].n);
     s.n_terms += host[0];
     s.n_terms_b += host[1];
     s.chunk_terms = grid_k(g.logl);
     s.block_k_b = (uint32_t)sum_variant_kb(c->variant);
     s.block_k_e = (uint32_t)sum_variant_ke(c->variant);
-    s.grid = blocks;
+    s.grid = grid_blocks(c, g.logl);
     return WV_OK;
+}
+
+// ---------------------------------------------------------------------------
+// request server: primes of a step out of the pool, results into it
+// ---------------------------------------------------------------------------
+
+namespace {
+
+// Pool slot of prime q of a step: span[a] holds primes q0 .. q0 + cnt - 1 at
+// pool slots i0 .. (spans ascending in q0).
+__device__ __forceinline__ uint32_t span_slot(const StepSpan *__restrict__ sp, uint32_t nsp, uint32_t q) {
+    uint32_t a = 0, b = nsp;
+    while (b - a > 1) {
+        const uint32_t m = (a + b) >> 1;
+        if (sp[m].q0 <= q) a = m;
+        else b = m;
+    }
+    return sp[a].i0 + (q - sp[a].q0);
+}
+
+__global__ void __launch_bounds__(256) k_pool_gather(const StepSpan *__restrict__ sp, uint32_t nsp, uint32_t n,
+                                                     const uint64_t *__restrict__ plist, uint64_t *__restrict__ out) {
+    const uint32_t q = blockIdx.x * 256 + threadIdx.x;
+    if (q < n) out[q] = plist[span_slot(sp, nsp, q)];
+}
+
+__global__ void __launch_bounds__(256) k_pool_scatter(const StepSpan *__restrict__ sp, uint32_t nsp, uint32_t n,
+                                                      const wv_result *__restrict__ res, wv_result *__restrict__ pool) {
+    const uint32_t q = blockIdx.x * 256 + threadIdx.x;
+    if (q < n) pool[span_slot(sp, nsp, q)] = res[q];
+}
+
+// Results of finished requests (pool slots base .. base + n - 1) to out + out0.
+__global__ void __launch_bounds__(256) k_pool_results(const FinReq *__restrict__ fr, uint32_t nfr,
+                                                      const wv_result *__restrict__ pool, wv_result *__restrict__ out) {
+    const FinReq f = fr[blockIdx.x];
+    for (uint32_t i = threadIdx.x; i < f.n; i += 256) out[f.out0 + i] = pool[f.base + i];
+}
+
+}  // namespace
+
+hipError_t launch_pool_gather(hipStream_t st, const StepSpan *sp, uint32_t nsp, uint32_t n, const uint64_t *plist,
+                              uint64_t *out) {
+    hipLaunchKernelGGL(k_pool_gather, dim3((n + 255) / 256), dim3(256), 0, st, sp, nsp, n, plist, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_pool_scatter(hipStream_t st, const StepSpan *sp, uint32_t nsp, uint32_t n, const wv_result *res,
+                               wv_result *pool) {
+    hipLaunchKernelGGL(k_pool_scatter, dim3((n + 255) / 256), dim3(256), 0, st, sp, nsp, n, res, pool);
+    return hipGetLastError();
+}
+
+hipError_t launch_pool_results(hipStream_t st, const FinReq *fr, uint32_t nfr, const wv_result *pool, wv_result *out) {
+    hipLaunchKernelGGL(k_pool_results, dim3(nfr), dim3(256), 0, st, fr, nfr, pool, out);
+    return hipGetLastError();
 }
 
 }  // namespace wv

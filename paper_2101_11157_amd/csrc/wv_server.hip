@@ -71,7 +71,9 @@ struct Request {
     uint32_t n = 0;            // primes in the pool
     uint32_t base = 0;         // first pool slot
     uint32_t next = 0;         // primes handed to launched steps
-    double tpp = 0;            // estimated terms per prime
+    uint64_t pmin = 0;         // a lower bound on them
+    bool grid = false;         // evaluated by the grid path (decided at admission)
+    double tpp = 0;            // estimated terms per prime (see admit)
     std::vector<wv_result> results;
 };
 
@@ -91,6 +93,12 @@ int pinned_reserve(T *&p, size_t &cap, size_t n) {
 // One step's device buffers, its pinned staging (reused once the step has
 // completed), its events and the requests it finalizes.
 struct StepSet {
+    DevBuf gspans, gprimes, gres, gfin;   // grid path: spans, primes and results of the step, finished requests
+    GridWork grid;
+    StepSpan *gspans_h = nullptr;
+    size_t gspans_cap = 0;
+    FinReq *gfin_h = nullptr;
+    size_t gfin_cap = 0;
     DevBuf spans, tasks, terms, cnt, off, tiles, target, tpairs, partials, tails, hist, scal, fin, res;
     StepSpan *spans_h = nullptr;
     size_t spans_cap = 0;
@@ -98,7 +106,7 @@ struct StepSet {
     size_t fin_cap = 0;
     wv_result *res_h = nullptr;
     size_t res_cap = 0;
-    uint64_t *scal_h = nullptr;     // pinned: the step's scalars (kScal* words) once it has run
+    uint64_t *scal_h = nullptr;     // pinned: the step's scalars (kScal* words, then the grid path's terms) once it has run
     hipEvent_t ev0 = nullptr, ev_sum0 = nullptr, ev_sum = nullptr, ev1 = nullptr;
     bool busy = false;              // launched and not yet completed
     uint64_t id = 0;                // step number (1, 2, ...)
@@ -125,10 +133,11 @@ struct wv_server {
     bool adm_pending[2] = {}, adm_recorded[2] = {}, fold_recorded[2] = {};
     double busy_end_ms = 0, sum_end_ms = 0;   // ends of the device intervals counted so far (from ev_ref)
     uint64_t step_terms = 1ull << 38;
+    bool step_default = true;  // step_terms not given: a step's time is what it stands for
     uint32_t pool = 1u << 16;
     int tb = 0, te = 0;        // congruences fixed at creation (the pool layout depends on them)
     int nB = 0, nE = 0, NS = 0;
-    DevBuf pr, segs, acc, terms, coefs, lhsmod, plist;   // pool (plist: each slot's prime)
+    DevBuf pr, segs, acc, terms, coefs, lhsmod, plist, pres;   // pool (plist: each slot's prime, pres: its result by the grid path)
     DevBuf sdesc, scount, sbits, soff;                    // sieve of one range admission
     StepSet set[2];
     int next = 0;              // the set the next launch uses
@@ -224,6 +233,11 @@ uint64_t count_primes_host(std::vector<uint32_t> &base, uint64_t &limit, uint64_
     return count;
 }
 
+// Terms that the term-sum kernels sum while the grid path runs one operation of
+// its model (6.2e12 terms/s against 1.7e13 operations/s).
+constexpr double kGridTermsPerOp = 6.2e12 / kGridRate;
+constexpr int kStepScal = 16, kStepGridTerms = 8;   // words of a step's scalars; the grid path's two
+
 // Estimated terms per prime of size p (the congruence that applies at p).
 double terms_per_prime(const wv_server *s, uint64_t p) {
     const wv_ctx *c = s->c;
@@ -302,7 +316,9 @@ int admit(wv_server *s, Request *r, bool *admitted, hipStream_t st) {
     } else {
         rc = stage_upload(s, r->primes.data(), n * sizeof(uint64_t), dp, st);
     }
-    if (rc == WV_OK) {
+    // a request of primes the grid path takes needs no plan of its sums
+    r->grid = r->pmin >= kGridMinP && grid_allowed(c, s->tb, s->te);
+    if (rc == WV_OK && !r->grid) {
         const size_t first = (size_t)base * s->NS, nseg = (size_t)n * s->NS;
         if (launch_plan(st, dp, (uint32_t)n, s->tb, s->te, table_fallback(c, s->tb), table_fallback(c, s->te), s->nB,
                         s->nE, table_store(c), as<PrimeRec>(s->pr) + base, as<SegRec>(s->segs) + first,
@@ -319,7 +335,10 @@ int admit(wv_server *s, Request *r, bool *admitted, hipStream_t st) {
     }
     r->t_admit = now_s();
     r->next = 0;
-    r->tpp = terms_per_prime(s, r->pmax);
+    // the default budget stands for about 45 ms of the GPU, so a grid prime
+    // counts for the terms summed in its time; a budget that the caller gave
+    // counts the terms of the configured congruences
+    r->tpp = r->grid && s->step_default ? grid_class(r->pmax).ops * kGridTermsPerOp : terms_per_prime(s, r->pmax);
     r->state = REQ_ACTIVE;
     s->active.push_back(r);
     *admitted = true;
@@ -331,7 +350,7 @@ int admit(wv_server *s, Request *r, bool *admitted, hipStream_t st) {
 int readmit_all(wv_server *s) {
     for (Request *r : s->active) {
         r->next = 0;
-        WV_HIP(launch_fill_pairs(s->c->stream, as<Pair>(s->acc) + (size_t)r->base * s->NS, (size_t)r->n * s->NS, 1, 0));
+        if (!r->grid) WV_HIP(launch_fill_pairs(s->c->stream, as<Pair>(s->acc) + (size_t)r->base * s->NS, (size_t)r->n * s->NS, 1, 0));
         s->readmits++;
     }
     WV_HIP(hipStreamSynchronize(s->c->stream));
@@ -361,15 +380,20 @@ int launch_step(wv_server *s, int sk, bool *launched) {
     const uint64_t nq = step_share(share.data(), share.size(), (double)s->step_terms, (uint64_t)s->NS, give.data());
     // spans in candidate order; requests whose last primes this step holds
     // are finalized at its end
-    std::vector<StepSpan> spans;
-    std::vector<FinReq> fins;
+    std::vector<StepSpan> spans, gspans;
+    std::vector<FinReq> fins, gfins;
+    std::vector<std::pair<uint64_t, size_t>> gcand;   // (largest prime, candidate) of the grid path's requests
     ss.finishing.clear();
     ss.fin_out.clear();
-    uint32_t q0 = 0, nres = 0;
+    uint32_t q0 = 0, nres = 0, ngres = 0;
     double t_est = 0;
     for (size_t k = 0; k < cand.size(); k++) {
         if (!give[k]) continue;
         Request *r = cand[k];
+        if (r->grid) {
+            gcand.push_back({r->pmax, k});
+            continue;
+        }
         spans.push_back(StepSpan{(uint64_t)r->base * s->NS, r->n, r->next, q0, give[k]});
         q0 += give[k];
         t_est += give[k] * r->tpp;
@@ -380,7 +404,34 @@ int launch_step(wv_server *s, int sk, bool *launched) {
             nres += r->n;
         }
     }
-    const uint64_t nt = nq * (uint64_t)s->NS, nbt = nq * (uint64_t)s->nB;
+    // the grid path's requests: largest primes first, in batches of one class;
+    // a span's i0 is its first pool slot and its q0 counts within the step
+    struct Batch {
+        GridClass g;
+        uint64_t pmax;
+        uint32_t q0, n;
+    };
+    std::vector<Batch> batches;
+    std::sort(gcand.begin(), gcand.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+    uint32_t gq = 0;
+    for (const auto &gk : gcand) {
+        Request *r = cand[gk.second];
+        const uint32_t m = give[gk.second];
+        const bool joins = !batches.empty() && r->pmin >= (4ull << (2 * batches.back().g.logl)) &&
+                           grid_joins(r->pmax, m, batches.back().g);
+        if (!joins) batches.push_back(Batch{grid_class(r->pmax), r->pmax, gq, 0});
+        batches.back().n += m;
+        gspans.push_back(StepSpan{0, r->n, r->base + r->next, gq, m});
+        gq += m;
+        if (r->next + m == r->n) {
+            gfins.push_back(FinReq{r->base, r->n, ngres, 0});
+            ss.finishing.push_back(r);
+            ss.fin_out.push_back(nres + ngres);
+            ngres += r->n;
+        }
+    }
+    const uint64_t nq_terms = q0;
+    const uint64_t nt = nq_terms * (uint64_t)s->NS, nbt = nq_terms * (uint64_t)s->nB;
     // partial pairs: room for the estimated terms at the configured (or
     // adaptive) chunk and for every task's tail; the device picks a chunk
     // size that fits whatever the terms turn out to be
@@ -394,7 +445,15 @@ int launch_step(wv_server *s, int sk, bool *launched) {
     const uint64_t cap = std::max<uint64_t>(
         2 * nt, (uint64_t)std::min<double>(std::max<double>(t_est / chunk + 2.0 * nt, (double)kMinChunks),
                                            (double)kMaxChunks));
-    WV_TRY(ensure(c, ss.spans, spans.size() * sizeof(StepSpan)));
+    WV_TRY(ensure(c, ss.spans, std::max<size_t>(spans.size(), 1) * sizeof(StepSpan)));
+    WV_TRY(ensure(c, ss.gspans, std::max<size_t>(gspans.size(), 1) * sizeof(StepSpan)));
+    WV_TRY(ensure(c, ss.gfin, std::max<size_t>(gfins.size(), 1) * sizeof(FinReq)));
+    WV_TRY(ensure(c, ss.gprimes, std::max<size_t>(gq, 1) * sizeof(uint64_t)));
+    WV_TRY(ensure(c, ss.gres, std::max<size_t>(gq, 1) * sizeof(wv_result)));
+    WV_TRY(pinned_reserve(ss.gspans_h, ss.gspans_cap, std::max<size_t>(gspans.size(), 1)));
+    WV_TRY(pinned_reserve(ss.gfin_h, ss.gfin_cap, std::max<size_t>(gfins.size(), 1)));
+    if (!gspans.empty()) memcpy(ss.gspans_h, gspans.data(), gspans.size() * sizeof(StepSpan));
+    if (!gfins.empty()) memcpy(ss.gfin_h, gfins.data(), gfins.size() * sizeof(FinReq));
     WV_TRY(ensure(c, ss.tasks, nt * sizeof(SegRec)));
     WV_TRY(ensure(c, ss.terms, nt * sizeof(uint64_t)));
     WV_TRY(ensure(c, ss.cnt, nt * sizeof(uint64_t)));
@@ -406,11 +465,11 @@ int launch_step(wv_server *s, int sk, bool *launched) {
     WV_TRY(ensure(c, ss.hist, 2 * kTailClasses * sizeof(uint64_t)));
     WV_TRY(ensure(c, ss.partials, cap * sizeof(Pair)));
     WV_TRY(ensure(c, ss.fin, std::max<size_t>(fins.size(), 1) * sizeof(FinReq)));
-    WV_TRY(ensure(c, ss.res, std::max<size_t>(nres, 1) * sizeof(wv_result)));
-    WV_TRY(pinned_reserve(ss.spans_h, ss.spans_cap, spans.size()));
+    WV_TRY(ensure(c, ss.res, std::max<size_t>(nres + ngres, 1) * sizeof(wv_result)));
+    WV_TRY(pinned_reserve(ss.spans_h, ss.spans_cap, std::max<size_t>(spans.size(), 1)));
     WV_TRY(pinned_reserve(ss.fin_h, ss.fin_cap, std::max<size_t>(fins.size(), 1)));
-    WV_TRY(pinned_reserve(ss.res_h, ss.res_cap, std::max<size_t>(nres, 1)));
-    memcpy(ss.spans_h, spans.data(), spans.size() * sizeof(StepSpan));
+    WV_TRY(pinned_reserve(ss.res_h, ss.res_cap, std::max<size_t>(nres + ngres, 1)));
+    if (!spans.empty()) memcpy(ss.spans_h, spans.data(), spans.size() * sizeof(StepSpan));
     if (!fins.empty()) memcpy(ss.fin_h, fins.data(), fins.size() * sizeof(FinReq));
 
     hipStream_t st = stream_of(s, sk);
@@ -422,44 +481,69 @@ int launch_step(wv_server *s, int sk, bool *launched) {
         s->adm_pending[1 - sk] = false;
     }
     WV_HIP(hipEventRecord(ss.ev0, st));
-    WV_HIP(hipMemcpyAsync(ss.spans.ptr, ss.spans_h, spans.size() * sizeof(StepSpan), hipMemcpyHostToDevice, st));
     if (!fins.empty())
         WV_HIP(hipMemcpyAsync(ss.fin.ptr, ss.fin_h, fins.size() * sizeof(FinReq), hipMemcpyHostToDevice, st));
-    WV_HIP(launch_set_u64(st, scal, 8, 0));
-    WV_HIP(launch_step_expand(st, as<StepSpan>(ss.spans), (uint32_t)spans.size(), (uint32_t)nq, s->nB, s->nE,
-                              as<SegRec>(s->segs), as<SegRec>(ss.tasks), as<uint64_t>(ss.terms),
-                              as<uint32_t>(ss.target)));
-    WV_HIP(launch_scan(st, as<uint64_t>(ss.terms), nt, off, as<uint64_t>(ss.tiles)));
-    WV_HIP(launch_pick_chunk(st, off + nt, nt, chunk_cfg, sum_lanes(c), cap, scal + kScalLayout));
-    WV_HIP(launch_copy_u64(st, off + nt, scal + kScalTerms, 1));
-    WV_HIP(launch_copy_u64(st, off + nbt, scal + kScalTermsB, 1));
-    WV_HIP(launch_chunk_layout(st, as<uint64_t>(ss.terms), nt, nbt, scal + kScalLayout, as<uint64_t>(ss.cnt), off,
-                               as<uint64_t>(ss.tiles), as<unsigned long long>(ss.hist), as<uint32_t>(ss.tails),
-                               scal + kScalChunks));
+    if (!gspans.empty())
+        WV_HIP(hipMemcpyAsync(ss.gspans.ptr, ss.gspans_h, gspans.size() * sizeof(StepSpan), hipMemcpyHostToDevice, st));
+    if (!gfins.empty())
+        WV_HIP(hipMemcpyAsync(ss.gfin.ptr, ss.gfin_h, gfins.size() * sizeof(FinReq), hipMemcpyHostToDevice, st));
+    WV_HIP(launch_set_u64(st, scal, kStepScal, 0));
+    if (nt) {
+        WV_HIP(hipMemcpyAsync(ss.spans.ptr, ss.spans_h, spans.size() * sizeof(StepSpan), hipMemcpyHostToDevice, st));
+        WV_HIP(launch_step_expand(st, as<StepSpan>(ss.spans), (uint32_t)spans.size(), (uint32_t)nq_terms, s->nB, s->nE,
+                                  as<SegRec>(s->segs), as<SegRec>(ss.tasks), as<uint64_t>(ss.terms),
+                                  as<uint32_t>(ss.target)));
+        WV_HIP(launch_scan(st, as<uint64_t>(ss.terms), nt, off, as<uint64_t>(ss.tiles)));
+        WV_HIP(launch_pick_chunk(st, off + nt, nt, chunk_cfg, sum_lanes(c), cap, scal + kScalLayout));
+        WV_HIP(launch_copy_u64(st, off + nt, scal + kScalTerms, 1));
+        WV_HIP(launch_copy_u64(st, off + nbt, scal + kScalTermsB, 1));
+        WV_HIP(launch_chunk_layout(st, as<uint64_t>(ss.terms), nt, nbt, scal + kScalLayout, as<uint64_t>(ss.cnt), off,
+                                   as<uint64_t>(ss.tiles), as<unsigned long long>(ss.hist), as<uint32_t>(ss.tails),
+                                   scal + kScalChunks));
+    }
     WV_HIP(hipEventRecord(ss.ev_sum0, st));
-    const int v = c->variant;
-    WV_HIP(launch_sum(st, v, (unsigned)c->sum_blocks[v], as<SegRec>(ss.tasks), off, (uint32_t)nt, as<PrimeRec>(s->pr),
-                      scal + kScalLayout, as<uint32_t>(ss.tails), as<Pair>(ss.partials), as<Pair>(ss.tpairs),
-                      (unsigned long long *)(scal + kScalCounter), UINT64_MAX,
-                      (unsigned long long *)(scal + kScalErr)));
+    if (nt) {
+        const int v = c->variant;
+        WV_HIP(launch_sum(st, v, (unsigned)c->sum_blocks[v], as<SegRec>(ss.tasks), off, (uint32_t)nt, as<PrimeRec>(s->pr),
+                          scal + kScalLayout, as<uint32_t>(ss.tails), as<Pair>(ss.partials), as<Pair>(ss.tpairs),
+                          (unsigned long long *)(scal + kScalCounter), UINT64_MAX,
+                          (unsigned long long *)(scal + kScalErr)));
+    }
+    if (gq) {
+        WV_HIP(launch_pool_gather(st, as<StepSpan>(ss.gspans), (uint32_t)gspans.size(), gq, as<uint64_t>(s->plist),
+                                  as<uint64_t>(ss.gprimes)));
+        for (const Batch &b : batches)
+            WV_TRY(grid_enqueue(c, ss.grid, st, b.g, as<uint64_t>(ss.gprimes) + b.q0, b.n, b.pmax,
+                                (unsigned long long *)(scal + kStepGridTerms), as<wv_result>(ss.gres) + b.q0));
+    }
     WV_HIP(hipEventRecord(ss.ev_sum, st));
-    WV_HIP(launch_reduce(st, as<SegRec>(ss.tasks), off, (uint32_t)nt, as<PrimeRec>(s->pr), as<Pair>(ss.partials),
-                         scal + kScalLayout, as<Pair>(ss.tpairs)));
-    WV_HIP(launch_fold(st, as<SegRec>(ss.tasks), as<uint32_t>(ss.target), as<Pair>(ss.tpairs), (uint32_t)nt,
-                       as<PrimeRec>(s->pr), as<Pair>(s->acc)));
+    if (nt) {
+        WV_HIP(launch_reduce(st, as<SegRec>(ss.tasks), off, (uint32_t)nt, as<PrimeRec>(s->pr), as<Pair>(ss.partials),
+                             scal + kScalLayout, as<Pair>(ss.tpairs)));
+        WV_HIP(launch_fold(st, as<SegRec>(ss.tasks), as<uint32_t>(ss.target), as<Pair>(ss.tpairs), (uint32_t)nt,
+                           as<PrimeRec>(s->pr), as<Pair>(s->acc)));
+    }
+    if (gq)
+        WV_HIP(launch_pool_scatter(st, as<StepSpan>(ss.gspans), (uint32_t)gspans.size(), gq, as<wv_result>(ss.gres),
+                                   as<wv_result>(s->pres)));
     WV_HIP(hipEventRecord(s->ev_fold[sk], st));
     s->fold_recorded[sk] = true;
-    if (!fins.empty()) {
-        // the finalized requests' earlier primes may have been folded by the
-        // other stream's step
+    if (nres + ngres) {
+        // the finished requests' earlier primes may have been folded (or their
+        // results stored) by the other stream's step
         if (s->fold_recorded[1 - sk]) WV_HIP(hipStreamWaitEvent(st, s->ev_fold[1 - sk], 0));
-        WV_HIP(launch_finalize_multi(st, table_store(c), as<PrimeRec>(s->pr), as<Pair>(s->acc),
-                                     as<uint64_t>(s->coefs), as<uint64_t>(s->lhsmod), as<FinReq>(ss.fin),
-                                     (uint32_t)fins.size(), nres, s->nB, s->nE, as<wv_result>(ss.res),
-                                     (const unsigned long long *)(scal + kScalErr)));
-        WV_HIP(hipMemcpyAsync(ss.res_h, ss.res.ptr, (size_t)nres * sizeof(wv_result), hipMemcpyDeviceToHost, st));
+        if (!gfins.empty())
+            WV_HIP(launch_pool_results(st, as<FinReq>(ss.gfin), (uint32_t)gfins.size(), as<wv_result>(s->pres),
+                                       as<wv_result>(ss.res) + nres));
+        if (!fins.empty())
+            WV_HIP(launch_finalize_multi(st, table_store(c), as<PrimeRec>(s->pr), as<Pair>(s->acc),
+                                         as<uint64_t>(s->coefs), as<uint64_t>(s->lhsmod), as<FinReq>(ss.fin),
+                                         (uint32_t)fins.size(), nres, s->nB, s->nE, as<wv_result>(ss.res),
+                                         (const unsigned long long *)(scal + kScalErr)));
+        WV_HIP(hipMemcpyAsync(ss.res_h, ss.res.ptr, (size_t)(nres + ngres) * sizeof(wv_result), hipMemcpyDeviceToHost,
+                              st));
     }
-    WV_HIP(hipMemcpyAsync(ss.scal_h, scal, 8 * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+    WV_HIP(hipMemcpyAsync(ss.scal_h, scal, kStepScal * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
     WV_HIP(hipEventRecord(ss.ev1, st));
     // the primes are handed out
     ss.id = ++s->launched;
@@ -491,8 +575,8 @@ int complete_step(wv_server *s, StepSet &ss) {
         s->fault_after = -1;   // one forced failure: the step's work is discarded
         return WV_EHIP;
     }
-    s->terms_done += ss.scal_h[kScalTerms];
-    s->terms_done_b += ss.scal_h[kScalTermsB];
+    s->terms_done += ss.scal_h[kScalTerms] + ss.scal_h[kStepGridTerms];
+    s->terms_done_b += ss.scal_h[kScalTermsB] + ss.scal_h[kStepGridTerms + 1];
     s->fail_streak = 0;
     if (ss.finishing.empty()) return WV_OK;
     for (size_t k = 0; k < ss.finishing.size(); k++) {
@@ -542,7 +626,10 @@ int wv_server_create(wv_ctx *c, const wv_server_config *cfg, wv_server **out) {
     wv_server *s = new (std::nothrow) wv_server();
     if (!s) return WV_ENOMEM;
     s->c = c;
-    if (cfg && cfg->step_terms) s->step_terms = cfg->step_terms;
+    if (cfg && cfg->step_terms) {
+        s->step_terms = cfg->step_terms;
+        s->step_default = false;
+    }
     s->tb = c->tb;
     s->te = c->te;
     s->nB = side_slots(c, c->tb);
@@ -565,6 +652,7 @@ int wv_server_create(wv_ctx *c, const wv_server_config *cfg, wv_server **out) {
         (rc = ensure(c, s->coefs, nseg * sizeof(uint64_t))) != WV_OK ||
         (rc = ensure(c, s->lhsmod, 2 * (size_t)s->pool * sizeof(uint64_t))) != WV_OK ||
         (rc = ensure(c, s->plist, s->pool * sizeof(uint64_t))) != WV_OK ||
+        (rc = ensure(c, s->pres, s->pool * sizeof(wv_result))) != WV_OK ||
         (rc = ensure(c, s->sdesc, kMaxBatchSegs * sizeof(SegDesc))) != WV_OK ||
         (rc = ensure(c, s->scount, kMaxBatchSegs * sizeof(uint32_t))) != WV_OK ||
         (rc = ensure(c, s->sbits, kMaxBatchSegs * kSegWords * sizeof(uint32_t))) != WV_OK ||
@@ -581,13 +669,13 @@ int wv_server_create(wv_ctx *c, const wv_server_config *cfg, wv_server **out) {
             rc = WV_EHIP;
     for (int k = 0; k < 2 && rc == WV_OK; k++) {
         StepSet &ss = s->set[k];
-        if ((rc = ensure(c, ss.scal, 8 * sizeof(uint64_t))) != WV_OK) break;
-        if (hipHostMalloc((void **)&ss.scal_h, 8 * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess ||
+        if ((rc = ensure(c, ss.scal, kStepScal * sizeof(uint64_t))) != WV_OK) break;
+        if (hipHostMalloc((void **)&ss.scal_h, kStepScal * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess ||
             hipEventCreate(&ss.ev0) != hipSuccess || hipEventCreate(&ss.ev_sum0) != hipSuccess ||
             hipEventCreate(&ss.ev_sum) != hipSuccess || hipEventCreate(&ss.ev1) != hipSuccess)
             rc = WV_EHIP;
         else
-            memset(ss.scal_h, 0, 8 * sizeof(uint64_t));
+            memset(ss.scal_h, 0, kStepScal * sizeof(uint64_t));
         Upload &u = s->up[k];
         if (rc == WV_OK && (hipHostMalloc((void **)&u.h, kUploadBytes, hipHostMallocDefault) != hipSuccess ||
                             hipEventCreate(&u.ev) != hipSuccess))
@@ -613,16 +701,18 @@ int wv_server_destroy(wv_server *s) {
     if (!s) return WV_OK;
     if (s->c) (void)hipStreamSynchronize(s->c->stream);
     if (s->own) (void)hipStreamSynchronize(s->own);
-    DevBuf *bufs[] = {&s->pr, &s->segs, &s->acc, &s->terms, &s->coefs, &s->lhsmod, &s->plist,
+    DevBuf *bufs[] = {&s->pr, &s->segs, &s->acc, &s->terms, &s->coefs, &s->lhsmod, &s->plist, &s->pres,
                       &s->sdesc, &s->scount, &s->sbits, &s->soff};
     for (DevBuf *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     for (StepSet &ss : s->set) {
         DevBuf *sb[] = {&ss.spans, &ss.tasks, &ss.terms, &ss.cnt, &ss.off, &ss.tiles, &ss.target,
-                        &ss.tpairs, &ss.partials, &ss.tails, &ss.hist, &ss.scal, &ss.fin, &ss.res};
+                        &ss.tpairs, &ss.partials, &ss.tails, &ss.hist, &ss.scal, &ss.fin, &ss.res,
+                        &ss.gspans, &ss.gprimes, &ss.gres, &ss.gfin};
         for (DevBuf *b : sb)
             if (b->ptr) (void)hipFree(b->ptr);
-        void *hb[] = {ss.spans_h, ss.fin_h, ss.res_h, ss.scal_h};
+        grid_free(ss.grid);
+        void *hb[] = {ss.spans_h, ss.fin_h, ss.res_h, ss.scal_h, ss.gspans_h, ss.gfin_h};
         for (void *h : hb)
             if (h) (void)hipHostFree(h);
         hipEvent_t evs[] = {ss.ev0, ss.ev_sum0, ss.ev_sum, ss.ev1};
@@ -656,6 +746,7 @@ int wv_server_submit_range(wv_server *s, uint64_t lo, uint64_t hi, uint64_t *id)
     r->lo = lo;
     r->hi = hi;
     r->n_primes = n;
+    r->pmin = lo;
     r->pmax = hi;
     r->t_submit = now_s();
     if (!s->submitted) s->t_first = r->t_submit;
@@ -669,17 +760,19 @@ int wv_server_submit_range(wv_server *s, uint64_t lo, uint64_t hi, uint64_t *id)
 int wv_server_submit_primes(wv_server *s, const uint64_t *primes, size_t n, uint64_t *id) {
     if (!s || !id || (n && !primes)) return WV_EINVAL;
     if (n > s->pool) return WV_EINVAL;
-    uint64_t pmax = 0;
+    uint64_t pmax = 0, pmin = UINT64_MAX;
     for (size_t i = 0; i < n; i++) {
         if (primes[i] < 5 || primes[i] >= WV_P_MAX) return WV_EDOMAIN;
         if (!is_prime_u64(primes[i])) return WV_ENOTPRIME;
         pmax = std::max(pmax, primes[i]);
+        pmin = std::min(pmin, primes[i]);
     }
     Request *r = new (std::nothrow) Request();
     if (!r) return WV_ENOMEM;
     r->id = s->next_id++;
     r->primes.assign(primes, primes + n);
     r->n_primes = n;
+    r->pmin = pmin;
     r->pmax = pmax;
     r->t_submit = now_s();
     if (!s->submitted) s->t_first = r->t_submit;
@@ -744,7 +837,7 @@ int wv_server_step(wv_server *s, uint32_t *n_active, uint32_t *n_pending) {
         if (!ok) {
             waiting.push_back(r);
         } else {
-            admitted_sums += (size_t)r->n * s->NS;
+            admitted_sums += (size_t)r->n * (r->grid ? 1 : s->NS);
             enqueued |= r->n > 0;
         }
     }

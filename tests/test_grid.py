@@ -136,3 +136,55 @@ def test_other_settings_keep_the_term_sums(terms):
         assert rows(c.eval_primes(ps)) == ref and seen
         c.set_progress(None)
         assert rows(c.eval_primes(ps)) == ref
+
+
+def drain(srv, ids, out):
+    for _ in range(100000):
+        for rid in ids:
+            if rid not in out:
+                r = srv.result(rid)
+                if r is not None:
+                    out[rid] = r[0]
+        if len(out) == len(ids):
+            return
+        srv.step()
+    raise AssertionError("server did not drain")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("step_terms, fault", [(0, None), (1 << 30, None), (1 << 30, 1)])
+def test_server_mixes_both_paths(grid, terms, step_terms, fault):
+    """Requests of every class, below the grid path's start, across it (the term
+    sums serve those) and empty, in one server, with whole-request and cut-up
+    steps and a forced failure: each equals the same primes on the term sums."""
+    print(f"case: server, step_terms {step_terms}, fault {fault}", flush=True)
+    reqs = [primes_from(lo, 1 + k % 3) for k, lo in enumerate(SIZES[:9])]
+    reqs += [(2 ** 27 - 1500, 2 ** 27 + 1500), (3 * 10 ** 9, 3 * 10 ** 9 + 900), (10 ** 6, 10 ** 6 + 2000), (24, 29),
+             primes_from(10 ** 6, 4) + primes_from(10 ** 9, 2)]
+    errors = 0
+    with wv.Server(grid, step_terms=step_terms) as srv:
+        if fault is not None:
+            srv.inject_fault(fault)
+        ids = []
+        for i, r in enumerate(reqs):
+            ids.append(srv.submit_range(*r) if isinstance(r, tuple) else srv.submit_primes(r))
+            if i % 5 == 4:
+                try:
+                    srv.step()
+                except wv.WvError:
+                    errors += 1
+        out = {}
+        for _ in range(3):
+            try:
+                drain(srv, ids, out)
+                break
+            except wv.WvError:
+                errors += 1
+        st = srv.stats()
+    assert errors == (0 if fault is None else 1)
+    assert st["failed"] == 0 and st["completed"] == len(reqs) and st["terms_done"] > 0
+    for r, rid in zip(reqs, ids):
+        ps = oracle.primes(*r) if isinstance(r, tuple) else r
+        assert [int(p) for p in out[rid]["p"]] == ps
+        if ps:
+            assert rows(out[rid]) == rows(terms.eval_primes(ps))
