@@ -21,28 +21,68 @@ struct GridClass {
 constexpr uint64_t grid_k(int logl) { return (1ull << (logl - 1)) - 1; }
 constexpr uint64_t grid_w(int logl) { return 1ull << (logl - 1); }
 
-// Upper bound on the shifts (workgroups of W block starts) of one prime p with
-// a table's sums: a sum over (x p, y p) holds at most (y - x) p + 1 terms.
-inline uint64_t grid_shifts(const TableDef &d, double p, int logl) {
-    const double K = (double)grid_k(logl), W = (double)grid_w(logl);
-    uint64_t r = 0;
-    for (int i = 0; i < d.n; i++) {
-        const TermDef &t = d.t[i];
-        const double len = ((double)t.ya / t.yb - (double)t.xa / t.xb) * p + 1.0;
-        r += (uint64_t)(len / K / W) + 1;
+// Sums whose intervals touch (one's upper endpoint is the next one's lower, and
+// y p is no integer, so their s follow one another) are one run: one
+// progression of block starts serves them all, and only the blocks that hold
+// an endpoint are summed term by term.  EE33's 33 sums are 6 runs.
+constexpr int kMaxRunSums = 34;
+struct GridRuns {
+    uint8_t n = 0;                       // runs
+    uint8_t first[kMaxRunSums] = {};     // first and last sum of each run, ascending in s
+    uint8_t last[kMaxRunSums] = {};
+    uint8_t run[kMaxRunSums] = {};       // run of each sum
+};
+
+inline GridRuns find_runs(const TableDef &d) {
+    GridRuns g;
+    int ord[kMaxRunSums];
+    for (int i = 0; i < d.n; i++) ord[i] = i;
+    std::sort(ord, ord + d.n, [&](int a, int b) {
+        return (uint64_t)d.t[a].xa * d.t[b].xb < (uint64_t)d.t[b].xa * d.t[a].xb;
+    });
+    for (int k = 0; k < d.n; k++) {
+        const TermDef &t = d.t[ord[k]];
+        const bool joins = k > 0 && (uint64_t)d.t[ord[k - 1]].ya * t.xb == (uint64_t)t.xa * d.t[ord[k - 1]].yb;
+        if (!joins) g.first[g.n++] = (uint8_t)ord[k];
+        g.last[g.n - 1] = (uint8_t)ord[k];
+        g.run[ord[k]] = (uint8_t)(g.n - 1);
     }
-    return r;
+    return g;
+}
+
+// runs of compiled table id (eqnBB1 .. eqnEE33)
+inline const GridRuns &grid_runs(int id) {
+    struct All {
+        GridRuns r[WV_TABLE_EE33 + 1];
+        All() {
+            for (int i = 0; i <= WV_TABLE_EE33; i++) r[i] = find_runs(kTables[i]);
+        }
+    };
+    static const All all;
+    return all.r[id];
+}
+
+inline double run_width(int id, int r) {
+    const GridRuns &g = grid_runs(id);
+    const TermDef &a = kTables[id].t[g.first[r]], &b = kTables[id].t[g.last[r]];
+    return (double)b.ya / b.yb - (double)a.xa / a.xb;
+}
+
+// Upper bound on the shifts (workgroups of W block starts) of one prime p with
+// a table's runs: a run over (x p, y p) holds at most (y - x) p + 1 terms.
+inline uint64_t grid_shifts(int id, double p, int logl) {
+    const double K = (double)grid_k(logl), W = (double)grid_w(logl);
+    uint64_t s = 0;
+    for (int r = 0; r < grid_runs(id).n; r++) s += (uint64_t)((run_width(id, r) * p + 1.0) / K / W) + 1;
+    return s;
 }
 
 // The same as an estimate: ceil of the blocks over W, no block no shift.
-inline double grid_shifts_est(const TableDef &d, double p, int logl) {
+inline double grid_shifts_est(int id, double p, int logl) {
     const double K = (double)grid_k(logl), W = (double)grid_w(logl);
-    double r = 0;
-    for (int i = 0; i < d.n; i++) {
-        const TermDef &t = d.t[i];
-        r += std::ceil(std::floor(((double)t.ya / t.yb - (double)t.xa / t.xb) * p / K) / W);
-    }
-    return r;
+    double s = 0;
+    for (int r = 0; r < grid_runs(id).n; r++) s += std::ceil(std::floor(run_width(id, r) * p / K) / W);
+    return s;
 }
 
 // Operations of a pair of transforms (both moduli) of length L: about 50 per
@@ -53,14 +93,17 @@ inline double grid_pair_ops(int logl) {
 }
 
 // One side's operations per prime: each shift transforms its kernel and brings
-// back `polys` value vectors; every sum has an inverse list and the terms
-// after its last block.
-inline double grid_side_ops(const TableDef &d, double p, int logl) {
+// back `polys` value vectors, whose values are folded once; every run has an
+// inverse list, every endpoint a block's worth of single terms (half of one at
+// the end of a run).
+inline double grid_side_ops(int id, double p, int logl) {
     const double W = (double)grid_w(logl), K = (double)grid_k(logl);
-    const int polys = d.deg + 1;
-    const double r = grid_shifts_est(d, p, logl);
+    const TableDef &d = kTables[id];
+    const int polys = d.deg + 1, runs = grid_runs(id).n;
+    const double s = grid_shifts_est(id, p, logl);
     const double pair = grid_pair_ops(logl);
-    return r * (pair + polys * (pair + 4.0 * W * 10.0)) + (r + d.n) * W * 30.0 + d.n * (0.5 * K * 30.0 + 4000.0);
+    return s * (pair + polys * (pair + 2.0 * W * 20.0) + W * 40.0) + (s + runs) * W * 30.0 +
+           (d.n - 0.5 * runs) * K * 30.0 + d.n * 4000.0;
 }
 
 // Node values of blocks of K terms, by doubling from blocks of 255.
@@ -82,7 +125,7 @@ inline GridClass grid_search(uint64_t p) {
         c.logl = logl;
         double b = 1e300, e = 1e300;
         for (int t = WV_TABLE_BB1; t <= WV_TABLE_EE33; t++) {
-            const double v = grid_side_ops(kTables[t], (double)p, logl);
+            const double v = grid_side_ops(t, (double)p, logl);
             if (kTables[t].deg == 3 && v < b) b = v, c.tb = t;
             if (kTables[t].deg == 2 && v < e) e = v, c.te = t;
         }
@@ -109,7 +152,7 @@ inline const GridClass &grid_class(uint64_t p) {
 
 // Operations per prime near p in class g.
 inline double grid_ops(uint64_t p, const GridClass &g) {
-    return grid_side_ops(kTables[g.tb], (double)p, g.logl) + grid_side_ops(kTables[g.te], (double)p, g.logl) +
+    return grid_side_ops(g.tb, (double)p, g.logl) + grid_side_ops(g.te, (double)p, g.logl) +
            grid_build_ops(g.logl);
 }
 

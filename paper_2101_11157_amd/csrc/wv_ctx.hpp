@@ -95,7 +95,7 @@ struct GraphEntry {
 // Device buffers of one grid-path batch: the plan's records and a workspace.
 // Each stream that runs such batches has its own.
 struct GridWork {
-    DevBuf pr, segs, terms, cnt, off, tiles, seg_pairs, coefs, lhsmod, ws;
+    DevBuf pr, segs, runs, terms, cnt, off, tiles, seg_pairs, coefs, lhsmod, ws;
 };
 
 // Per-batch consumer of device results that never go to the host: residue
@@ -134,6 +134,7 @@ struct wv_ctx {
         tbl_term, tbl_limb, tails, tail_hist, irr_tasks, irr_units, irr_primes, irr_roff, irr_v, irr_fix,
         irr_counts, irr_pairs, irr_b, irr_e;
     wv::GridWork grid;                             // grid path's records and workspace
+    wv::DevBuf grid_tabs;                          // runs of the compiled tables (grid path)
     wv::DevBuf ntt_tab[wv::kNttMaxLog + 1];       // twiddle tables per log2 length (grid path)
     // congruence registry: the compiled tables (ids < WV_TABLE_COUNT), then
     // those defined at run time; device copy in tbl_* (TableStore)

@@ -61,19 +61,30 @@ __device__ __forceinline__ double f_pow_u(double a, uint64_t e, const Fmod &f) {
 // plan: shifts per sum
 // ---------------------------------------------------------------------------
 
-// One thread per (prime, sum): the shifts of W blocks its blocks need; the
-// terms of each side added to terms[0] (all) and terms[1] (s^-3 side).
-__global__ void __launch_bounds__(256) k_grid_count(const SegRec *__restrict__ segs, uint64_t nseg, uint64_t K,
-                                                    int logw, uint64_t *__restrict__ cnt,
-                                                    unsigned long long *__restrict__ terms) {
+// One thread per (prime, run), laid out as the sums are (s^-3 runs of prime i at
+// i rB + r, then the s^-2 ones): its first term and length, and the shifts of
+// W block starts it needs; the terms of each side added to terms[0] (all) and
+// terms[1] (s^-3 side).
+__global__ void __launch_bounds__(256) k_grid_runs(const SegRec *__restrict__ segs, uint32_t n, int nB, int nE,
+                                                   const GridRuns *__restrict__ tabs, int tb, int te, uint64_t K,
+                                                   int logw, SegRec *__restrict__ runs, uint64_t *__restrict__ cnt,
+                                                   unsigned long long *__restrict__ terms) {
     const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t rB = tabs[tb].n, rE = tabs[te].n;
     uint64_t len = 0, len_b = 0;
-    if (i < nseg) {
-        const SegRec s = segs[i];
+    if (i < (uint64_t)n * (rB + rE)) {
+        const bool bern = i < (uint64_t)n * rB;
+        const uint64_t k = bern ? i : i - (uint64_t)n * rB;
+        const uint32_t prime = (uint32_t)(k / (bern ? rB : rE)), r = (uint32_t)(k % (bern ? rB : rE));
+        const GridRuns &g = tabs[bern ? tb : te];
+        const uint64_t base = bern ? (uint64_t)prime * nB : (uint64_t)n * nB + (uint64_t)prime * nE;
+        SegRec s = segs[base + g.first[r]];
+        const SegRec e = segs[base + g.last[r]];
+        s.len = e.lo + e.len - s.lo;   // 0 for a rejected prime (every sum empty)
+        runs[i] = s;
+        cnt[i] = (s.len / K + (1ull << logw) - 1) >> logw;
         len = s.len;
-        len_b = s.deg == 3 ? s.len : 0;
-        const uint64_t t = s.len / K;
-        cnt[i] = (t + (1ull << logw) - 1) >> logw;
+        len_b = bern ? s.len : 0;
     }
     for (int o = 32; o >= 1; o >>= 1) {
         len += shfl_xor_u64(len, o);
@@ -89,9 +100,9 @@ __global__ void __launch_bounds__(256) k_grid_count(const SegRec *__restrict__ s
 // inverses along a progression
 // ---------------------------------------------------------------------------
 
-// inv[e] = 1 / (lo + K n) mod p for n = 0 .. (R + 1) W - 1 of every sum with R
+// inv[e] = 1 / (lo + K n) mod p for n = 0 .. (R + 1) W - 1 of every run with R
 // shifts, at (off[slot] + slot) W + n.  A wave takes 64 C consecutive entries
-// of one sum, each lane C of them: products up, one Fermat inverse, products
+// of one run, each lane C of them: products up, one Fermat inverse, products
 // down.
 template <int C>
 __global__ void __launch_bounds__(256) k_grid_inv(const SegRec *__restrict__ segs, const uint64_t *__restrict__ off,
@@ -131,77 +142,114 @@ WV_UNROLL
     }
 }
 
-// Prefix products of get(0 .. 256 c - 1) over a workgroup of 256 threads, thread
-// t holding entries [t c, t c + c): put(i, A_i, 1 / A_i, A_{i-1}) for every i.
-template <class Get, class Put>
-__device__ __forceinline__ void prefix_inverses(int c, const Fmod &f, uint64_t p, double *__restrict__ s, Get get,
-                                                Put put) {
+// Prefix products A_i of get(0 .. 256 C - 1) over a workgroup of 256 threads,
+// and their inverses: thread t holds entries [t C, t C + C).  prev: A before
+// its first entry.
+template <int C, class Get>
+__device__ __forceinline__ void prefix_inverses(const Fmod &f, uint64_t p, double *__restrict__ s, Get get,
+                                                double (&A)[C], double (&iA)[C], double &prev) {
     const int tid = threadIdx.x;
-    double prod = 1.0;
-    for (int i = 0; i < c; i++) prod = f_mulmod(prod, get(tid * c + i), f);
-    s[tid] = prod;
+    double v[C];
+WV_UNROLL
+    for (int i = 0; i < C; i++) {
+        v[i] = get(tid * C + i);
+        A[i] = i ? f_mulmod(A[i ? i - 1 : 0], v[i], f) : v[0];
+    }
+    s[tid] = A[C - 1];
     __syncthreads();
     for (int o = 1; o < 256; o <<= 1) {
-        const double v = tid >= o ? s[tid - o] : 1.0;
+        const double u = tid >= o ? s[tid - o] : 1.0;
         __syncthreads();
-        s[tid] = f_mulmod(s[tid], v, f);
+        s[tid] = f_mulmod(s[tid], u, f);
         __syncthreads();
     }
-    const double excl = tid ? s[tid - 1] : 1.0;
+    prev = tid ? s[tid - 1] : 1.0;
     double r = f_pow_u(s[tid], p - 2, f);   // inverse of the prefix up to this thread's last entry
-    // downwards: A_{i-1} = A_i / a_i would need inverses, so A is kept per entry
-    double a[32];
+    __syncthreads();                        // s is free
 WV_UNROLL
-    for (int i = 0; i < 32; i++) {
-        if (i < c) a[i] = f_mulmod(i ? a[i ? i - 1 : 0] : excl, get(tid * c + i), f);
-    }
+    for (int i = 0; i < C; i++) A[i] = f_mulmod(A[i], prev, f);
 WV_UNROLL
-    for (int i = 31; i >= 0; i--) {
-        if (i < c) {
-            put(tid * c + i, a[i], r, i ? a[i ? i - 1 : 0] : excl);
-            r = f_mulmod(r, get(tid * c + i), f);
-        }
+    for (int i = C - 1; i >= 0; i--) {
+        iA[i] = r;
+        r = f_mulmod(r, v[i], f);
     }
 }
 
-// Factorials and their inverses mod p up to K (a workgroup per prime):
-// fact[i], fact[(K + 1) + i].
-__global__ void __launch_bounds__(256) k_grid_fact(const PrimeRec *__restrict__ pr, uint32_t K, double *__restrict__ fact) {
-    __shared__ double s[256];
+// A thread's C consecutive entries of an array of 256 C through LDS (one pad
+// per 16), so that memory sees whole lines: stored entry by entry they took
+// most of the time of the kernels below.
+__host__ __device__ constexpr int stage_at(int i) { return i + (i >> 4); }
+template <int C>
+struct Stage {
+    double v[stage_at(256 * C)];
+};
+
+template <int C, int N>
+__device__ __forceinline__ void stage_store(Stage<C> &s, double *__restrict__ out) {
+    __syncthreads();
+WV_UNROLL
+    for (int i = 0; i < (N + 255) / 256; i++) {
+        const int at = i * 256 + (int)threadIdx.x;
+        if (at < N) out[at] = s.v[stage_at(at)];
+    }
+    __syncthreads();
+}
+
+// Factorials and their inverses mod p up to K = 256 C - 1 (a workgroup per
+// prime): fact[i], fact[(K + 1) + i].
+template <int C>
+__global__ void __launch_bounds__(256) k_grid_fact(const PrimeRec *__restrict__ pr, double *__restrict__ fact) {
+    __shared__ Stage<C> s;
+    const int tid = threadIdx.x;
     const uint64_t p = pr[blockIdx.x].p;
     const Fmod f = fmod_of(p);
-    double *F = fact + (size_t)blockIdx.x * 2 * (K + 1);
-    prefix_inverses((int)(K + 1) / 256, f, p, s, [](int i) { return i ? (double)i : 1.0; },
-                    [&](int i, double A, double iA, double) {
-                        F[i] = A;
-                        F[K + 1 + i] = iA;
-                    });
+    double *F = fact + (size_t)blockIdx.x * 2 * (256 * C);
+    double A[C], iA[C], prev;
+    prefix_inverses<C>(f, p, s.v, [](int i) { return i ? (double)i : 1.0; }, A, iA, prev);
+WV_UNROLL
+    for (int i = 0; i < C; i++) s.v[stage_at(tid * C + i)] = A[i];
+    stage_store<C, 256 * C>(s, F);
+WV_UNROLL
+    for (int i = 0; i < C; i++) s.v[stage_at(tid * C + i)] = iA[i];
+    stage_store<C, 256 * C>(s, F + 256 * C);
 }
 
-// Level arrays of one doubling step (blocks of k terms, L = 2 (k + 1)): for
-// shift s of prime i, a(n) = K n (s = 0: the next k + 1 nodes), k + K (n - L/2)
-// (s = 1: the nodes moved by k) or k + K n (s = 2: both); beta[n] = 1 / a(n),
-// A[n] = prod_{m <= n} a(m) and iA its inverse (a(0) counts as 1).
-// cst[i] = K^-k.
-__global__ void __launch_bounds__(256) k_grid_level(const PrimeRec *__restrict__ pr, uint32_t K, uint32_t k,
-                                                    double *__restrict__ beta, double *__restrict__ A,
-                                                    double *__restrict__ iA, double *__restrict__ cst) {
-    __shared__ double sc[256];
-    const uint32_t i = blockIdx.x / 3, sh = blockIdx.x - 3 * i, L = 2 * (k + 1);
+// Level arrays of one doubling step (blocks of k terms, L = 2 (k + 1) = 256
+// C): for shift s of prime i, a(n) = K n (s = 0: the next k + 1 nodes), k + K
+// (n - L/2) (s = 1: the nodes moved by k) or k + K n (s = 2: both); beta[n] =
+// 1 / a(n), n >= 1, and pi[t] = prod_{t < n <= t + L/2} a(n), the factor
+// prod (X - Y_i) at point t.  cst[i] = K^-k.
+template <int C>
+__global__ void __launch_bounds__(256) k_grid_level(const PrimeRec *__restrict__ pr, uint32_t K,
+                                                    double *__restrict__ beta, double *__restrict__ pi,
+                                                    double *__restrict__ cst) {
+    constexpr int L = 256 * C, k = L / 2 - 1;
+    __shared__ Stage<C> s;
+    const int tid = threadIdx.x;
+    const uint32_t i = blockIdx.x / 3, sh = blockIdx.x - 3 * i;
     const uint64_t p = pr[i].p;
     const Fmod f = fmod_of(p);
     const double Kd = (double)K;
     const double a0 = sh == 0 ? 0.0 : (sh == 1 ? (double)k - Kd * (double)(k + 1) : (double)k);
-    const size_t at = (size_t)blockIdx.x * L;
-    prefix_inverses((int)L / 256, f, p, sc, [&](int n) { return n ? fma((double)n, Kd, a0) : 1.0; },
-                    [&](int n, double a, double ia, double prev) {
-                        beta[at + n] = f_mulmod(ia, prev, f);
-                        A[at + n] = a;
-                        iA[at + n] = ia;
-                    });
+    double A[C], iA[C], prev;
+    prefix_inverses<C>(f, p, s.v, [&](int n) { return n ? fma((double)n, Kd, a0) : 1.0; }, A, iA, prev);
+WV_UNROLL
+    for (int e = 0; e < C; e++) s.v[stage_at(tid * C + e)] = f_mulmod(iA[e], e ? A[e ? e - 1 : 0] : prev, f);
+    stage_store<C, L>(s, beta + (size_t)blockIdx.x * L);
+    // A of the upper half meets 1 / A of the lower half
+    if (tid >= 128) {
+WV_UNROLL
+        for (int e = 0; e < C; e++) s.v[stage_at((tid - 128) * C + e)] = A[e];
+    }
+    __syncthreads();
+    if (tid < 128) {
+WV_UNROLL
+        for (int e = 0; e < C; e++) s.v[stage_at(tid * C + e)] = f_mulmod(s.v[stage_at(tid * C + e)], iA[e], f);
+    }
+    stage_store<C, L / 2>(s, pi + (size_t)blockIdx.x * (L / 2));
     if (sh == 0) {
         const double c = f_pow_u(f_pow_u(Kd, p - 2, f), k, f);
-        if (threadIdx.x == 0) cst[i] = c;
+        if (tid == 0) cst[i] = c;
     }
 }
 
@@ -277,12 +325,11 @@ struct ShiftArgs {
     const double *beta;       // kernel entries
     const double *uhat;       // transformed node vectors
     const double *tab;
-    double *out;              // level: residues; sums: scratch of each workgroup
-    const SegRec *segs;       // sums only, from here
+    double *out;              // level: residues mod q; runs: values mod p
+    const SegRec *runs;       // runs only, from here
     const uint64_t *off;
-    Pair *pairs;
     unsigned long long *counters;   // 8, one per XCD's share, zero at launch
-    uint32_t nseg, K;
+    uint32_t nruns, nruns_b;
 };
 
 // A vector of length L, every load requested before the first is used.
@@ -324,16 +371,23 @@ WV_UNROLL
     }
 }
 
+// Where the values of an item's vectors start: W per vector, four vectors for
+// an s^-3 shift, three for an s^-2 one (the s^-3 items, items_b of them, come
+// first).
+__device__ __forceinline__ uint64_t value_base(uint64_t item, uint64_t items_b, uint32_t W) {
+    return (item < items_b ? 4 * item : items_b + 3 * item) * W;
+}
+
 // What bounds this kernel: issue of f64 operations (about 66 per element of a
 // transform, 0.58 of the issue slots at L = 2^14), then the vector loads of
-// node vectors, twiddles and scratch between them.  One transform at a time
+// node vectors, twiddles and values between them.  One transform at a time
 // stays in a workgroup's registers (16 values a thread, four waves per SIMD);
-// at L = 2^14 a workgroup fills a CU.  1e11 window of 310 primes: 24.6 ms of
-// 27.3 ms a call; the term sums took 402 ms.
+// at L = 2^14 a workgroup fills a CU.
 //
-// The shifts of every sum (persistent; the items split evenly over the eight
+// The shifts of every run (persistent; the items split evenly over the eight
 // XCDs, taken one by one, so that neighbouring items, which share a prime's
-// node vectors, meet in one L2): values of g_0 .. g_d at the W block starts, folded into one pair.
+// node vectors, meet in one L2): values of g_0 .. g_d mod p at the W block
+// starts, up to a factor common to one block start.
 template <int LOGL>
 __global__ void __launch_bounds__(NttShape<LOGL>::T, 4) k_grid_shift(ShiftArgs A) {
     using S = NttShape<LOGL>;
@@ -341,9 +395,8 @@ __global__ void __launch_bounds__(NttShape<LOGL>::T, 4) k_grid_shift(ShiftArgs A
     __shared__ NttLds<LOGL> lds;
     __shared__ unsigned long long ticket;
     const int tid = threadIdx.x;
-    const uint64_t total = A.off[A.nseg];
+    const uint64_t total = A.off[A.nruns], items_b = A.off[A.nruns_b];
     const VecBuf tab = vec_buf(A.tab, 2 * S::STRIDE);
-    const VecBuf scr = vec_buf(A.out + (size_t)blockIdx.x * 4 * W, 4 * W);
     // the items of this workgroup's XCD, then those the others have left
     uint32_t part = 0;
     while (part < 8) {
@@ -356,16 +409,14 @@ __global__ void __launch_bounds__(NttShape<LOGL>::T, 4) k_grid_shift(ShiftArgs A
             part++;
             continue;
         }
-        const uint32_t slot = __builtin_amdgcn_readfirstlane(find_seg(A.off, A.nseg, item));
-        const uint64_t first = readfirst_u64(A.off[slot]), sigma = item - first;
-        const uint32_t prime = __builtin_amdgcn_readfirstlane(A.segs[slot].prime);
-        const int np = __builtin_amdgcn_readfirstlane(A.segs[slot].deg) == 3 ? 4 : 3;
-        // block starts from this shift's first
-        const uint32_t blocks = (uint32_t)min(readfirst_u64(A.segs[slot].len / A.K - sigma * W), (uint64_t)W);
+        const uint32_t slot = __builtin_amdgcn_readfirstlane(find_seg(A.off, A.nruns, item));
+        const uint32_t prime = __builtin_amdgcn_readfirstlane(A.runs[slot].prime);
+        const int np = slot < A.nruns_b ? 4 : 3;
         const Fmod fp = fmod_of(readfirst_u64(A.pr[prime].p));
         const double q1p = f_reduce((double)kNttQ[0], fp);   // q1 mod p, balanced
-        const double *beta = A.beta + (first + slot + sigma) * W;
+        const double *beta = A.beta + (slot + item) * W;      // entry off[slot] + slot + (item - off[slot])
         const double *uh = A.uhat + (size_t)prime * 8 * L;   // vector j modulo q at (2 j + q) L
+        const VecBuf out = vec_buf(A.out + value_base(item, items_b, W), np * W);
         double w[E], x[E], t1[E];
 WV_NO_UNROLL
         for (int q = 0; q < 2; q++) {
@@ -379,63 +430,21 @@ WV_NO_UNROLL
                 load_vec<LOGL>(x, uh + (size_t)(2 * j + q) * L, tid);
                 mulmod_range<kNttGroup, 0, E>(x, w, f);
                 ntt_inverse<LOGL>(x, t1, lds, q, f, tid);
+                // the residues mod q1 wait where the values go
                 const int o = j * W;
                 if (q == 0) {
 WV_UNROLL
-                    for (int e = 0; e < E / 2; e++) vec_store(scr, tid, o + e * T, f_reduce(x[E / 2 + e], f));
+                    for (int e = 0; e < E / 2; e++) vec_store(out, tid, o + e * T, f_reduce(x[E / 2 + e], f));
                 } else {
                     double r[E / 2];
 WV_UNROLL
-                    for (int e = 0; e < E / 2; e++) r[e] = vec_load(scr, tid, o + e * T);
+                    for (int e = 0; e < E / 2; e++) r[e] = vec_load(out, tid, o + e * T);
                     __builtin_amdgcn_sched_barrier(0);
 WV_UNROLL
                     for (int e = 0; e < E / 2; e++)
-                        vec_store(scr, tid, o + e * T, ntt_crt(r[e], x[E / 2 + e], kNttQ1Inv, q1p, f, fp));
+                        vec_store(out, tid, o + e * T, ntt_crt(r[e], x[E / 2 + e], kNttQ1Inv, q1p, f, fp));
                 }
             }
-        }
-        double a0 = 1.0, a1 = 0.0;
-        // four values of every vector at a time (g_3 is read for s^-2 sums
-        // too, where it is whatever the scratch held, and not used)
-        constexpr int G = E / 2 < 4 ? E / 2 : 4;
-WV_NO_UNROLL
-        for (int e0 = 0; e0 < E / 2; e0 += G) {
-            if ((uint32_t)(T * e0) >= blocks) break;
-            double v[4][G];
-WV_UNROLL
-            for (int e = 0; e < G; e++)
-WV_UNROLL
-                for (int j = 0; j < 4; j++) v[j][e] = vec_load(scr, tid, j * W + (e0 + e) * T);
-            __builtin_amdgcn_sched_barrier(0);
-WV_UNROLL
-            for (int e = 0; e < G; e++) {
-                if ((uint32_t)(tid + T * (e0 + e)) >= blocks) break;
-                const double r0 = v[0][e], r1 = v[1][e], r2 = v[2][e], r3 = v[3][e];
-                double P, Q;
-                if (np == 3) {
-                    P = f_mulmod(r0, r0, fp);
-                    const double u = f_mulmod(r0, r2, fp);
-                    Q = f_mulmod(r1, r1, fp) - (u + u);
-                } else {
-                    const double sq = f_mulmod(r0, r0, fp);
-                    P = f_mulmod(sq, r0, fp);
-                    const double u = fma(f_mulmod(r0, r2, fp), -3.0, f_mulmod(r1, r1, fp));
-                    Q = fma(f_mulmod(r3, sq, fp), 3.0, f_mulmod(r1, u, fp));
-                }
-                a1 = f_mulmod(a0, Q, fp) + f_mulmod(a1, P, fp);
-                a0 = f_mulmod(a0, P, fp);
-            }
-        }
-        const Mont m = mont_of(A.pr[prime]);
-        uint64_t c0 = f_canon(a0, fp), c1 = f_canon(a1, fp);
-        wave_pair_reduce(c0, c1, m);
-        Pair *sp = reinterpret_cast<Pair *>(lds.v);
-        __syncthreads();
-        if ((tid & 63) == 0) sp[tid >> 6] = Pair{c0, c1};
-        __syncthreads();
-        if (tid == 0) {
-            for (int v = 1; v < T / 64; v++) pair_mul(c0, c1, sp[v].c0, sp[v].c1, m);
-            A.pairs[item] = Pair{c0, c1};
         }
     }
 }
@@ -445,8 +454,8 @@ WV_UNROLL
 // 2).  One thread per (prime, node).
 __global__ void __launch_bounds__(256) k_grid_combine(const PrimeRec *__restrict__ pr, uint32_t n, uint32_t K, uint32_t k,
                                                       const double *__restrict__ node, const double *__restrict__ res,
-                                                      const double *__restrict__ A, const double *__restrict__ iA,
-                                                      const double *__restrict__ cst, double *__restrict__ next) {
+                                                      const double *__restrict__ pi, const double *__restrict__ cst,
+                                                      double *__restrict__ next) {
     const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     const uint32_t h = k + 1, L = 2 * h;
     if (g >= (uint64_t)n * L) return;
@@ -458,10 +467,10 @@ __global__ void __launch_bounds__(256) k_grid_combine(const PrimeRec *__restrict
     // values of shift s at point tt, times prod (X - Y_i) K^-k
     auto shifted = [&](uint32_t s, double (&v)[4]) {
         const size_t item = (size_t)i * 3 + s;
-        const double pi = f_mulmod(f_mulmod(A[item * L + tt + h], iA[item * L + tt], fp), cst[i], fp);
+        const double w = f_mulmod(pi[item * h + tt], cst[i], fp);
         for (int j = 0; j < 4; j++) {
             const double r1 = res[((item * 4 + j) * 2) * h + tt], r2 = res[((item * 4 + j) * 2 + 1) * h + tt];
-            v[j] = f_mulmod(ntt_crt(r1, r2, kNttQ1Inv, q1p, f2, fp), pi, fp);
+            v[j] = f_mulmod(ntt_crt(r1, r2, kNttQ1Inv, q1p, f2, fp), w, fp);
         }
     };
     double x[4], y[4];
@@ -483,37 +492,73 @@ __global__ void __launch_bounds__(256) k_grid_combine(const PrimeRec *__restrict
     for (int j = 1; j < 4; j++) o[(size_t)j * L] = f_reduce(f_mulmod(z[j], last, fp) + z[j - 1], fp);
 }
 
-// Every (prime, sum): the pairs of its shifts joined with the terms after its
-// last block (NW waves per sum).
+// Every (prime, sum): its blocks' pairs, from the values at their starts, and
+// the terms of the blocks that hold its endpoints, joined (NW waves per sum;
+// one where a sum has few blocks).  Reads each value once.
 template <int NW>
-__global__ void __launch_bounds__(256) k_grid_join(const SegRec *__restrict__ segs, const uint64_t *__restrict__ off,
-                                                   uint64_t nseg, const PrimeRec *__restrict__ pr,
-                                                   const Pair *__restrict__ pairs, uint32_t K,
-                                                   Pair *__restrict__ seg_pairs) {
-    __shared__ Pair part[4];
+__global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) k_grid_join(
+    const SegRec *__restrict__ segs, uint32_t n, int nB, int nE, const GridRuns *__restrict__ tabs, int tb, int te,
+    const SegRec *__restrict__ runs, const uint64_t *__restrict__ off, const PrimeRec *__restrict__ pr,
+    const double *__restrict__ vals, uint32_t K, int logw, Pair *__restrict__ seg_pairs) {
+    __shared__ Pair part[NW];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint64_t nseg = (uint64_t)n * (nB + nE);
     const uint64_t j = NW == 1 ? (uint64_t)blockIdx.x * 4 + wave : blockIdx.x;
-    const bool live = j < nseg;   // NW == 4: the grid has a workgroup per sum
+    const bool live = j < nseg;   // NW > 1: the grid has a workgroup per sum
     uint64_t c0 = 1, c1 = 0;
     Mont m;
     if (live) {
+        const bool bern = j < (uint64_t)n * nB;
+        const uint32_t k = (uint32_t)(bern ? j : j - (uint64_t)n * nB);
+        const uint32_t i = k / (uint32_t)(bern ? nB : nE), sum = k - i * (uint32_t)(bern ? nB : nE);
+        const uint32_t rB = tabs[tb].n, rE = tabs[te].n;
+        const uint32_t slot = bern ? i * rB + tabs[tb].run[sum] : n * rB + i * rE + tabs[te].run[sum];
         const SegRec s = segs[j];
+        const uint64_t run0 = runs[slot].lo;
         const PrimeRec P = pr[s.prime];
         m = mont_of(P);
         const Fmod f = fmod_of(P.p);
-        const int me = NW == 1 ? lane : (int)threadIdx.x;
+        const uint32_t me = NW == 1 ? lane : threadIdx.x;
+        // blocks [b0, b1) of the run lie inside the sum
+        const uint64_t d0 = s.len ? s.lo - run0 : 0;
+        const uint64_t b0 = (d0 + K - 1) / K, b1 = max((d0 + s.len) / K, b0);
         double a0 = 1.0, a1 = 0.0;
-        const uint64_t done = s.len / K * K;
-        for (uint64_t t = done + me; t < s.len; t += 64 * NW) {
-            const double v = (double)(s.lo + t);
+        auto fold = [&](double P0, double Q) {
+            a1 = f_mulmod(a0, Q, f) + f_mulmod(a1, P0, f);
+            a0 = f_mulmod(a0, P0, f);
+        };
+        const uint32_t W = 1u << logw;
+        const uint64_t first = off[slot], items_b = off[n * rB];
+        const double *v0 = vals + value_base(first, items_b, W);
+        const uint64_t per = (uint64_t)(bern ? 4 : 3) << logw;   // values of one item
+        if (bern) {
+            for (uint64_t t = b0 + me; t < b1; t += 64 * NW) {
+                const double *v = v0 + (t >> logw) * per + (t & (W - 1));
+                const double r0 = v[0], r1 = v[W], r2 = v[2 * W], r3 = v[3 * W];
+                const double sq = f_mulmod(r0, r0, f);
+                const double u = fma(f_mulmod(r0, r2, f), -3.0, f_mulmod(r1, r1, f));
+                fold(f_mulmod(sq, r0, f), fma(f_mulmod(r3, sq, f), 3.0, f_mulmod(r1, u, f)));
+            }
+        } else {
+            for (uint64_t t = b0 + me; t < b1; t += 64 * NW) {
+                const double *v = v0 + (t >> logw) * per + (t & (W - 1));
+                const double r0 = v[0], r1 = v[W], r2 = v[2 * W];
+                const double u = f_mulmod(r0, r2, f);
+                fold(f_mulmod(r0, r0, f), f_mulmod(r1, r1, f) - (u + u));
+            }
+        }
+        // the terms before the first block and after the last (all of them
+        // when no block fits)
+        const uint64_t head = b1 > b0 ? b0 * K - d0 : s.len, gap = b1 > b0 ? (b1 - b0) * K : 0;
+        for (uint64_t t = me; t < s.len - gap; t += 64 * NW) {
+            const double v = (double)(s.lo + (t < head ? t : t + gap));
             const double v2 = f_mulmod(v, v, f);
-            const double u = s.deg == 3 ? f_mulmod(v2, v, f) : v2;
+            const double u = bern ? f_mulmod(v2, v, f) : v2;
             a1 = f_mulmod(a1, u, f) + a0;   // |a1| < 1.15 p
             a0 = f_mulmod(a0, u, f);
         }
         c0 = f_canon(a0, f);
         c1 = f_canon(a1, f);
-        for (uint64_t i = off[j] + me; i < off[j + 1]; i += 64 * NW) pair_mul(c0, c1, pairs[i].c0, pairs[i].c1, m);
         wave_pair_reduce(c0, c1, m);
         if (NW == 1 && lane == 0) seg_pairs[j] = Pair{c0, c1};
     }
@@ -561,6 +606,33 @@ int with_shape(int logl, F &&fn) {
     }
 }
 
+template <class F>
+int with_chunks(int c, F &&fn) {
+    switch (c) {
+    case 1: return fn(std::integral_constant<int, 1>{});
+    case 2: return fn(std::integral_constant<int, 2>{});
+    case 4: return fn(std::integral_constant<int, 4>{});
+    case 8: return fn(std::integral_constant<int, 8>{});
+    case 16: return fn(std::integral_constant<int, 16>{});
+    case 32: return fn(std::integral_constant<int, 32>{});
+    default: return WV_EINVAL;
+    }
+}
+
+// Constant data into an empty buffer (waited for; the buffer stays empty if it
+// fails).
+int upload_once(wv_ctx *c, DevBuf &buf, const void *h, size_t bytes) {
+    WV_TRY(ensure(c, buf, bytes));
+    const hipError_t e = hipMemcpyAsync(buf.ptr, h, bytes, hipMemcpyHostToDevice, c->stream);
+    const hipError_t e2 = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess || e2 != hipSuccess) {
+        (void)hipFree(buf.ptr);
+        buf = DevBuf{};
+        return WV_EHIP;
+    }
+    return WV_OK;
+}
+
 // Twiddle tables of one length (both moduli), uploaded once per context.
 int ntt_tables(wv_ctx *c, int logl) {
     DevBuf &buf = c->ntt_tab[logl];
@@ -588,30 +660,30 @@ int ntt_tables(wv_ctx *c, int logl) {
         return WV_OK;
     });
     WV_TRY(rc);
-    WV_TRY(ensure(c, buf, h.size() * sizeof(double)));
-    const hipError_t e = hipMemcpyAsync(buf.ptr, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    const hipError_t e2 = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess || e2 != hipSuccess) {
-        (void)hipFree(buf.ptr);
-        buf = DevBuf{};
-        return WV_EHIP;
-    }
-    return WV_OK;
+    return upload_once(c, buf, h.data(), h.size() * sizeof(double));
+}
+
+// The runs of the compiled tables, uploaded once per context.
+int runs_table(wv_ctx *c) {
+    if (c->grid_tabs.ptr) return WV_OK;
+    std::vector<GridRuns> h(WV_TABLE_EE33 + 1);
+    for (int i = 0; i <= WV_TABLE_EE33; i++) h[i] = grid_runs(i);
+    return upload_once(c, c->grid_tabs, h.data(), h.size() * sizeof(GridRuns));
 }
 
 // Bytes of device memory a batch of n primes needs besides the plan's records.
 struct GridLayout {
-    uint64_t items;   // bound on the shifts
-    size_t node0, node1, fact, beta, A, iA, cst, uhat, res, inv, pairs, scratch, counters, total;
+    size_t node0, node1, fact, beta, pi, cst, uhat, res, inv, vals, counters, total;
 };
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-GridLayout grid_layout(const GridClass &g, uint64_t n, uint64_t pmax, unsigned blocks) {
+GridLayout grid_layout(const GridClass &g, uint64_t n, uint64_t pmax) {
     const uint64_t L = 1ull << g.logl, W = L / 2;
-    const uint64_t nseg = n * (kTables[g.tb].n + kTables[g.te].n);
+    const uint64_t nruns = n * (grid_runs(g.tb).n + grid_runs(g.te).n);
+    const uint64_t items_b = n * grid_shifts(g.tb, (double)pmax, g.logl);
+    const uint64_t items_e = n * grid_shifts(g.te, (double)pmax, g.logl);
     GridLayout y;
-    y.items = n * (grid_shifts(kTables[g.tb], (double)pmax, g.logl) + grid_shifts(kTables[g.te], (double)pmax, g.logl));
     size_t at = 0;
     auto take = [&](size_t &where, size_t doubles) {
         where = at;
@@ -621,14 +693,12 @@ GridLayout grid_layout(const GridClass &g, uint64_t n, uint64_t pmax, unsigned b
     take(y.node1, n * 4 * W);
     take(y.fact, n * 2 * W);
     take(y.beta, n * 3 * W);
-    take(y.A, n * 3 * W);
-    take(y.iA, n * 3 * W);
+    take(y.pi, n * 3 * W / 2);
     take(y.cst, n);
     take(y.uhat, n * 8 * L);
     take(y.res, n * 12 * W);
-    take(y.inv, (y.items + nseg) * W);
-    take(y.pairs, y.items * 2);
-    take(y.scratch, (size_t)blocks * 4 * W);
+    take(y.inv, (items_b + items_e + nruns) * W);
+    take(y.vals, (4 * items_b + 3 * items_e) * W);
     take(y.counters, 8);
     y.total = at;
     return y;
@@ -658,24 +728,29 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
     const uint64_t nseg = (uint64_t)n * (nB + nE);
     if (nseg >= (1ull << 31) || (uint64_t)n * (K + 1) >= (1ull << 31)) return WV_EINVAL;
     PrimeRec *pr = as<PrimeRec>(b.pr);
-    SegRec *segs = as<SegRec>(b.segs);
+    SegRec *segs = as<SegRec>(b.segs), *runs = as<SegRec>(b.runs);
     uint64_t *off = as<uint64_t>(b.off);
+    const GridRuns *tabs = as<GridRuns>(c->grid_tabs);
+    const uint32_t nruns_b = n * grid_runs(g.tb).n, nruns = nruns_b + n * grid_runs(g.te).n;
     char *ws = as<char>(b.ws);
     auto at = [&](size_t o) { return reinterpret_cast<double *>(ws + o); };
     WV_HIP(launch_plan(st, d_primes, n, g.tb, g.te, g.tb, g.te, nB, nE, table_store(c), pr, segs,
                        as<uint64_t>(b.terms), as<uint64_t>(b.coefs), as<uint64_t>(b.lhsmod), 0));
-    hipLaunchKernelGGL(k_grid_count, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, st, segs, nseg, (uint64_t)K, logw,
-                       as<uint64_t>(b.cnt), terms);
-    WV_HIP(launch_scan(st, as<uint64_t>(b.cnt), nseg, off, as<uint64_t>(b.tiles)));
+    hipLaunchKernelGGL(k_grid_runs, dim3((nruns + 255) / 256), dim3(256), 0, st, segs, n, nB, nE, tabs, g.tb, g.te,
+                       (uint64_t)K, logw, runs, as<uint64_t>(b.cnt), terms);
+    WV_HIP(launch_scan(st, as<uint64_t>(b.cnt), nruns, off, as<uint64_t>(b.tiles)));
     const unsigned inv_grid = (unsigned)c->num_cus * 8;
     double *inv = at(y.inv);
     switch (logw) {
-    case 8: launch_inv<4>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
-    case 9: launch_inv<8>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
-    case 10: launch_inv<16>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
-    default: launch_inv<32>(st, inv_grid, segs, off, (uint32_t)nseg, pr, K, logw, inv); break;
+    case 8: launch_inv<4>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
+    case 9: launch_inv<8>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
+    case 10: launch_inv<16>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
+    default: launch_inv<32>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
     }
-    hipLaunchKernelGGL(k_grid_fact, dim3(n), dim3(256), 0, st, pr, K, at(y.fact));
+    WV_TRY(with_chunks((int)(K + 1) / 256, [&](auto c) -> int {
+        hipLaunchKernelGGL(k_grid_fact<decltype(c)::value>, dim3(n), dim3(256), 0, st, pr, at(y.fact));
+        return WV_OK;
+    }));
     hipLaunchKernelGGL(k_grid_base, dim3(n), dim3(256), 0, st, pr, K, at(y.node0));
     double *node = at(y.node0), *next = at(y.node1);
     auto fwd = [&](int logl) -> int {
@@ -688,8 +763,11 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
     };
     for (int l = kNttMinLog; l < g.logl; l++) {
         const uint32_t k = (uint32_t)grid_k(l);
-        hipLaunchKernelGGL(k_grid_level, dim3(3 * n), dim3(256), 0, st, pr, K, k, at(y.beta), at(y.A), at(y.iA),
-                           at(y.cst));
+        WV_TRY(with_chunks((1 << l) / 256, [&](auto c) -> int {
+            hipLaunchKernelGGL(k_grid_level<decltype(c)::value>, dim3(3 * n), dim3(256), 0, st, pr, K, at(y.beta),
+                               at(y.pi), at(y.cst));
+            return WV_OK;
+        }));
         WV_TRY(fwd(l));
         WV_TRY(with_shape(l, [&](auto s) -> int {
             constexpr int LG = decltype(s)::value;
@@ -703,7 +781,7 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
         }));
         const uint64_t points = (uint64_t)n * 2 * (k + 1);
         hipLaunchKernelGGL(k_grid_combine, dim3((unsigned)((points + 255) / 256)), dim3(256), 0, st, pr, n, K, k, node,
-                           at(y.res), at(y.A), at(y.iA), at(y.cst), next);
+                           at(y.res), at(y.pi), at(y.cst), next);
         std::swap(node, next);
     }
     WV_TRY(fwd(g.logl));
@@ -715,23 +793,28 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
         a.beta = inv;
         a.uhat = at(y.uhat);
         a.tab = as<double>(c->ntt_tab[LG]);
-        a.out = at(y.scratch);
-        a.segs = segs;
+        a.out = at(y.vals);
+        a.runs = runs;
         a.off = off;
-        a.pairs = reinterpret_cast<Pair *>(at(y.pairs));
         a.counters = reinterpret_cast<unsigned long long *>(at(y.counters));
-        a.nseg = (uint32_t)nseg;
-        a.K = K;
+        a.nruns = nruns;
+        a.nruns_b = nruns_b;
         hipLaunchKernelGGL(k_grid_shift<LG>, dim3(grid_blocks(c, LG)), dim3(NttShape<LG>::T), 0, st, a);
         return WV_OK;
     }));
-    const Pair *pairs = reinterpret_cast<const Pair *>(at(y.pairs));
-    if (K < 2047)
-        hipLaunchKernelGGL(k_grid_join<1>, dim3((unsigned)((nseg + 3) / 4)), dim3(256), 0, st, segs, off, nseg, pr, pairs,
-                           K, as<Pair>(b.seg_pairs));
-    else
-        hipLaunchKernelGGL(k_grid_join<4>, dim3((unsigned)nseg), dim3(256), 0, st, segs, off, nseg, pr, pairs, K,
-                           as<Pair>(b.seg_pairs));
+    auto join = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        hipLaunchKernelGGL(k_grid_join<NW>, dim3(NW == 1 ? (unsigned)((nseg + 3) / 4) : (unsigned)nseg),
+                           dim3(NW == 1 ? 256 : 64 * NW), 0, st, segs, n, nB, nE, tabs, g.tb, g.te, runs, off, pr,
+                           at(y.vals), K, logw, as<Pair>(b.seg_pairs));
+    };
+    // a wave's reduction costs about what 50 of its terms or blocks do, so
+    // batches of many sums take few waves each (those of 4832 primes near 1e9
+    // 1.24 ms with eight, 0.5 with two), small ones enough to end soon
+    if (nseg < 2048) join(std::integral_constant<int, 8>{});
+    else if (K < 2047) join(std::integral_constant<int, 1>{});
+    else if (K < 8191) join(std::integral_constant<int, 2>{});
+    else join(std::integral_constant<int, 8>{});
     WV_HIP(hipGetLastError());
     WV_HIP(launch_finalize(st, table_store(c), pr, as<Pair>(b.seg_pairs), as<uint64_t>(b.coefs),
                            as<uint64_t>(b.lhsmod), n, nB, nE, d_out, nullptr));
@@ -758,17 +841,18 @@ int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, con
                  uint64_t pmax, unsigned long long *terms, wv_result *d_out) {
     if (n == 0) return WV_OK;
     for (int l = kNttMinLog; l <= g.logl; l++) WV_TRY(ntt_tables(c, l));
-    const unsigned blocks = grid_blocks(c, g.logl);
+    WV_TRY(runs_table(c));
     // sub-batches within the workspace bound
-    const size_t one = grid_layout(g, 64, pmax, 0).total / 64 + 1;
+    const size_t one = grid_layout(g, 64, pmax).total / 64 + 1;
     uint32_t step = (uint32_t)std::min<uint64_t>(n, std::max<uint64_t>(1, kGridBytes / one));
     step = std::min<uint32_t>(step, 1u << 16);
     const uint32_t parts = (n + step - 1) / step;
     step = (n + parts - 1) / parts;
-    const GridLayout y = grid_layout(g, step, pmax, blocks);
+    const GridLayout y = grid_layout(g, step, pmax);
     const uint64_t nseg = (uint64_t)step * (kTables[g.tb].n + kTables[g.te].n);
     WV_TRY(ensure(c, b.pr, step * sizeof(PrimeRec)));
     WV_TRY(ensure(c, b.segs, nseg * sizeof(SegRec)));
+    WV_TRY(ensure(c, b.runs, nseg * sizeof(SegRec)));   // no more runs than sums
     WV_TRY(ensure(c, b.terms, nseg * sizeof(uint64_t)));
     WV_TRY(ensure(c, b.cnt, nseg * sizeof(uint64_t)));
     WV_TRY(ensure(c, b.off, (nseg + 1) * sizeof(uint64_t)));
@@ -783,7 +867,7 @@ int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, con
 }
 
 void grid_free(GridWork &b) {
-    DevBuf *bufs[] = {&b.pr, &b.segs, &b.terms, &b.cnt, &b.off, &b.tiles, &b.seg_pairs, &b.coefs, &b.lhsmod, &b.ws};
+    DevBuf *bufs[] = {&b.pr, &b.segs, &b.runs, &b.terms, &b.cnt, &b.off, &b.tiles, &b.seg_pairs, &b.coefs, &b.lhsmod, &b.ws};
     for (DevBuf *x : bufs)
         if (x->ptr) (void)hipFree(x->ptr);
 }

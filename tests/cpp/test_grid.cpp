@@ -105,17 +105,34 @@ static void classes() {
         const uint64_t K = grid_k(c.logl), W = grid_w(c.logl);
         CHECK(W == K + 1);
         for (int t : {c.tb, c.te}) {
-            uint64_t shifts = 0;
-            for (int i = 0; i < kTables[t].n; i++) {
+            // a run's sums follow one another; its blocks need at most the bound
+            const GridRuns &g = grid_runs(t);
+            uint64_t shifts = 0, covered = 0;
+            auto ends = [&](int i, uint64_t &lo, uint64_t &len) {
                 const TermDef &d = kTables[t].t[i];
-                const uint64_t lo = (uint64_t)((u128)d.xa * p / d.xb) + 1, hi = (uint64_t)(((u128)d.ya * p - 1) / d.yb);
+                lo = (uint64_t)((u128)d.xa * p / d.xb) + 1;
+                len = (uint64_t)(((u128)d.ya * p - 1) / d.yb) - lo + 1;
                 CHECK(2 * (u128)d.ya <= d.yb);   // up to p / 2
-                const uint64_t len = hi - lo + 1, r = (len / K + W - 1) / W;
-                shifts += r;
-                // every denominator of the inverse list, 0 <= n < (r + 1) W, lies in (0, p)
-                CHECK(r == 0 || lo + K * ((r + 1) * W - 1) < p);
+            };
+            uint64_t lo, len, sums = 0;
+            for (int i = 0; i < kTables[t].n; i++) {
+                ends(i, lo, len);
+                sums += len;
+                CHECK(g.run[i] < g.n);
             }
-            CHECK(shifts <= grid_shifts(kTables[t], (double)p, c.logl));
+            for (int r = 0; r < g.n; r++) {
+                uint64_t a, b, la, lb;
+                ends(g.first[r], a, la);
+                ends(g.last[r], b, lb);
+                len = b + lb - a;
+                covered += len;
+                const uint64_t m = (len / K + W - 1) / W;
+                shifts += m;
+                // every denominator of the inverse list, 0 <= n < (m + 1) W, lies in (0, p)
+                CHECK(m == 0 || a + K * ((m + 1) * W - 1) < p);
+            }
+            CHECK(covered == sums || p % 3 == 0 || p % 5 == 0);   // (p prime: no endpoint is an integer)
+            CHECK(shifts <= grid_shifts(t, (double)p, c.logl));
         }
     }
 }
