@@ -285,12 +285,13 @@ typedef struct {
  * WV_ENOTPRIME, WV_ENOMEM, WV_EHIP. */
 int wv_bernoulli_euler_all(wv_ctx *ctx, uint64_t p, uint64_t *b, uint64_t *e);
 
-/* Kernel of the power sums behind wv_bernoulli_euler_all / wv_irregular_pairs:
- * 0 automatic (matrix cores for batches with every p < 2^24, where partial
- * sums of up to 1024 products, reduced mod p before they reach 2^53, stay
- * exact f64 integers; vector ALU otherwise),
- * 1 vector ALU always, 2 matrix cores where exact (same as 0).  Results do not
- * depend on it.  Errors: WV_EINVAL. */
+/* Method of wv_bernoulli_euler_all / wv_irregular_pairs:
+ * 0 automatic (the power sums of all exponents as one discrete Fourier
+ * transform per prime and side, by exact convolutions),
+ * 1 power sums on the vector ALU, 2 power sums on the matrix cores for batches
+ * with every p < 2^24 (where partial sums of up to 1024 products, reduced mod p
+ * before they reach 2^53, stay exact f64 integers; vector ALU otherwise).
+ * Results do not depend on it.  Errors: WV_EINVAL. */
 int wv_set_irregular_path(wv_ctx *ctx, int path);
 
 /* All irregular and E-irregular pairs of the primes p in [lo, hi) (p >= 5),

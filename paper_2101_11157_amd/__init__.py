@@ -424,8 +424,9 @@ class Context:
         return hb, he, nr[:n_near.value], n_primes.value
 
     def set_irregular_path(self, path):
-        """Power-sum kernel of the irregular-pair calls: 0 automatic, 1 vector
-        ALU, 2 matrix cores where exact (p < 2^24)."""
+        """Method of the irregular-pair calls: 0 automatic (one transform per
+        prime), 1 power sums on the vector ALU, 2 on the matrix cores where
+        exact (p < 2^24)."""
         _check(lib().wv_set_irregular_path(self._h, int(path)), "wv_set_irregular_path")
 
     def bernoulli_euler_all(self, p):

@@ -24,6 +24,7 @@
 // (2^51).
 #pragma once
 #include <cstdint>
+#include <type_traits>
 
 #include "sum_core.hpp"
 
@@ -445,7 +446,31 @@ __device__ __forceinline__ void ntt_inverse(double (&x)[NttShape<LOGL>::E], cons
     ntt_inv_from<LOGL, S::NT>(x, t1, lds, rt, f, tid);
 }
 
+// A vector of length L, every load requested before the first is used.
+template <int LOGL>
+__device__ __forceinline__ void load_vec(double (&x)[NttShape<LOGL>::E], const double *base, int tid) {
+    using S = NttShape<LOGL>;
+    const VecBuf b = vec_buf(base, S::L);
+WV_UNROLL
+    for (int e = 0; e < S::E; e++) x[e] = vec_load(b, tid, e * S::T);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 #endif
+
+// fn(integral_constant<int, logl>) for a compiled length
+template <class F>
+inline int with_shape(int logl, F &&fn) {
+    switch (logl) {
+    case 9: return fn(std::integral_constant<int, 9>{});
+    case 10: return fn(std::integral_constant<int, 10>{});
+    case 11: return fn(std::integral_constant<int, 11>{});
+    case 12: return fn(std::integral_constant<int, 12>{});
+    case 13: return fn(std::integral_constant<int, 13>{});
+    case 14: return fn(std::integral_constant<int, 14>{});
+    default: return -1   /* WV_EINVAL */;
+    }
+}
 
 // The residue mod p (< 0.51 p) of the integer c, |c| <= q1 q2 / 4, given r1 ==
 // c (mod q1), |r1| <= 0.51 q1, and r2 == c (mod q2), |r2| <= 10.3 q2: c = r1 +

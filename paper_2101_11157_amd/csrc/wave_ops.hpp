@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "mont.hpp"
+#include "sum_core.hpp"
 #include "wv_internal.hpp"
 
 namespace wv {
@@ -90,6 +91,24 @@ __device__ __forceinline__ void wave_pair_reduce(uint64_t &c0, uint64_t &c1, con
     c0 = readlane_u64(c0, 0);
     c1 = readlane_u64(c1, 0);
     pair_mul(c0, c1, d0, d1, m);
+}
+
+__device__ __forceinline__ Fmod fmod_of(uint64_t p) {
+    Fmod f;
+    f.p = (double)p;
+    f.pinv = 1.0 / f.p;
+    return f;
+}
+
+// a^e, e >= 1 the same for the whole wave (scalar control flow)
+__device__ __forceinline__ double f_pow_u(double a, uint64_t e, const Fmod &f) {
+    e = readfirst_u64(e);
+    double r = a;
+    for (int i = 62 - __builtin_clzll(e); i >= 0; i--) {
+        r = f_mulmod(r, r, f);
+        if ((e >> i) & 1) r = f_mulmod(r, a, f);
+    }
+    return r;
 }
 
 }  // namespace wv

@@ -842,7 +842,8 @@ int wv_destroy(wv_ctx *c) {
                       &c->seg_off, &c->seg_desc, &c->pad_primes, &c->stats_hist, &c->stats_near, &c->coefs,
                       &c->lhsmod, &c->tbl_head, &c->tbl_term, &c->tbl_limb, &c->tails, &c->tail_hist,
                       &c->irr_tasks, &c->irr_units, &c->irr_primes, &c->irr_roff, &c->irr_v, &c->irr_fix,
-                      &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e, &c->grid_tabs};
+                      &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e, &c->irr_dft,
+                      &c->irr_root, &c->irr_seq, &c->irr_hat, &c->grid_tabs};
     for (DevBuf *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     grid_free(c->grid);

@@ -132,7 +132,7 @@ struct wv_ctx {
     wv::DevBuf base_primes, primes, pr, segs, terms, cnt, off, tiles, scal, partials, seg_pairs, results,
         seg_counts, seg_bits, seg_off, seg_desc, pad_primes, stats_hist, stats_near, coefs, lhsmod, tbl_head,
         tbl_term, tbl_limb, tails, tail_hist, irr_tasks, irr_units, irr_primes, irr_roff, irr_v, irr_fix,
-        irr_counts, irr_pairs, irr_b, irr_e;
+        irr_counts, irr_pairs, irr_b, irr_e, irr_dft, irr_root, irr_seq, irr_hat;
     wv::GridWork grid;                             // grid path's records and workspace
     wv::DevBuf grid_tabs;                          // runs of the compiled tables (grid path)
     wv::DevBuf ntt_tab[wv::kNttMaxLog + 1];       // twiddle tables per log2 length (grid path)
@@ -146,7 +146,7 @@ struct wv_ctx {
     wv_progress_fn progress = nullptr;
     void *progress_user = nullptr;
     uint64_t launch_terms = 1ull << 44;
-    int irr_path = 0;                             // 0 automatic, 1 vector ALU, 2 matrix cores
+    int irr_path = 0;                             // 0 transforms, 1 vector ALU, 2 matrix cores where exact
     std::vector<wv::GraphEntry> graphs;
     std::vector<wv::TuneEntry> tune;
     void *scratch = nullptr;                      // this device's fixed scratch array (wv_eval_primes_static)
@@ -230,6 +230,9 @@ constexpr double kGraphSearchTerms = 17179869184.0;
 constexpr int kGraphNotTaken = 1;
 int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uint64_t pmax, wv_result *out,
                  size_t *n_out);
+// twiddle tables of transforms of length 2^logl (wv_grid.hip), uploaded once
+int ntt_tables(wv_ctx *c, int logl);
+
 // The grid path (wv_grid.hip) takes primes from this size on when the context
 // has its default congruences and no forced shape, chunk or progress callback.
 // Both paths measured on MI355X, microseconds per prime of a large window,

@@ -39,24 +39,6 @@ namespace {
 
 constexpr int kBaseK = 255;   // blocks whose node values are multiplied out
 
-__device__ __forceinline__ Fmod fmod_of(uint64_t p) {
-    Fmod f;
-    f.p = (double)p;
-    f.pinv = 1.0 / f.p;
-    return f;
-}
-
-// a^e, e >= 1 the same for the whole wave (scalar control flow)
-__device__ __forceinline__ double f_pow_u(double a, uint64_t e, const Fmod &f) {
-    e = readfirst_u64(e);
-    double r = a;
-    for (int i = 62 - __builtin_clzll(e); i >= 0; i--) {
-        r = f_mulmod(r, r, f);
-        if ((e >> i) & 1) r = f_mulmod(r, a, f);
-    }
-    return r;
-}
-
 // ---------------------------------------------------------------------------
 // plan: shifts per sum
 // ---------------------------------------------------------------------------
@@ -332,16 +314,6 @@ struct ShiftArgs {
     uint32_t nruns, nruns_b;
 };
 
-// A vector of length L, every load requested before the first is used.
-template <int LOGL>
-__device__ __forceinline__ void load_vec(double (&x)[NttShape<LOGL>::E], const double *base, int tid) {
-    using S = NttShape<LOGL>;
-    const VecBuf b = vec_buf(base, S::L);
-WV_UNROLL
-    for (int e = 0; e < S::E; e++) x[e] = vec_load(b, tid, e * S::T);
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 // One shift of a doubling step: residues mod q of every value vector at the
 // L/2 points, out[((item 4 + j) 2 + q) L/2 + t]; a workgroup per (item =
 // prime 3 + shift, modulus).
@@ -594,19 +566,6 @@ uint32_t bitrev(uint32_t v, int bits) {
 }
 
 template <class F>
-int with_shape(int logl, F &&fn) {
-    switch (logl) {
-    case 9: return fn(std::integral_constant<int, 9>{});
-    case 10: return fn(std::integral_constant<int, 10>{});
-    case 11: return fn(std::integral_constant<int, 11>{});
-    case 12: return fn(std::integral_constant<int, 12>{});
-    case 13: return fn(std::integral_constant<int, 13>{});
-    case 14: return fn(std::integral_constant<int, 14>{});
-    default: return WV_EINVAL;
-    }
-}
-
-template <class F>
 int with_chunks(int c, F &&fn) {
     switch (c) {
     case 1: return fn(std::integral_constant<int, 1>{});
@@ -632,6 +591,8 @@ int upload_once(wv_ctx *c, DevBuf &buf, const void *h, size_t bytes) {
     }
     return WV_OK;
 }
+
+}  // namespace
 
 // Twiddle tables of one length (both moduli), uploaded once per context.
 int ntt_tables(wv_ctx *c, int logl) {
@@ -662,6 +623,8 @@ int ntt_tables(wv_ctx *c, int logl) {
     WV_TRY(rc);
     return upload_once(c, buf, h.data(), h.size() * sizeof(double));
 }
+
+namespace {
 
 // The runs of the compiled tables, uploaded once per context.
 int runs_table(wv_ctx *c) {
