@@ -90,71 +90,142 @@ __global__ void __launch_bounds__(1024) k_base_sieve(uint32_t *out, uint32_t *n_
     if (tid == 1023) *n_out = scan[1023];
 }
 
+// Words of a segment's bitmap that hold numbers below H = min(L + 2^20, hi).
+__device__ inline uint32_t seg_words(const SegDesc &d) {
+    const uint64_t H = min(d.L + kSegSpan, d.hi);
+    return H <= d.L ? 0 : (uint32_t)min((uint64_t)kSegWords, (H - d.L + 63) >> 6);
+}
+
+// Bit of the first odd multiple of q that is >= max(q^2, first), ~0 where q^2
+// >= H.  The quotient in doubles (numbers below 2^53), put right by one step.
+__device__ inline uint32_t first_mark(uint32_t q, uint64_t L, uint64_t first, uint64_t H) {
+    const uint64_t qq = (uint64_t)q * q;
+    if (qq >= H) return ~0u;
+    const uint64_t x = max(qq, first);
+    const double xd = (double)x, qd = (double)q;
+    double r = fma(-floor(xd * (1.0 / qd)), qd, xd);
+    if (r < 0.0) r += qd;
+    if (r >= qd) r -= qd;
+    uint32_t at = (uint32_t)(x - L) + (r > 0.0 ? q - (uint32_t)r : 0);
+    if (!(at & 1)) at += q;
+    return at >> 1;
+}
+
 // Segment desc[blockIdx.x]; bit i stands for L + 2i + 1.  Marks odd multiples
 // of every odd base prime q with q^2 < min(L + 2^20, hi), then keeps the
 // primes p with max(lo, 5) <= p < hi.  Writes the count to counts[seg] and,
-// when bits_out is non-null, the prime bitmap (1 = prime) to
-// bits_out + seg * kSegWords.
+// when bits_out is non-null, the prime bitmap (1 = prime; the words that
+// seg_words counts) to bits_out + seg * kSegWords.
+//
+// Bound by the LDS atomics of the marks, one per multiple, and by the first
+// multiples before them.  The primes up to 31 (six marks in ten) come as whole
+// words of a pattern; the next kSegCoop, at most where each has 48 multiples, are
+// strided by one wave each, the rest by one lane each; every first multiple is
+// found once, in doubles.  954 whole segments at 1e11: 0.20 ms (1.31 ms with
+// every small prime strided by the whole workgroup, each thread dividing 64-bit
+// integers for it); the one segment of the primes below 1e5 19 us (58 us).
+constexpr int kSegSmall = 10;
+constexpr int kSegSmallQ[kSegSmall] = {3, 5, 7, 11, 13, 17, 19, 23, 29, 31};
+constexpr int kSegPat = 158;                 // their residues
+constexpr uint32_t kSegCoop = 1024;
+
 __global__ void __launch_bounds__(1024) k_seg_sieve(const SegDesc *__restrict__ desc,
                                                     const uint32_t *__restrict__ bp, uint32_t n_bp,
                                                     uint32_t *__restrict__ bits_out,
                                                     uint32_t *__restrict__ counts) {
     __shared__ uint32_t bits[kSegWords];
+    __shared__ uint32_t pat[kSegPat];        // words with the bits = s mod q, s < q
+    __shared__ uint32_t start[kSegCoop];
     __shared__ uint32_t red[16];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const SegDesc d = desc[blockIdx.x];
     const uint64_t L = d.L, lo = d.lo, hi = d.hi;
     const uint64_t H = min(L + kSegSpan, hi);
-    for (int w = tid; w < kSegWords; w += 1024) bits[w] = 0;
-    __syncthreads();
     // only [max(lo, L + 1), H) is kept (the count masks the rest): composites
     // are marked there, bits i < i_end hold n = L + 2i + 1 up to H
     const uint64_t first = max(lo, L + 1);
-    const uint64_t i_end = min((uint64_t)kSegBits, (H - L + 1) >> 1);
-    // primes below 2048 (the first 308 odd ones): all threads stride one prime
-    const uint32_t n_coop = min(n_bp, 308u);
-    for (uint32_t k = 0; k < n_coop; k++) {
-        const uint64_t q = bp[k];
-        if (q * q >= H) break;
-        uint64_t x = max(q * q, first);
-        uint64_t m0 = ((x + q - 1) / q) * q;
-        if (!(m0 & 1)) m0 += q;
-        const uint64_t i0 = (m0 - L - 1) >> 1;
-        for (uint64_t i = i0 + (uint64_t)tid * q; i < i_end; i += 1024 * q)
-            atomicOr(&bits[i >> 5], 1u << (i & 31));
+    const uint32_t i_end = H <= L ? 0u : (uint32_t)min((uint64_t)kSegBits, (H - L + 1) >> 1), nw = seg_words(d);
+    const uint32_t range = H > first ? (uint32_t)((H - first + 1) >> 1) : 0;   // odd numbers that matter
+    {
+        int at = tid;
+WV_UNROLL
+        for (int k = 0; k < kSegSmall; k++) {
+            const int q = kSegSmallQ[k];
+            if (at >= 0 && at < q) {
+                uint32_t v = 0;
+                for (int b = at; b < 32; b += q) v |= 1u << b;
+                pat[tid] = v;
+            }
+            at -= q;
+        }
     }
-    // larger primes: one prime per thread
-    for (uint32_t k = n_coop + tid; k < n_bp; k += 1024) {
-        const uint64_t q = bp[k];
-        if (q * q >= H) break;
-        uint64_t x = max(q * q, first);
-        uint64_t m0 = ((x + q - 1) / q) * q;
-        if (!(m0 & 1)) m0 += q;
-        for (uint64_t i = (m0 - L - 1) >> 1; i < i_end; i += q)
-            atomicOr(&bits[i >> 5], 1u << (i & 31));
+    const uint32_t k0 = min(n_bp, (uint32_t)kSegSmall + tid);
+    const uint32_t my_q = k0 < n_bp ? bp[k0] : 0;
+    // primes with at least 48 multiples in range are a wave's (ascending: a prefix)
+    const bool coop = my_q && (uint64_t)my_q * 48 <= range;
+    if (coop) start[tid] = first_mark(my_q, L, first, H);
+    const uint32_t n_coop = (uint32_t)__syncthreads_count(coop);
+    {
+        int s[kSegSmall];                    // (first multiple's bit - 32 w) mod q for word w
+WV_UNROLL
+        for (int k = 0; k < kSegSmall; k++) {
+            const uint32_t q = kSegSmallQ[k];
+            const uint32_t i0 = (q - (uint32_t)((L + 1) % q)) * ((q + 1) / 2);
+            s[k] = (int)((i0 + q * 32768u - 32u * tid) % q);
+        }
+        for (uint32_t w = tid; w < nw; w += 1024) {
+            uint32_t v = 0;
+            int base = 0;
+WV_UNROLL
+            for (int k = 0; k < kSegSmall; k++) {
+                const int q = kSegSmallQ[k];
+                v |= pat[base + s[k]];
+                base += q;
+                s[k] -= 32768 % q;
+                if (s[k] < 0) s[k] += q;
+            }
+            bits[w] = v;
+        }
     }
     __syncthreads();
-    // keep max(lo,5) <= n < hi, n = L + 2i + 1
+    // the small primes themselves
+    if (tid == 0) {
+        for (int k = 0; k < kSegSmall; k++) {
+            const uint64_t q = kSegSmallQ[k], i = (q - L - 1) >> 1;
+            if (q > L && i < (uint64_t)i_end) atomicAnd(&bits[i >> 5], ~(1u << (i & 31)));
+        }
+    }
+    for (uint32_t k = wave; k < n_coop; k += 16) {
+        const uint32_t q = __builtin_amdgcn_readfirstlane(bp[kSegSmall + k]);
+        const uint32_t i0 = __builtin_amdgcn_readfirstlane(start[k]);
+        if (i0 == ~0u) break;
+        for (uint32_t i = i0 + lane * q; i < i_end; i += 64 * q) atomicOr(&bits[i >> 5], 1u << (i & 31));
+    }
+    for (uint32_t k = kSegSmall + n_coop + tid; k < n_bp; k += 1024) {
+        const uint32_t q = bp[k];
+        const uint32_t i0 = first_mark(q, L, first, H);
+        if (i0 == ~0u) break;
+        for (uint32_t i = i0; i < i_end; i += q) atomicOr(&bits[i >> 5], 1u << (i & 31));
+    }
+    __syncthreads();
+    // keep max(lo,5) <= n < H, n = L + 2i + 1: bits [a, b)
     const uint64_t nlo = max(lo, (uint64_t)5);
+    const int64_t a = nlo > L + 1 ? (int64_t)((nlo - L) >> 1) : 0, b = H > L ? (int64_t)((H - L) >> 1) : 0;
     uint32_t cnt = 0;
-    for (int w = tid; w < kSegWords; w += 1024) {
+    for (uint32_t w = tid; w < nw; w += 1024) {
+        const int64_t w0 = 32 * (int64_t)w;
         uint32_t v = ~bits[w];
-        const uint64_t n0 = L + 64ull * w + 1;           // number of bit 0 of this word
-        const uint64_t n31 = n0 + 62;
-        if (n0 < nlo || n31 >= hi) {
-            uint32_t mask = 0;
-            for (int b = 0; b < 32; b++) {
-                uint64_t n = n0 + 2ull * b;
-                if (n >= nlo && n < hi) mask |= 1u << b;
-            }
-            v &= mask;
+        if (w0 + 32 <= a || w0 >= b) v = 0;
+        else {
+            if (w0 < a) v &= ~0u << (a - w0);
+            if (w0 + 32 > b) v &= ~0u >> (w0 + 32 - b);
         }
         if (bits_out) bits_out[(size_t)blockIdx.x * kSegWords + w] = v;
         cnt += __popc(v);
     }
     // block sum of the counts
     for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor((int)cnt, off, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = cnt;
+    if (lane == 0) red[wave] = cnt;
     __syncthreads();
     if (tid == 0) {
         uint32_t t = 0;
@@ -163,27 +234,32 @@ __global__ void __launch_bounds__(1024) k_seg_sieve(const SegDesc *__restrict__ 
     }
 }
 
-// Writes the primes of segment blockIdx.x, ascending, at out + off[seg].
+// Writes the primes of segment blockIdx.x, ascending, at out + off[seg]; the
+// words that hold numbers are shared by all threads (12 us for the primes below
+// 1e5, 20 us with 16 words each, most threads without any).
 __global__ void __launch_bounds__(1024) k_seg_compact(const SegDesc *__restrict__ desc,
                                                       const uint32_t *__restrict__ bits_in,
                                                       const uint64_t *__restrict__ off,
                                                       uint64_t *__restrict__ out, uint64_t limit) {
-    __shared__ uint32_t scan[1024];
-    const int tid = threadIdx.x;
+    __shared__ uint32_t part[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t *bits = bits_in + (size_t)blockIdx.x * kSegWords;
-    const uint64_t L = desc[blockIdx.x].L;
+    const SegDesc d = desc[blockIdx.x];
+    const uint64_t L = d.L;
+    const uint32_t nw = seg_words(d), per = (nw + 1023) / 1024;
+    const uint32_t w0 = min(nw, tid * per), w1 = min(nw, w0 + per);
     uint32_t cnt = 0;
-    for (int w = tid * 16; w < tid * 16 + 16; w++) cnt += __popc(bits[w]);
-    scan[tid] = cnt;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        uint32_t v = tid >= o ? scan[tid - o] : 0;
-        __syncthreads();
-        scan[tid] += v;
-        __syncthreads();
+    for (uint32_t w = w0; w < w1; w++) cnt += __popc(bits[w]);
+    uint32_t inc = cnt;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)inc, o, 64);
+        if (lane >= o) inc += v;
     }
-    uint64_t pos = off[blockIdx.x] + scan[tid] - cnt;
-    for (int w = tid * 16; w < tid * 16 + 16; w++) {
+    if (lane == 63) part[wave] = inc;
+    __syncthreads();
+    uint64_t pos = off[blockIdx.x] + inc - cnt;
+    for (int q = 0; q < wave; q++) pos += part[q];
+    for (uint32_t w = w0; w < w1; w++) {
         uint32_t v = bits[w];
         while (v) {
             int b = __ffs(v) - 1;
