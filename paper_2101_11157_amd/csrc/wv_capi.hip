@@ -420,7 +420,10 @@ int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector
         WV_TRY(ensure(c, c->results, got * sizeof(wv_result)));
         uint64_t pmax = 0;
         for (size_t k = i; k < j; k++) pmax = std::max(pmax, std::min(descs[k].hi, descs[k].L + kSegSpan));
-        if (grid)
+        DirectShape ds;
+        if (direct_takes(c, got, pmax, &ds))
+            WV_TRY(direct_batch_sync(c, ds, as<uint64_t>(c->primes), (uint32_t)got, as<wv_result>(c->results)));
+        else if (grid)
             WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
         else
             WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
@@ -654,15 +657,21 @@ uint64_t prime_count_bound(uint64_t lo, uint64_t hi) {
 // The device counts the primes; the count, the batch's scalars and the
 // results come back after the call's one wait.  d: the segments (at most
 // kMaxBatchSegs), in ascending order, so the compacted primes ascend.
-int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uint64_t pmax, wv_result *out,
+int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uint64_t n_est, uint64_t pmax, wv_result *out,
                  size_t *n_out) {
     hipStream_t st = c->stream;
     const uint64_t ns = d.size();
     const uint64_t n_pad = (n_bound + 1023) & ~1023ull;
-    BatchShape sh;
-    WV_TRY(batch_shape(c, (uint32_t)n_pad, pmax, &sh));
-    if (sh.nseg > kMaxBatchSlots) return kGraphNotTaken;   // more than one batch: the counted path
-    WV_TRY(prepare(c, sh));
+    BatchShape sh{};
+    DirectShape ds;
+    const bool direct = direct_takes(c, n_est, pmax, &ds);
+    if (direct) {
+        WV_TRY(direct_reserve(c, (uint32_t)n_pad, ds));
+    } else {
+        WV_TRY(batch_shape(c, (uint32_t)n_pad, pmax, &sh));
+        if (sh.nseg > kMaxBatchSlots) return kGraphNotTaken;   // more than one batch: the counted path
+        WV_TRY(prepare(c, sh));
+    }
     WV_TRY(ensure(c, c->seg_desc, ns * sizeof(SegDesc)));
     WV_TRY(ensure(c, c->seg_counts, ns * sizeof(uint32_t)));
     WV_TRY(ensure(c, c->seg_bits, ns * kSegWords * sizeof(uint32_t)));
@@ -674,7 +683,8 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
     hipGraphExec_t exec = nullptr;
     for (GraphEntry &g : c->graphs)
         if (g.ns == ns && g.n_pad == n_pad && g.gen == c->gen && g.variant == c->variant && g.tb == c->tb &&
-            g.te == c->te && g.chunk == chunk && g.tbl_b == sh.tb && g.tbl_e == sh.te)
+            g.te == c->te && g.chunk == chunk && g.tbl_b == sh.tb && g.tbl_e == sh.te &&
+            g.direct == (direct ? ds.key() : 0))
             exec = g.exec;
     if (!exec) {
         WV_HIP(hipStreamSynchronize(st));   // the capture stream must be idle
@@ -691,9 +701,13 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
             launch_seg_compact(st, as<SegDesc>(c->seg_desc), (unsigned)ns, as<uint32_t>(c->seg_bits),
                                as<uint64_t>(c->seg_off), primes, n_pad) != hipSuccess)
             rc = WV_EHIP;
-        if (rc == WV_OK) rc = enqueue_plan(c, bufs, primes, sh, st);
-        if (rc == WV_OK) rc = enqueue_sum(c, bufs, sh, st, 0, UINT64_MAX);
-        if (rc == WV_OK) rc = enqueue_finish(c, bufs, sh, st, as<wv_result>(c->results));
+        if (rc == WV_OK && direct) {
+            rc = direct_enqueue(c, ds, primes, (uint32_t)n_pad, as<wv_result>(c->results));
+        } else {
+            if (rc == WV_OK) rc = enqueue_plan(c, bufs, primes, sh, st);
+            if (rc == WV_OK) rc = enqueue_sum(c, bufs, sh, st, 0, UINT64_MAX);
+            if (rc == WV_OK) rc = enqueue_finish(c, bufs, sh, st, as<wv_result>(c->results));
+        }
         hipError_t e = hipStreamEndCapture(st, &graph);
         if (rc != WV_OK) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -707,6 +721,7 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
         g.ns = ns;
         g.tbl_b = sh.tb;
         g.tbl_e = sh.te;
+        g.direct = direct ? ds.key() : 0;
         c->graphs.push_back(g);
     }
     WV_HIP(hipMemcpyAsync(c->seg_desc.ptr, d.data(), ns * sizeof(SegDesc), hipMemcpyHostToDevice, st));
@@ -727,6 +742,10 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
     const double ms = elapsed(c->ev[EV_PLAN0], c->ev[EV_FINAL]);
     s.ms_total += ms;
     s.ms_sum += ms;   // one graph: the phases are not timed apart
+    if (direct) {
+        direct_stats(c, ds, n, host);
+        return WV_OK;
+    }
     s.n_primes += n;
     s.n_sums += n * (sh.nB + sh.nE);
     s.n_chunks += host[kScalChunks];
@@ -843,7 +862,8 @@ int wv_destroy(wv_ctx *c) {
                       &c->lhsmod, &c->tbl_head, &c->tbl_term, &c->tbl_limb, &c->tails, &c->tail_hist,
                       &c->irr_tasks, &c->irr_units, &c->irr_primes, &c->irr_roff, &c->irr_v, &c->irr_fix,
                       &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e, &c->irr_dft,
-                      &c->irr_root, &c->irr_seq, &c->irr_hat, &c->grid_tabs};
+                      &c->irr_root, &c->irr_seq, &c->irr_hat, &c->grid_tabs, &c->direct_terms, &c->direct_part,
+                      &c->direct_ticket};
     for (DevBuf *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     grid_free(c->grid);
@@ -987,14 +1007,20 @@ int wv_search_windows(wv_ctx *c, const uint64_t *lo, const uint64_t *hi, size_t 
     first[nwin] = d.size();
     // a small single-window search: one graph, sized by the prime-count bound
     GridClass gc;
-    if (nwin == 1 && out && !d.empty() && d.size() <= kMaxBatchSegs && !c->progress && !desc_grid(c, d[0], &gc)) {
+    if (nwin == 1 && out && !d.empty() && d.size() <= kMaxBatchSegs && !c->progress) {
         const uint64_t bound = prime_count_bound(std::max<uint64_t>(lo[0], 5), hi[0]);
         const double work = (double)bound * (double)pmax * (side_cost(c, c->tb) + side_cost(c, c->te));
-        if (bound <= cap && bound <= kMaxBatchPrimes && work <= kGraphSearchTerms) {
+        // about as many as there are (the bound is up to three times that): the
+        // shape of the launch and the choice of the path
+        const double mid = std::max(10.0, 0.5 * ((double)lo[0] + (double)hi[0]));
+        const uint64_t est = std::min<uint64_t>(bound, 16 + (uint64_t)(1.1 * (double)(hi[0] - lo[0]) / std::log(mid)));
+        DirectShape ds;
+        if (bound <= cap && bound <= kMaxBatchPrimes && work <= kGraphSearchTerms &&
+            (!desc_grid(c, d[0], &gc) || direct_takes(c, est, pmax + 1, &ds))) {
             c->stats = wv_stats{};
             pick_tuned(c, pmax);
             size_t n = 0;
-            const int rc = search_graph(c, d, bound, pmax + 1, out, &n);
+            const int rc = search_graph(c, d, bound, est, pmax + 1, out, &n);
             if (rc != kGraphNotTaken) {
                 if (rc != WV_OK) return rc;
                 *n_out = n;
@@ -1114,6 +1140,11 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
     WV_TRY(ensure(c, c->primes, n * sizeof(uint64_t)));
     WV_TRY(ensure(c, c->results, n * sizeof(wv_result)));
     WV_HIP(hipMemcpyAsync(c->primes.ptr, primes, n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
+    DirectShape ds;
+    if (direct_takes(c, n, pmax, &ds)) {
+        WV_TRY(direct_batch_sync(c, ds, as<uint64_t>(c->primes), (uint32_t)n, as<wv_result>(c->results)));
+        return results_to_host(c, as<wv_result>(c->results), n, out);
+    }
     // the primes of the grid path first, by class, the others (ascending
     // too) after them; results go back to input order
     std::vector<std::pair<uint64_t, size_t>> ord;

@@ -90,6 +90,7 @@ struct GraphEntry {
     hipGraphExec_t exec;
     uint64_t ns = 0;       // search graphs: sieve segments (0: the eval graph)
     int tbl_b = -1, tbl_e = -1;   // search graphs: the batch's table choice
+    uint64_t direct = 0;          // search graphs: shape of the direct path (0: term sums)
 };
 
 // Device buffers of one grid-path batch: the plan's records and a workspace.
@@ -133,6 +134,7 @@ struct wv_ctx {
         seg_counts, seg_bits, seg_off, seg_desc, pad_primes, stats_hist, stats_near, coefs, lhsmod, tbl_head,
         tbl_term, tbl_limb, tails, tail_hist, irr_tasks, irr_units, irr_primes, irr_roff, irr_v, irr_fix,
         irr_counts, irr_pairs, irr_b, irr_e, irr_dft, irr_root, irr_seq, irr_hat;
+    wv::DevBuf direct_terms, direct_part, direct_ticket;   // the direct path: terms, fractions, tickets
     wv::GridWork grid;                             // grid path's records and workspace
     wv::DevBuf grid_tabs;                          // runs of the compiled tables (grid path)
     wv::DevBuf ntt_tab[wv::kNttMaxLog + 1];       // twiddle tables per log2 length (grid path)
@@ -228,10 +230,41 @@ constexpr double kGraphSearchTerms = 17179869184.0;
 // Returns kGraphNotTaken (and does nothing) when the batch would exceed one
 // batch's slots; the caller then takes the counted path.
 constexpr int kGraphNotTaken = 1;
-int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uint64_t pmax, wv_result *out,
+// n_est: about how many primes there will be
+int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uint64_t n_est, uint64_t pmax, wv_result *out,
                  size_t *n_out);
 // twiddle tables of transforms of length 2^logl (wv_grid.hip), uploaded once
 int ntt_tables(wv_ctx *c, int logl);
+
+// The direct path (wv_direct.hip): batches of little work, contexts as for the
+// grid path.  Measured on MI355X, ms a call, term sums (or grid path) / direct:
+//   n primes below 2^27, by their terms in all: 4e6 x 4096 (1.4e9 terms) 0.95 /
+//   0.80, 1e7 x 1024 (0.9e9) 0.70 / 0.46, x 4096 (3.6e9) 1.43 / 1.76, 2e7 x 1024
+//   (1.8e9) 0.86 / 0.80, 4e7 x 256 (0.9e9) 0.66 / 0.53, 8e7 x 256 (1.8e9) 0.88 /
+//   0.96, one prime at 1e8 0.53 / 0.08;
+//   every batch of small primes, whose (prime, sum) records cost more than the
+//   terms: 1e6 x 20000 1.97 / 1.01, 4e6 x 20000 2.83 / 2.83;
+//   from 2^27 on, where a product is six operations: 1.4e8 x 64 (0.8e9) 0.58 / 0.53,
+//   3e8 x 16 (0.4e9) 0.40 / 0.31, x 64 (1.7e9) 0.52 / 0.91, one prime at 3e9 (0.26e9)
+//   0.39 / 0.22, at 1e10 (0.9e9) 0.50 / 0.54.
+constexpr uint64_t kDirectSmallP = 1ull << 27;   // products exact in double precision below
+constexpr uint64_t kDirectAllP = 3ull << 20;
+constexpr double kDirectSmallTerms = 1.6e9, kDirectTerms = 5e8;
+// Lanes the primes of a batch share, and the least terms for one: 2^20 are 16
+// waves for each SIMD, rounds enough to even out the ends (2e7 x 1024: 0.80 ms,
+// with 2^19 0.98 ms).
+constexpr double kDirectLanes = 1048576.0, kDirectLaneTerms = 48.0;
+struct DirectShape {
+    bool small;              // p < kDirectSmallP
+    uint32_t G, threads;     // workgroups per prime and their threads
+    uint64_t key() const { return (uint64_t)G << 32 | threads << 1 | (small ? 1 : 0); }
+};
+// whether a batch of n primes <= pmax goes this way
+bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, DirectShape *d);
+int direct_reserve(wv_ctx *c, uint32_t n, const DirectShape &d);
+int direct_enqueue(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, uint32_t n, wv_result *d_out);
+int direct_batch_sync(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, uint32_t n, wv_result *d_out);
+void direct_stats(wv_ctx *c, const DirectShape &d, uint64_t n, const uint64_t *scal);
 
 // The grid path (wv_grid.hip) takes primes from this size on when the context
 // has its default congruences and no forced shape, chunk or progress callback.

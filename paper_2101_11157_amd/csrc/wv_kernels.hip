@@ -356,32 +356,6 @@ __global__ void __launch_bounds__(256) k_scan_add(uint64_t *__restrict__ out, ui
 // plan
 // --------------------------------------------------------------------------
 
-// A signed integer of any size (limbs of its magnitude, base 2^32, least
-// significant first) mod p, canonical.
-__device__ uint64_t limbs_mod(const uint32_t *__restrict__ limb, uint32_t off, int nlimb, bool neg, uint64_t p) {
-    uint64_t r = 0;
-    for (int k = nlimb - 1; k >= 0; k--) r = shift_in_limb(r, limb[off + k], p);
-    return neg && r ? p - r : r;
-}
-
-// Table of one side for prime p: the configured one where it applies, else
-// the table it names for the primes it does not serve (a chain of defined
-// tables with falling min_p that ends at a compiled table; fb if a chain were
-// ever longer than the registry); the root forms for p = 5 and 7 (readings of
-// the paper: the specialised tables need p >= 11).
-__device__ int pick_table(TableStore ts, int side, uint64_t p, int cfg, int fb) {
-    if (side == 0 && p == 5) return WV_TABLE_BB1;
-    if (side == 0 && p == 7) return WV_TABLE_V12;
-    if (side == 1 && p < 11) return WV_TABLE_E1;
-    int t = cfg;
-    for (int hop = 0; hop <= kMaxTableChain && t >= WV_TABLE_COUNT; hop++) {
-        const TableHead h = ts.head[t];
-        if (p >= h.min_p && limbs_mod(ts.limb, h.lhs_off, h.lhs_nlimb, false, p) != 0) return t;
-        t = h.below;
-    }
-    return t >= WV_TABLE_COUNT ? fb : t;
-}
-
 // One thread per prime: PrimeRec, the table of each side and the residues of
 // their left sides.
 __global__ void __launch_bounds__(256) k_plan_primes(const uint64_t *__restrict__ primes, uint32_t n, int tb_cfg,
