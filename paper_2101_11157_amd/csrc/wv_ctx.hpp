@@ -268,11 +268,11 @@ void direct_stats(wv_ctx *c, const DirectShape &d, uint64_t n, const uint64_t *s
 
 // The grid path (wv_grid.hip) takes primes from this size on when the context
 // has its default congruences and no forced shape, chunk or progress callback.
-// Both paths measured on MI355X, microseconds per prime of a large window,
-// term sums / grid: 4e7 0.69 / 1.00, 1e8 1.45 / 1.42, 1e9 13.2 / 5.2, 1e10 139
-// / 23, 1e11 1295 / 87; of 64 primes alone the grid wins from 2e8 (0.82 / 0.68
-// ms a call) and loses at 1e8 (0.64 / 0.73).
-constexpr uint64_t kGridMinP = 1ull << 27;
+// Both paths measured on MI355X, microseconds per prime of a window of 20000,
+// term sums / grid: 4e7 0.81 / 0.83, 6e7 0.83 / 0.89, 8e7 1.09 / 1.02, 1e8 1.35 /
+// 1.11, 1.3e8 1.71 / 1.24, 2e8 2.64 / 1.53, 1e9 13.2 / 4.0, 1e11 1295 / 70; of
+// 256 primes alone, ms a call: 6e7 0.98 / 1.08, 8e7 1.06 / 0.93.
+constexpr uint64_t kGridMinP = 9ull << 23;
 bool grid_allowed(const wv_ctx *c, int tb, int te);   // with these tables configured
 bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g);
 // n primes in [4 * 4^logl, pmax] on the device -> d_out, enqueued on st with
