@@ -18,6 +18,12 @@ struct GridClass {
     bool operator==(const GridClass &o) const { return logl == o.logl && tb == o.tb && te == o.te; }
 };
 
+// The longest transform of one workgroup is 2^kNttMaxLog; one of twice that is
+// split into two of them (below 2^39, where its sums of 2^14 products stay
+// below a quarter of the moduli's product).
+constexpr int kGridMaxLog = kNttMaxLog + 1;
+constexpr uint64_t kGridSplitMaxP = 1ull << 39;
+
 constexpr uint64_t grid_k(int logl) { return (1ull << (logl - 1)) - 1; }
 constexpr uint64_t grid_w(int logl) { return 1ull << (logl - 1); }
 
@@ -86,10 +92,12 @@ inline double grid_shifts_est(int id, double p, int logl) {
 }
 
 // Operations of a pair of transforms (both moduli) of length L: about 50 per
-// element and modulus at every length used.
+// element and modulus at every length used; a split one, bound by memory, takes
+// 1.4 times as long (330 primes, split / whole: 3e10 9.9 / 9.2 ms, 5e10 12.8 /
+// 13.5, 1e11 19.7 / 22.2, 4e11 57.6 / 86.0).
 inline double grid_pair_ops(int logl) {
     const double L = (double)(1ull << logl);
-    return 2.0 * L * (14.0 + 2.6 * logl);
+    return 2.0 * L * (14.0 + 2.6 * logl) * (logl > kNttMaxLog ? 1.4 : 1.0);
 }
 
 // One side's operations per prime: each shift transforms its kernel and brings
@@ -116,11 +124,11 @@ inline double grid_build_ops(int logl) {
 // The least modelled work over the lengths and compiled congruences for primes
 // near p.  A length needs p >= 4 L^2: every
 // difference of two points, at most p/2 + 2 K W, is then below p and nonzero.
-inline GridClass grid_search(uint64_t p) {
+inline GridClass grid_search(uint64_t p, int max_log) {
     GridClass best;
     best.ops = 1e300;
-    for (int logl = kNttMinLog; logl <= kNttMaxLog; logl++) {
-        if (p < (4ull << (2 * logl))) break;
+    for (int logl = kNttMinLog; logl <= max_log; logl++) {
+        if (p < (4ull << (2 * logl)) || (logl > kNttMaxLog && p >= kGridSplitMaxP)) break;
         GridClass c;
         c.logl = logl;
         double b = 1e300, e = 1e300;
@@ -137,17 +145,34 @@ inline GridClass grid_search(uint64_t p) {
 
 // The grid path's class for p: that of the least prime of its sixteenth of an
 // octave (so primes of one size share a class), searched once per process.
-inline const GridClass &grid_class(uint64_t p) {
+inline const GridClass &grid_class(uint64_t p, int max_log = kGridMaxLog) {
     struct Table {
-        GridClass c[16 * 41];
+        GridClass c[2][16 * 41];
         Table() {
-            for (int i = 0; i < 16 * 41; i++) c[i] = grid_search((uint64_t)std::ceil(std::exp2(i / 16.0)));
+            for (int i = 0; i < 16 * 41; i++)
+                for (int k = 0; k < 2; k++) c[k][i] = grid_search((uint64_t)std::ceil(std::exp2(i / 16.0)), kNttMaxLog + k);
         }
     };
     static const Table t;
     int i = std::min((int)(std::log2((double)p) * 16.0), 16 * 41 - 1);
     while (i > 0 && p < (uint64_t)std::ceil(std::exp2(i / 16.0))) i--;   // rounding of the logarithm
-    return t.c[i];
+    // (the last prime of a sixteenth may lie beyond the split's range when its first does not)
+    const bool split = max_log > kNttMaxLog && p < kGridSplitMaxP;
+    return t.c[split ? 1 : 0][i];
+}
+
+// The class a batch of n primes up to pmax of class g runs in.  Few primes: the
+// rounds of shifts the 256 CUs take, a split one 3.2 times as long as a whole one
+// (331 and 104 us), and one more doubling step (half a round): 7 primes at 1e11
+// take 1.28 ms split and 1.03 whole, 9 at 2e11 1.64 and 1.90.
+inline const GridClass &grid_batch_class(const GridClass &g, uint64_t n, uint64_t pmax) {
+    if (g.logl <= kNttMaxLog) return g;
+    const GridClass &whole = grid_class(pmax, kNttMaxLog);
+    auto rounds = [&](const GridClass &c) {
+        return std::ceil((double)n / 256.0 * (grid_shifts_est(c.tb, (double)pmax, c.logl) +
+                                              grid_shifts_est(c.te, (double)pmax, c.logl)));
+    };
+    return n < 256 && 3.2 * rounds(g) + 0.5 > rounds(whole) ? whole : g;
 }
 
 // Operations per prime near p in class g.

@@ -106,6 +106,19 @@ __device__ __forceinline__ void vec_store(const VecBuf &b, int i, int k, double 
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), b.r, i * 8, k * 8, 0);
 }
 
+// The same for values read once and too late to be kept in the caches
+// (non-temporal).
+constexpr int kAuxStream = 2;
+
+__device__ __forceinline__ double vec_load_stream(const VecBuf &b, int i, int k) {
+    const v2u v = __builtin_amdgcn_raw_buffer_load_b64(b.r, i * 8, k * 8, kAuxStream);
+    return __builtin_bit_cast(double, v);
+}
+
+__device__ __forceinline__ void vec_store_stream(const VecBuf &b, int i, int k, double x) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), b.r, i * 8, k * 8, kAuxStream);
+}
+
 // LDS writes of a wave become visible to the wave's other lanes (LDS
 // operations of one wave complete in order; this keeps the compiler to it).
 __device__ __forceinline__ void wave_lds_sync() {
@@ -277,9 +290,13 @@ WV_UNROLL
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int E>
+template <bool NEG, int E>
 __device__ __forceinline__ void twiddle1_mul(double (&x)[E], const double (&t)[E], const Fmod &f) {
     constexpr int G = kNttGroup;
+    if constexpr (NEG) {
+        mulmod_range<G, 0, E>(x, t, f);
+        return;
+    }
     double a[G - 1], b[G - 1];
     x[0] = f_reduce(x[0], f);   // its twiddle is 1
 WV_UNROLL
@@ -288,6 +305,35 @@ WV_UNROLL
 WV_UNROLL
     for (int k = 1; k < G; k++) x[k] = a[k - 1];
     mulmod_range<G, G, E>(x, t, f);
+}
+
+// NEG: transforms modulo X^L + 1, the cyclic ones of x[n] psi^n, psi of order 2 L.
+// n = tid + T e, so psi^n = psi^tid theta^e with theta = psi^T of order 2 E: with E = 16
+// theta is the 32nd root of kNttRt, and psi^tid goes into the twiddles of product
+// 1 (then not 1 for register 0 either).
+template <int E>
+__device__ __forceinline__ void theta_mul(double (&x)[E], const double *rt, const Fmod &f) {
+    static_assert(E == 16, "theta is the 32nd root");
+    double t[E];
+WV_UNROLL
+    for (int e = 0; e < E; e++) t[e] = rt[e];
+    double a[3], b[3];
+WV_UNROLL
+    for (int e = 1; e < 4; e++) a[e - 1] = x[e], b[e - 1] = t[e];
+    mulmod_step<3>(a, a, b, f);
+WV_UNROLL
+    for (int e = 1; e < 4; e++) x[e] = a[e - 1];
+    mulmod_range<4, 4, E>(x, t, f);
+}
+
+// product 1's twiddles modulo X^L + 1: both moduli's, forward then inverse, L each
+template <int LOGL>
+__device__ __forceinline__ void neg_twiddle1_load(double (&t)[NttShape<LOGL>::E], const double *tab, int at, int tid) {
+    using S = NttShape<LOGL>;
+    const VecBuf b = vec_buf(tab + (size_t)at * S::L, S::L);
+WV_UNROLL
+    for (int m = 0; m < S::E; m++) t[m] = vec_load(b, tid, m * S::T);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Those of the later products are short (1088 values at L = 2^14): both
@@ -365,16 +411,21 @@ struct NttStep {
     static constexpr int in_at(int e) { return K < S::P ? S::at(e * S::N(K < S::P ? K + 1 : K)) : e; }
 };
 
-template <int LOGL, int K>
+template <int LOGL, int K, bool NEG = false>
 __device__ __forceinline__ void ntt_fwd_from(double (&x)[NttShape<LOGL>::E], NttLds<LOGL> &lds, const VecBuf &tab, int q,
-                                             const double *rt, const Fmod &f, int tid) {
+                                             const double *rt, const Fmod &f, int tid, const double *neg = nullptr) {
     using S = NttShape<LOGL>;
     constexpr int E = S::E;
     if constexpr (K == 1) {
         double t[E];
-        twiddle1_load<LOGL>(t, tab, q * S::STRIDE, tid);
+        if constexpr (NEG) {
+            theta_mul(x, rt, f);
+            neg_twiddle1_load<LOGL>(t, neg, 2 * q, tid);
+        } else {
+            twiddle1_load<LOGL>(t, tab, q * S::STRIDE, tid);
+        }
         ntt_dif<E, E>(x, rt, f);
-        twiddle1_mul(x, t, f);
+        twiddle1_mul<NEG>(x, t, f);
     } else {
         ntt_dif<E, E>(x, rt, f);
         if constexpr (K <= S::NT) twiddle_mul(x, lds.tw + (S::table(K) - S::L) + tid % S::N(K), S::N(K), f);
@@ -404,13 +455,20 @@ __device__ __forceinline__ void ntt_forward(double (&x)[NttShape<LOGL>::E], NttL
     ntt_fwd_from<LOGL, 1>(x, lds, tab, q, kNttRt[2 * q], f, tid);
 }
 
+// The same modulo X^L + 1; neg: its tables of product 1 (neg_twiddle1_load).
+template <int LOGL>
+__device__ __forceinline__ void ntt_forward_neg(double (&x)[NttShape<LOGL>::E], NttLds<LOGL> &lds, const VecBuf &tab,
+                                                const double *neg, int q, const Fmod &f, int tid) {
+    ntt_fwd_from<LOGL, 1, true>(x, lds, tab, q, kNttRt[2 * q], f, tid, neg);
+}
+
 // base of the inverse's product 1 for twiddle1_load
 template <int LOGL>
 __device__ __forceinline__ int ntt_inverse_tw1(int q) {
     return q * NttShape<LOGL>::STRIDE + NttShape<LOGL>::DIR;
 }
 
-template <int LOGL, int K>
+template <int LOGL, int K, bool NEG = false>
 __device__ __forceinline__ void ntt_inv_from(double (&x)[NttShape<LOGL>::E], const double (&t1)[NttShape<LOGL>::E],
                                              NttLds<LOGL> &lds, const double *rt, const Fmod &f, int tid) {
     using S = NttShape<LOGL>;
@@ -426,24 +484,26 @@ WV_UNROLL
         else __syncthreads();
 WV_UNROLL
         for (int i = 0; i < E; i++) x[i] = o[X::out_at(i)];
-        if constexpr (K == 1) twiddle1_mul(x, t1, f);
+        if constexpr (K == 1) twiddle1_mul<NEG>(x, t1, f);
         else twiddle_mul(x, lds.tw + (S::DIR - S::L) + (S::table(K) - S::L) + tid % S::N(K), S::N(K), f);
         ntt_dit<E, E>(x, rt, f);
-        ntt_inv_from<LOGL, K - 1>(x, t1, lds, rt, f, tid);
+        if constexpr (K == 1 && NEG) theta_mul(x, rt, f);
+        ntt_inv_from<LOGL, K - 1, NEG>(x, t1, lds, rt, f, tid);
     }
 }
 
 // The inverse times L: transform layout in, x[e] = value tid + T e out
 // (unreduced, < 10.3 q for |x| < 0.7 q in).  Two workgroup barriers, the first
 // before LDS is written.
-template <int LOGL>
+// NEG: modulo X^L + 1, t1 from neg_twiddle1_load.
+template <int LOGL, bool NEG = false>
 __device__ __forceinline__ void ntt_inverse(double (&x)[NttShape<LOGL>::E], const double (&t1)[NttShape<LOGL>::E],
                                             NttLds<LOGL> &lds, int q, const Fmod &f, int tid) {
     using S = NttShape<LOGL>;
     const double *rt = kNttRt[2 * q + 1];
     if constexpr (S::R > 1) ntt_dit<S::R, S::E>(x, rt, f);
     else ntt_dit<S::E, S::E>(x, rt, f);
-    ntt_inv_from<LOGL, S::NT>(x, t1, lds, rt, f, tid);
+    ntt_inv_from<LOGL, S::NT, NEG>(x, t1, lds, rt, f, tid);
 }
 
 // A vector of length L, every load requested before the first is used.

@@ -863,7 +863,7 @@ int wv_destroy(wv_ctx *c) {
                       &c->irr_tasks, &c->irr_units, &c->irr_primes, &c->irr_roff, &c->irr_v, &c->irr_fix,
                       &c->irr_counts, &c->irr_pairs, &c->irr_b, &c->irr_e, &c->irr_dft,
                       &c->irr_root, &c->irr_seq, &c->irr_hat, &c->grid_tabs, &c->direct_terms, &c->direct_part,
-                      &c->direct_ticket};
+                      &c->direct_ticket, &c->ntt_split};
     for (DevBuf *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     grid_free(c->grid);

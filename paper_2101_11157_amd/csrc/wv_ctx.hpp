@@ -138,6 +138,7 @@ struct wv_ctx {
     wv::GridWork grid;                             // grid path's records and workspace
     wv::DevBuf grid_tabs;                          // runs of the compiled tables (grid path)
     wv::DevBuf ntt_tab[wv::kNttMaxLog + 1];       // twiddle tables per log2 length (grid path)
+    wv::DevBuf ntt_split;                         // powers of the root that splits a transform of twice the longest
     // congruence registry: the compiled tables (ids < WV_TABLE_COUNT), then
     // those defined at run time; device copy in tbl_* (TableStore)
     std::vector<wv::TableHead> t_head;

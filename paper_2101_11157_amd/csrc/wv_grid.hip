@@ -350,6 +350,22 @@ __device__ __forceinline__ uint64_t value_base(uint64_t item, uint64_t items_b, 
     return (item < items_b ? 4 * item : items_b + 3 * item) * W;
 }
 
+// The next of `total` items for this workgroup: those of its XCD (one eighth,
+// in order), then those the others have left; part counts the shares used up.
+__device__ __forceinline__ bool next_item(unsigned long long *counters, uint64_t total, uint32_t &part,
+                                          unsigned long long *ticket, uint64_t &item) {
+    while (part < 8) {
+        const uint32_t X = (blockIdx.x + part) & 7;
+        __syncthreads();   // LDS free
+        if (threadIdx.x == 0) *ticket = atomicAdd(&counters[X], 1ull);
+        __syncthreads();
+        item = total * X / 8 + readfirst_u64(*ticket);
+        if (item < total * (X + 1) / 8) return true;
+        part++;
+    }
+    return false;
+}
+
 // What bounds this kernel: issue of f64 operations (about 66 per element of a
 // transform, 0.58 of the issue slots at L = 2^14), then the vector loads of
 // node vectors, twiddles and values between them.  One transform at a time
@@ -369,18 +385,9 @@ __global__ void __launch_bounds__(NttShape<LOGL>::T, 4) k_grid_shift(ShiftArgs A
     const int tid = threadIdx.x;
     const uint64_t total = A.off[A.nruns], items_b = A.off[A.nruns_b];
     const VecBuf tab = vec_buf(A.tab, 2 * S::STRIDE);
-    // the items of this workgroup's XCD, then those the others have left
     uint32_t part = 0;
-    while (part < 8) {
-        const uint32_t X = (blockIdx.x + part) & 7;
-        __syncthreads();   // LDS free
-        if (tid == 0) ticket = atomicAdd(&A.counters[X], 1ull);
-        __syncthreads();
-        const uint64_t item = total * X / 8 + readfirst_u64(ticket);
-        if (item >= total * (X + 1) / 8) {
-            part++;
-            continue;
-        }
+    uint64_t item;
+    while (next_item(A.counters, total, part, &ticket, item)) {
         const uint32_t slot = __builtin_amdgcn_readfirstlane(find_seg(A.off, A.nruns, item));
         const uint32_t prime = __builtin_amdgcn_readfirstlane(A.runs[slot].prime);
         const int np = slot < A.nruns_b ? 4 : 3;
@@ -415,6 +422,134 @@ WV_UNROLL
 WV_UNROLL
                     for (int e = 0; e < E / 2; e++)
                         vec_store(out, tid, o + e * T, ntt_crt(r[e], x[E / 2 + e], kNttQ1Inv, q1p, f, fp));
+                }
+            }
+        }
+    }
+}
+
+// Convolutions of length 2 N, N = 2^kNttMaxLog, modulo X^2N - 1 = (X^N - 1)
+// (X^N + 1): of the halves' sum and difference, by transforms of N.  Of c's
+// halves, c[N + n] = (c+[n] - c-[n]) / 2.
+constexpr int kSplitN = 1 << kNttMaxLog;
+
+// u_i / 2 N of one value vector, as k_grid_fwd: out[(((prime 4 + j) 2 + q) 2 + sub)
+// N + ...], a workgroup each.
+__global__ void __launch_bounds__(NttShape<kNttMaxLog>::T, 4) k_grid_fwd_split(
+    const PrimeRec *__restrict__ pr, const double *__restrict__ node, const double *__restrict__ fact,
+    const double *__restrict__ tab, const double *__restrict__ neg, double *__restrict__ out) {
+    using S = NttShape<kNttMaxLog>;
+    constexpr int E = S::E, T = S::T, N = S::L;
+    __shared__ NttLds<kNttMaxLog> lds;
+    const int tid = threadIdx.x;
+    const uint32_t i = blockIdx.x >> 4, j = (blockIdx.x >> 2) & 3, q = (blockIdx.x >> 1) & 1, sub = blockIdx.x & 1;
+    const Fmod fp = fmod_of(pr[i].p);
+    const Fmod f = ntt_mod(q);
+    const VecBuf tb = vec_buf(tab, 2 * S::STRIDE);
+    const VecBuf v = vec_buf(node + ((size_t)i * 4 + j) * N, N);
+    const VecBuf iF = vec_buf(fact + (size_t)i * 2 * N + N, N);   // K + 1 = N
+    double x[E];
+WV_UNROLL
+    for (int e = 0; e < E; e++) {
+        const double u = f_mulmod(f_mulmod(vec_load(v, tid, T * e), vec_load(iF, tid, T * e), fp),
+                                  vec_load(iF, T - 1 - tid, N - T - T * e), fp);
+        x[e] = (tid & 1) ? u : -u;
+    }
+    ntt_lds_tables<kNttMaxLog>(lds, tb, (int)q, tid);
+    if (sub) ntt_forward_neg<kNttMaxLog>(x, lds, tb, neg, (int)q, f, tid);
+    else ntt_forward<kNttMaxLog>(x, lds, tb, (int)q, f, tid);
+    const double li = -(f.p - 1.0) / (double)(2 * N);   // 1 / 2 N mod q
+    const VecBuf o = vec_buf(out + (size_t)blockIdx.x * N, N);
+WV_UNROLL
+    for (int m = 0; m < E; m++) vec_store(o, tid, m * T, f_mulmod(x[m], li, f));
+}
+
+// k_grid_shift for W = N block starts: 2 N terms of the kernel, two transforms
+// of N each way per modulus and vector, so twice the work of a shift of N / 2
+// block starts for four times its terms.  Bound by its memory traffic, which no
+// longer stays in the L2s: of each vector and modulus 2 N values of the node
+// vectors, and N of c+, which wait in the workgroup's share of half (np N
+// values) for c-: 3.5 TB/s past the L2s, 0.44 of the f64 issue slots.  Shifts of 310
+// primes near 1e11: 16.5 ms, by whole transforms 17.4.  (With c+ in registers, the
+// kernel's transforms and the twiddles read again for every vector, 18.4; with
+// the weights psi^n of X^N + 1 from memory instead of in the twiddles, 21.0.)
+__global__ void __launch_bounds__(NttShape<kNttMaxLog>::T, 4) k_grid_shift_split(ShiftArgs A,
+                                                                                 const double *__restrict__ neg,
+                                                                                 double *__restrict__ half) {
+    using S = NttShape<kNttMaxLog>;
+    constexpr int E = S::E, T = S::T, N = S::L, LG = kNttMaxLog, G = 8;
+    __shared__ NttLds<LG> lds;
+    __shared__ unsigned long long ticket;
+    const int tid = threadIdx.x;
+    const uint64_t total = A.off[A.nruns], items_b = A.off[A.nruns_b];
+    const VecBuf tab = vec_buf(A.tab, 2 * S::STRIDE);
+    const VecBuf hb = vec_buf(half + (size_t)blockIdx.x * 4 * N, 4 * N);
+    uint32_t part = 0;
+    uint64_t item;
+    while (next_item(A.counters, total, part, &ticket, item)) {
+        const uint32_t slot = __builtin_amdgcn_readfirstlane(find_seg(A.off, A.nruns, item));
+        const uint32_t prime = __builtin_amdgcn_readfirstlane(A.runs[slot].prime);
+        const int np = slot < A.nruns_b ? 4 : 3;
+        const Fmod fp = fmod_of(readfirst_u64(A.pr[prime].p));
+        const double q1p = f_reduce((double)kNttQ[0], fp);
+        const double *beta = A.beta + (slot + item) * N;      // 2 N entries
+        const double *uh = A.uhat + (size_t)prime * 16 * N;   // vector j modulo q, part sub at ((2 j + q) 2 + sub) N
+        const VecBuf out = vec_buf(A.out + value_base(item, items_b, N), np * N);
+        double w[E], x[E], t1[E];
+WV_NO_UNROLL
+        for (int q = 0; q < 2; q++) {
+            const Fmod f = ntt_mod(q);
+            load_vec<LG>(w, beta, tid);
+            load_vec<LG>(x, beta + N, tid);
+WV_UNROLL
+            for (int e = 0; e < E; e++) w[e] += x[e];
+            ntt_lds_tables<LG>(lds, tab, q, tid);
+            ntt_forward<LG>(w, lds, tab, q, f, tid);
+            twiddle1_load<LG>(t1, tab, ntt_inverse_tw1<LG>(q), tid);
+WV_NO_UNROLL
+            for (int j = 0; j < np; j++) {
+                load_vec<LG>(x, uh + (size_t)(2 * j + q) * 2 * N, tid);
+                mulmod_range<kNttGroup, 0, E>(x, w, f);
+                ntt_inverse<LG>(x, t1, lds, q, f, tid);
+WV_UNROLL
+                for (int e = 0; e < E; e++) vec_store(hb, tid, j * N + e * T, x[e]);
+            }
+            load_vec<LG>(w, beta, tid);
+            load_vec<LG>(x, beta + N, tid);
+WV_UNROLL
+            for (int e = 0; e < E; e++) w[e] -= x[e];
+            ntt_forward_neg<LG>(w, lds, tab, neg, q, f, tid);
+            neg_twiddle1_load<LG>(t1, neg, 2 * q + 1, tid);
+WV_NO_UNROLL
+            for (int j = 0; j < np; j++) {
+                load_vec<LG>(x, uh + ((size_t)(2 * j + q) * 2 + 1) * N, tid);
+                mulmod_range<kNttGroup, 0, E>(x, w, f);
+                ntt_inverse<LG, true>(x, t1, lds, q, f, tid);
+                const int o = j * N;
+WV_UNROLL
+                for (int e0 = 0; e0 < E; e0 += G) {
+                    double h[G];
+WV_UNROLL
+                    for (int e = 0; e < G; e++) h[e] = vec_load(hb, tid, o + (e0 + e) * T);
+                    __builtin_amdgcn_sched_barrier(0);
+WV_UNROLL
+                    for (int e = 0; e < G; e++) x[e0 + e] = f_reduce(h[e] - x[e0 + e], f);   // < 20.6 q before
+                }
+                // the residues mod q1 wait where the values go
+                if (q == 0) {
+WV_UNROLL
+                    for (int e = 0; e < E; e++) vec_store_stream(out, tid, o + e * T, x[e]);
+                } else {
+WV_UNROLL
+                    for (int e0 = 0; e0 < E; e0 += G) {
+                        double r[G];
+WV_UNROLL
+                        for (int e = 0; e < G; e++) r[e] = vec_load_stream(out, tid, o + (e0 + e) * T);
+                        __builtin_amdgcn_sched_barrier(0);
+WV_UNROLL
+                        for (int e = 0; e < G; e++)
+                            vec_store_stream(out, tid, o + (e0 + e) * T, ntt_crt(r[e], x[e0 + e], kNttQ1Inv, q1p, f, fp));
+                    }
                 }
             }
         }
@@ -574,6 +709,7 @@ int with_chunks(int c, F &&fn) {
     case 8: return fn(std::integral_constant<int, 8>{});
     case 16: return fn(std::integral_constant<int, 16>{});
     case 32: return fn(std::integral_constant<int, 32>{});
+    case 64: return fn(std::integral_constant<int, 64>{});
     default: return WV_EINVAL;
     }
 }
@@ -626,6 +762,28 @@ int ntt_tables(wv_ctx *c, int logl) {
 
 namespace {
 
+// Product 1's twiddles modulo X^N + 1 of both moduli: those of ntt_tables times
+// psi^t (forward) and psi^-t (inverse), psi of order 2 N, for thread t.
+int split_table(wv_ctx *c) {
+    if (c->ntt_split.ptr) return WV_OK;
+    using S = NttShape<kNttMaxLog>;
+    constexpr uint64_t N = S::L, T = S::T, M = 2 * N;
+    std::vector<double> h(4 * N);
+    std::vector<uint64_t> pw(M);
+    for (int q = 0; q < 2; q++) {
+        const uint64_t Q = kNttQ[q], w = powmod_q(kNttRoot[q], (1ull << 17) / M, Q);
+        pw[0] = 1;
+        for (uint64_t i = 1; i < M; i++) pw[i] = mulmod_q(pw[i - 1], w, Q);
+        for (uint64_t m = 0; m < (uint64_t)S::E; m++)
+            for (uint64_t t = 0; t < T; t++) {
+                const uint64_t e = (2 * bitrev((uint32_t)m, S::LE) + 1) * t % M;
+                h[(2 * q) * N + m * T + t] = balanced(pw[e], Q);
+                h[(2 * q + 1) * N + m * T + t] = balanced(pw[(M - e) % M], Q);
+            }
+    }
+    return upload_once(c, c->ntt_split, h.data(), h.size() * sizeof(double));
+}
+
 // The runs of the compiled tables, uploaded once per context.
 int runs_table(wv_ctx *c) {
     if (c->grid_tabs.ptr) return WV_OK;
@@ -636,12 +794,12 @@ int runs_table(wv_ctx *c) {
 
 // Bytes of device memory a batch of n primes needs besides the plan's records.
 struct GridLayout {
-    size_t node0, node1, fact, beta, pi, cst, uhat, res, inv, vals, counters, total;
+    size_t node0, node1, fact, beta, pi, cst, uhat, res, inv, vals, counters, half, total;
 };
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-GridLayout grid_layout(const GridClass &g, uint64_t n, uint64_t pmax) {
+GridLayout grid_layout(const GridClass &g, uint64_t n, uint64_t pmax, unsigned blocks) {
     const uint64_t L = 1ull << g.logl, W = L / 2;
     const uint64_t nruns = n * (grid_runs(g.tb).n + grid_runs(g.te).n);
     const uint64_t items_b = n * grid_shifts(g.tb, (double)pmax, g.logl);
@@ -663,6 +821,7 @@ GridLayout grid_layout(const GridClass &g, uint64_t n, uint64_t pmax) {
     take(y.inv, (items_b + items_e + nruns) * W);
     take(y.vals, (4 * items_b + 3 * items_e) * W);
     take(y.counters, 8);
+    take(y.half, g.logl > kNttMaxLog ? (size_t)blocks * 4 * W : 0);   // a share per workgroup of the shifts
     y.total = at;
     return y;
 }
@@ -671,7 +830,7 @@ constexpr size_t kGridBytes = (size_t)8 << 30;   // workspace of one sub-batch, 
 
 // Workgroups of the persistent kernel: four waves per SIMD of 128 registers.
 unsigned grid_blocks(const wv_ctx *c, int logl) {
-    const int T = (1 << logl) / (logl >= 10 ? 16 : 8);
+    const int T = (1 << std::min(logl, kNttMaxLog)) / (logl >= 10 ? 16 : 8);
     return (unsigned)std::max(8, c->num_cus * (1024 / T) / 8 * 8);
 }
 
@@ -747,21 +906,29 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
                            at(y.res), at(y.pi), at(y.cst), next);
         std::swap(node, next);
     }
-    WV_TRY(fwd(g.logl));
+    const bool split = g.logl > kNttMaxLog;
+    if (split)
+        hipLaunchKernelGGL(k_grid_fwd_split, dim3(n * 16), dim3(NttShape<kNttMaxLog>::T), 0, st, pr, node, at(y.fact),
+                           as<double>(c->ntt_tab[kNttMaxLog]), as<double>(c->ntt_split), at(y.uhat));
+    else
+        WV_TRY(fwd(g.logl));
     WV_HIP(launch_set_u64(st, reinterpret_cast<uint64_t *>(at(y.counters)), 8, 0));
-    WV_TRY(with_shape(g.logl, [&](auto s) -> int {
+    ShiftArgs a{};
+    a.pr = pr;
+    a.beta = inv;
+    a.uhat = at(y.uhat);
+    a.tab = as<double>(c->ntt_tab[std::min(g.logl, kNttMaxLog)]);
+    a.out = at(y.vals);
+    a.runs = runs;
+    a.off = off;
+    a.counters = reinterpret_cast<unsigned long long *>(at(y.counters));
+    a.nruns = nruns;
+    a.nruns_b = nruns_b;
+    if (split)
+        hipLaunchKernelGGL(k_grid_shift_split, dim3(grid_blocks(c, g.logl)), dim3(NttShape<kNttMaxLog>::T), 0, st, a,
+                           as<double>(c->ntt_split), at(y.half));
+    else WV_TRY(with_shape(g.logl, [&](auto s) -> int {
         constexpr int LG = decltype(s)::value;
-        ShiftArgs a{};
-        a.pr = pr;
-        a.beta = inv;
-        a.uhat = at(y.uhat);
-        a.tab = as<double>(c->ntt_tab[LG]);
-        a.out = at(y.vals);
-        a.runs = runs;
-        a.off = off;
-        a.counters = reinterpret_cast<unsigned long long *>(at(y.counters));
-        a.nruns = nruns;
-        a.nruns_b = nruns_b;
         hipLaunchKernelGGL(k_grid_shift<LG>, dim3(grid_blocks(c, LG)), dim3(NttShape<LG>::T), 0, st, a);
         return WV_OK;
     }));
@@ -800,18 +967,21 @@ bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g) {
     return true;
 }
 
-int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const uint64_t *d_primes, uint32_t n,
+int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &own, const uint64_t *d_primes, uint32_t n,
                  uint64_t pmax, unsigned long long *terms, wv_result *d_out) {
     if (n == 0) return WV_OK;
-    for (int l = kNttMinLog; l <= g.logl; l++) WV_TRY(ntt_tables(c, l));
+    const GridClass &g = grid_batch_class(own, n, pmax);
+    for (int l = kNttMinLog; l <= std::min(g.logl, kNttMaxLog); l++) WV_TRY(ntt_tables(c, l));
+    if (g.logl > kNttMaxLog) WV_TRY(split_table(c));
     WV_TRY(runs_table(c));
     // sub-batches within the workspace bound
-    const size_t one = grid_layout(g, 64, pmax).total / 64 + 1;
+    const unsigned blocks = grid_blocks(c, g.logl);
+    const size_t one = grid_layout(g, 64, pmax, 0).total / 64 + 1;
     uint32_t step = (uint32_t)std::min<uint64_t>(n, std::max<uint64_t>(1, kGridBytes / one));
     step = std::min<uint32_t>(step, 1u << 16);
     const uint32_t parts = (n + step - 1) / step;
     step = (n + parts - 1) / parts;
-    const GridLayout y = grid_layout(g, step, pmax);
+    const GridLayout y = grid_layout(g, step, pmax, blocks);
     const uint64_t nseg = (uint64_t)step * (kTables[g.tb].n + kTables[g.te].n);
     WV_TRY(ensure(c, b.pr, step * sizeof(PrimeRec)));
     WV_TRY(ensure(c, b.segs, nseg * sizeof(SegRec)));
@@ -835,14 +1005,15 @@ void grid_free(GridWork &b) {
         if (x->ptr) (void)hipFree(x->ptr);
 }
 
-int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
+int grid_batch_sync(wv_ctx *c, const GridClass &own, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
                     wv_result *d_out) {
     if (n == 0) return WV_OK;
+    const GridClass &g = grid_batch_class(own, n, pmax);   // as grid_enqueue takes it
     hipStream_t st = c->stream;
     auto *terms = as<unsigned long long>(c->scal);
     WV_HIP(hipEventRecord(c->ev[EV_PLAN0], st));
     WV_HIP(launch_set_u64(st, as<uint64_t>(c->scal), 8, 0));
-    WV_TRY(grid_enqueue(c, c->grid, st, g, d_primes, n, pmax, terms, d_out));
+    WV_TRY(grid_enqueue(c, c->grid, st, own, d_primes, n, pmax, terms, d_out));
     WV_HIP(hipEventRecord(c->ev[EV_FINAL], st));
     uint64_t host[2];
     WV_HIP(hipMemcpyAsync(host, terms, sizeof(host), hipMemcpyDeviceToHost, st));

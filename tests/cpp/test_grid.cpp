@@ -100,7 +100,7 @@ static void classes() {
             CHECK(p < (4ull << (2 * kNttMinLog)));
             continue;
         }
-        CHECK(c.logl >= kNttMinLog && c.logl <= kNttMaxLog && p >= (4ull << (2 * c.logl)));
+        CHECK(c.logl >= kNttMinLog && c.logl <= kGridMaxLog && p >= (4ull << (2 * c.logl)));
         CHECK(c.tb >= WV_TABLE_BB1 && c.tb <= WV_TABLE_BB30 && c.te >= WV_TABLE_EE3 && c.te <= WV_TABLE_EE33);
         const uint64_t K = grid_k(c.logl), W = grid_w(c.logl);
         CHECK(W == K + 1);
