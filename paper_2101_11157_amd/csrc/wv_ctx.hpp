@@ -223,6 +223,8 @@ void pick_tuned(wv_ctx *c, uint64_t pmax);
 // stream
 int results_to_host(wv_ctx *c, const wv_result *d, size_t n, wv_result *out);
 int pin_res_reserve(wv_ctx *c, size_t n);
+// two arrays of n words, the same way
+int words_to_host(wv_ctx *c, const uint64_t *d0, uint64_t *out0, const uint64_t *d1, uint64_t *out1, size_t n);
 // an upper bound on the primes in [lo, hi) (lo >= 5)
 uint64_t prime_count_bound(uint64_t lo, uint64_t hi);
 // Work (terms, estimated from the prime-count bound) below which a

@@ -1125,9 +1125,7 @@ int wv_bernoulli_euler_all(wv_ctx *c, uint64_t p, uint64_t *b, uint64_t *e) {
     double work = 0.0;
     WV_TRY(irr_batch(c, std::vector<uint64_t>{p}, as<uint64_t>(c->irr_b), as<uint64_t>(c->irr_e), 0, counts, &ms,
                      &work));
-    WV_HIP(hipMemcpyAsync(b, c->irr_b.ptr, nt * sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream));
-    WV_HIP(hipMemcpyAsync(e, c->irr_e.ptr, nt * sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream));
-    WV_HIP(hipStreamSynchronize(c->stream));
+    WV_TRY(words_to_host(c, as<uint64_t>(c->irr_b), b, as<uint64_t>(c->irr_e), e, nt));
     c->stats.n_primes = 1;
     c->stats.n_terms = (uint64_t)work;
     c->stats.ms_sum = ms;

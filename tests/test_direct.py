@@ -60,3 +60,18 @@ def test_windows_equal_the_term_sums(ctxs, lo, hi):
         ctxs[0].count_primes(5, 2000)
     both = ctxs[0].search_windows([lo, 5], [hi, 300])
     assert np.array_equal(both[0], want) and [int(p) for p in both[1]["p"]] == oracle.primes(5, 300)
+
+
+@pytest.mark.gpu
+def test_lists_hold_primes_only(ctxs):
+    """Strong pseudoprimes to the first bases, squares and products of the
+    smallest primes a trial division does not catch are refused; the bases of the
+    test themselves are primes."""
+    print("case: primality of list entries", flush=True)
+    for n in (41 * 41, 41 * 43, 1373653, 25326001, 161304001, 960946321, 1157839381, 3215031751,
+              118670087467, 307768373641, 546348519181):
+        with pytest.raises(wv.WvError) as e:
+            ctxs[0].eval_primes([n])
+        assert e.value.status == wv.WV_ENOTPRIME, n
+    got = ctxs[0].eval_primes([13, 23, 41, 43, 1662803, 1093, 3511])
+    assert [int(p) for p in got["p"]] == [13, 23, 41, 43, 1662803, 1093, 3511]
