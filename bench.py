@@ -6,11 +6,19 @@ below 2^37, each tested for both residues B_{p-3} mod p and E_{p-3} mod p with
 the congruences eqnBB30 (Section 3) and eqnEE33 (Section 5).  A step is one
 pass of the whole path over the next sub-window of `--window` consecutive
 integers of that range (about window / 25.3 primes): segmented sieve, plan,
-term sums, reductions, finalize, results copied to the host.  Warm-up steps
-take the sub-windows before the timed ones, so no step repeats work.
+sums, finalize, results copied to the host.  Warm-up steps take the sub-windows
+before the timed ones, so no step repeats work.
 
-Prints one JSON line.  `roofline` describes the term-sum kernel (the dominant
-kernel), which is bound by vector-ALU issue: the full-rate VALU operations its
+The default context evaluates its congruences' sums along arithmetic
+progressions by exact number-theoretic transforms; with `--tables derived` (the
+shipped ladders of derived congruences), a block shape or a chunk size the sums
+are taken term by term.
+
+Prints one JSON line.  With transforms `roofline` counts the double-precision
+operations of the shifts' transforms (GRID_OPS per value and transform; node
+values, inverses and the folding of the blocks are left out) over the device
+time of the batches, against the vector ALU's issue rate.  With term sums it
+describes the term-sum kernel, which is bound by vector-ALU issue too: the full-rate VALU operations its
 algorithm needs (ops_per_term below: double-precision modular products,
 difference-table additions and the periodic table reductions of the blocked
 Taylor-coefficient loop, times the terms it summed; plus setup_ops_per_chunk
@@ -274,6 +282,56 @@ def bench_peak(args):
                       "published_f64_matrix_flops": PEAK_MFMA_F64, "valu": valu, "mfma_f64": mfma}), flush=True)
 
 
+# operations per value of one transform of the shifts, the products in the
+# transform domain and the remainder theorem's share included (counted by the
+# device: SQ_INSTS_VALU of the shift kernel x 64 over its values)
+GRID_OPS = 66
+
+
+def grid_shift_ops(primes, st):
+    """The operations of the shifts' transforms for `primes`, all in one class
+    (st: the statistics of their batch), or None where the sums were not
+    evaluated along progressions."""
+    import ctypes
+    import math
+    import paper_2101_11157_amd as wv
+    K = st["chunk_terms"]
+    n = len(primes)
+    if n == 0 or K < 255 or (K + 1) & K or st["n_sums"] % n:
+        return None
+    L = wv.lib()
+    tables = {}
+    for tid in range(13):
+        ns = ctypes.c_int()
+        L.wv_table_info(tid, ctypes.byref(ns), None, None, None)
+        tables[(tid <= 6, ns.value)] = tid
+    per = 0.0
+    sums_e = 33
+    if (True, st["n_sums"] // n - sums_e) not in tables:
+        return None
+    p = float(sum(primes)) / n
+    for tid, polys in ((tables[(True, st["n_sums"] // n - sums_e)], 4), (tables[(False, sums_e)], 3)):
+        ends = []
+        j = 0
+        while True:
+            v = [ctypes.c_uint32() for _ in range(4)]
+            if L.wv_table_term(tid, j, None, *[ctypes.byref(x) for x in v]):
+                break
+            ends.append((v[0].value / v[1].value, v[2].value / v[3].value))
+            j += 1
+        ends.sort()
+        runs = [list(ends[0])]
+        for a, b in ends[1:]:
+            if abs(a - runs[-1][1]) < 1e-12:
+                runs[-1][1] = b
+            else:
+                runs.append([a, b])
+        W = K + 1
+        shifts = sum(math.ceil(math.floor((b - a) * p / K) / W) for a, b in runs)
+        per += shifts * 2 * (1 + polys) * 2.0 * W * GRID_OPS   # both moduli; 2 W values, split or not
+    return per * n
+
+
 def use_tables(ctx, which, p=10 ** 11 - 1):
     """Select the congruences; returns their description (at prime size p)."""
     if which == "derived":
@@ -333,6 +391,11 @@ def table_cost(tables, p=10 ** 11 - 1):
     return 227 / 6480, 27 / 512
 
 
+def takes_term_sums(args):
+    """Whether the context of these arguments sums term by term throughout."""
+    return args.tables == "derived" or bool(args.chunk) or bool(args.block)
+
+
 def measure_plain(args, wv, wins, lo0, hi0, W):
     """The headline: consecutive sub-windows through wv_search_range."""
     ctx = wv.Context(0)
@@ -363,20 +426,24 @@ def measure_plain(args, wv, wins, lo0, hi0, W):
         ms_sum += st["ms_sum"]
         ms_dev += st["ms_total"]
         timed.append(res)
-        steps_st.append((st["n_terms_b"], st["n_terms"], st["chunk_terms"]))
+        steps_st.append(st)
         print(f"step {k - args.warmup}: {len(res)} primes, {st['n_terms']:.3e} terms, "
-              f"sum kernel {st['ms_sum']:.1f} ms, device {st['ms_total']:.1f} ms", file=sys.stderr, flush=True)
+              f"sums {st['ms_sum']:.1f} ms, device {st['ms_total']:.1f} ms", file=sys.stderr, flush=True)
     wall = time.perf_counter() - t0
     ctx.close()
     # bookkeeping outside the timed region: the modelled operations of each
     # step's launch, with and without the chunks' set-up
     ops = ops_terms = 0.0
+    by_terms = takes_term_sums(args)
     if block:
         om = OpsModel(args.tables, block[0], block[1])
-        for res, (nb, nt, C) in zip(timed, steps_st):
+        for res, st in zip(timed, steps_st):
             plist = [int(p) for p in res["p"]]
-            ops += om.ops(plist, nb, nt, chunk=C)
-            ops_terms += om.ops(plist, nb, nt)
+            if by_terms:
+                ops += om.ops(plist, st["n_terms_b"], st["n_terms"], chunk=st["chunk_terms"])
+                ops_terms += om.ops(plist, st["n_terms_b"], st["n_terms"])
+            else:
+                ops += grid_shift_ops(plist, st) or 0.0
     return dict(tables=tables, primes=primes, terms=terms, terms_b=terms_b, ops=ops, ops_terms=ops_terms, muls=muls,
                 block=block, ms_sum=ms_sum, ms_dev=ms_dev, wall=wall, results=timed)
 
@@ -400,15 +467,17 @@ def measure_batch(args, wv, nwin):
             last[0] = t
             print(f"batch progress {done}/{total} chunks at {t - t_start:.1f} s", file=sys.stderr, flush=True)
 
-    ctx.set_progress(progress)
+    if takes_term_sums(args):   # a progress callback splits the term sums (and asks for them)
+        ctx.set_progress(progress)
     t0 = time.perf_counter()
     res = ctx.search_windows([a for a, _ in wins], [b for _, b in wins])
     wall = time.perf_counter() - t0
     st = ctx.stats()
     primes = sum(len(r) for r in res)
     plist = [int(p) for r in res for p in r["p"]]
-    ops = OpsModel(args.tables, st["block_k_b"], st["block_k_e"]).ops(plist, st["n_terms_b"], st["n_terms"],
-                                                                       chunk=st["chunk_terms"])
+    # (windows of many sizes take many classes: no operation count for transforms)
+    ops = OpsModel(args.tables, st["block_k_b"], st["block_k_e"]).ops(
+        plist, st["n_terms_b"], st["n_terms"], chunk=st["chunk_terms"]) if takes_term_sums(args) else None
     ok = None
     if args.verify:
         ctx.set_progress(None)
@@ -500,6 +569,9 @@ def requests_alone(args, wv, trace, served):
 def rate_summary(primes, terms, ops, wall, ms_sum):
     """primes/s and terms/s over the wall clock, and the term-sum kernel's
     modelled VALU rate over its own time (frac of the issue peak)."""
+    if ops is None:
+        return {"primes_per_s": primes / wall, "terms_per_s": terms / wall, "primes": primes, "terms": terms,
+                "wall_s": wall, "sum_kernel_ms": ms_sum}
     achieved = ops / (ms_sum * 1e-3) / 1e12 if ms_sum > 0 else 0.0
     return {"primes_per_s": primes / wall, "terms_per_s": terms / wall, "primes": primes, "terms": terms,
             "wall_s": wall, "sum_kernel_ms": ms_sum, "valu_tops": achieved, "frac": achieved / (PEAK_VALU / 1e12)}
@@ -523,11 +595,12 @@ def main():
     ap.add_argument("--window", type=int, default=0, help="integers per step (0: config default)")
     ap.add_argument("--chunk", type=int, default=0, help="terms per lane chunk (0: automatic)")
     ap.add_argument("--block", default="", help="term-sum block shape KB,KE (default: the library's)")
-    ap.add_argument("--tables", default="derived", choices=["derived", "printed"],
-                    help="derived: the package's ladders of greedy-derived congruences (Section 2.2), "
-                         "printed: eqnBB30 + eqnEE33")
+    ap.add_argument("--tables", default="printed", choices=["derived", "printed"],
+                    help="printed: the default context, the paper's congruences evaluated along progressions; "
+                         "derived: the package's ladders of greedy-derived congruences (Section 2.2), term by term")
     ap.add_argument("--irr-path", default="auto", choices=["auto", "valu", "mfma"],
-                    help="irregular: power-sum kernel (auto: matrix cores below 2^24)")
+                    help="irregular: transforms (auto) or the power sums one by one on the vector ALU or the "
+                         "matrix cores")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-batch", action="store_true", help="1e11: leave the batched workload out of the line")
     ap.add_argument("--no-serve", action="store_true", help="1e11: leave the served trace out of the line")
@@ -620,9 +693,15 @@ def main():
                                else "not measured for this kernel source / configuration"),
         },
     }
+    if not takes_term_sums(args):
+        for k in ("achieved_terms_only", "frac_terms_only"):
+            del line["roofline"][k]
+        if not m["ops"]:   # primes too small for transforms
+            line["roofline"]["achieved"] = line["roofline"]["frac"] = None
     # the multiply view: the blocked loop needs few multiplies per term, so
     # this fraction is low although the kernel is bound by VALU issue
-    line["multiply_ops"] = {"achieved": mul_rate, "peak": peak, "unit": "Tops/s", "frac": mul_rate / peak}
+    else:
+        line["multiply_ops"] = {"achieved": mul_rate, "peak": peak, "unit": "Tops/s", "frac": mul_rate / peak}
 
     if args.config == "1e11" and not args.no_batch and not args.no_same_work:
         line["batched_1e11"] = same_windows_batched(args, wv, wins_extra)
@@ -665,8 +744,9 @@ def main():
         # derived ladder trades terms for sums, so terms/s depends on the mix);
         # the same work through the plain path is in per_window_plain /
         # alone_plain above
-        line["vs_plain"] = {k: {"frac_ratio": line[k]["frac"] / line["roofline"]["frac"],
-                                "terms_per_s_ratio": line[k]["terms_per_s"] / line["config"]["terms_per_s"]}
+        line["vs_plain"] = {k: dict({"terms_per_s_ratio": line[k]["terms_per_s"] / line["config"]["terms_per_s"]},
+                                    **({"frac_ratio": line[k]["frac"] / line["roofline"]["frac"]}
+                                       if takes_term_sums(args) else {}))
                             for k in ("batched", "served") if k in line}
 
     if not args.no_cpu_baseline and m["results"]:
@@ -715,12 +795,29 @@ OPS_IRR_PAIR_VALU = 7
 PEAK_MFMA_F64 = 78.6e12                  # dense f64 matrix peak of MI355X
 
 
+def prime_list(lo, hi):
+    import oracle
+    return oracle.primes(lo, hi)
+
+
+def dft_ops(h):
+    """Operations of one prime's transforms of h values, one modulus."""
+    best = None
+    for logl in range(9, 15):
+        a, length = -(-h // (1 << (logl - 1))), 1 << logl
+        w = length * ((6 * a - 1) * (14 + 2.6 * logl) + 2 * a * a * 16)
+        if best is None or w < best[0]:
+            best = (w, length * ((6 * a - 1) * 50.0 + 2 * a * a * 8))
+    return best[1]
+
+
 def bench_irregular(args, wv):
     """Irregular-pair census: every B_{2k} and E_{2k} mod p (2k <= p - 3) of the
     primes in [2^15, 2^16), a step being the next window of `--window` (default
     4096) integers; the pairs found are compared with the oracle on the first
-    timed window's smallest primes.  `roofline` describes the power-sum kernel
-    on the matrix cores (one f64 multiply-add per (s, t) pair)."""
+    timed window's smallest primes.  `roofline` describes the transforms, or
+    with --irr-path mfma or valu the power-sum kernel (one f64 multiply-add or
+    one modular multiply-add per (s, t) pair)."""
     import numpy as np
     lo0, hi0 = 1 << 15, 1 << 16
     W = args.window or 4096
@@ -731,7 +828,7 @@ def bench_irregular(args, wv):
     wins = [(lo0 + k * W, lo0 + (k + 1) * W) for k in range(nwin)]
     ctx = wv.Context(0)
     ctx.set_irregular_path({"auto": 0, "valu": 1, "mfma": 2}[args.irr_path])
-    attained = mfma_f64_attained() if args.irr_path != "valu" else None
+    attained = mfma_f64_attained() if args.irr_path == "mfma" else None
     for k in range(args.warmup):
         ctx.irregular_pairs(*wins[k])
         print(f"warmup {k}: window {wins[k]}", file=sys.stderr, flush=True)
@@ -784,6 +881,20 @@ def bench_irregular(args, wv):
             "traffic": None,
         },
     }
+    if args.irr_path == "auto":
+        # transforms: about 50 operations per value, modulus and transform and 8 per
+        # product of blocks (k_irr_fwd, k_irr_out, k_irr_mul), as the library models
+        # its block lengths, over the whole batch's time
+        ops = 0.0
+        for w in wins[args.warmup:]:
+            for p in prime_list(*w):
+                ops += dft_ops((p - 1) // 2) * (1 if p < 1 << 16 else 2)
+        rate = ops / (ms_sum * 1e-3) / 1e12
+        line["roofline"] = {"bound": "alu", "achieved": rate, "peak": PEAK_VALU / 1e12,
+                            "unit": "Tops/s (full-rate VALU lane ops)", "frac": rate / (PEAK_VALU / 1e12),
+                            "traffic": None}
+        line["config"]["kernel"] = "transforms"
+        attained = None
     if attained:
         # context for the published peak: what back-to-back independent f64
         # matrix operations attain on this device
@@ -873,6 +984,8 @@ def run_trace(wv, ctx, trace, step_terms, tables="derived"):
     ops = OpsModel(tables, st["block_k_b"], st["block_k_e"]).ops(served, st["terms_done_b"], st["terms_done"],
                                                                  chunk=1 << 18)
     valu = ops / st["sum_s"] / 1e12 if st["sum_s"] > 0 else 0.0
+    if tables != "derived":   # mostly transforms: no operation count
+        valu = None
     v = sorted(lat.values())
     pct = lambda q: v[min(len(v) - 1, int(round(q * (len(v) - 1))))]
     span = trace[-1][0] if trace else 0.0
@@ -882,7 +995,7 @@ def run_trace(wv, ctx, trace, step_terms, tables="derived"):
                "max_ms": v[-1], "requests": len(trace), "primes": primes, "terms": st["terms_done"],
                "wall_s": wall, "busy_s": st["busy_s"], "steps": st["steps"], "offered_terms_per_s": offered,
                "capacity_terms_per_s": capacity, "offered_over_capacity": offered / capacity if capacity else None,
-               "sum_kernel_s": st["sum_s"], "valu_tops": valu, "frac": valu / (PEAK_VALU / 1e12)}
+               "sum_kernel_s": st["sum_s"], "valu_tops": valu, "frac": valu / (PEAK_VALU / 1e12) if valu is not None else None}
     return summary, out
 
 
