@@ -2,7 +2,7 @@
 // launch takes the primes to their residues, instead of the plan, chunk
 // layout, sums, reduction and finish over (prime, sum) slots, whose launches and
 // records cost more than the sums (a call of 16 primes near 2e7 0.46 ms, now
-// 0.12; the search of the primes below 1e5 0.62 ms, now 0.22, k_direct 73 us of it
+// 0.12; the search of the primes below 1e5 0.62 ms, now 0.18, k_direct 72 us of it
 // for 4e7 terms and 9590 stagings and inverses).
 //
 // The sums of a side, sum_j coef_j sum_s s^-3 or s^-2, are kept as one
@@ -124,15 +124,33 @@ __device__ __forceinline__ void side_part(const Side &S, uint64_t t, uint64_t al
     const int n = S.n;
     using Idx = typename std::conditional<SMALL, uint32_t, uint64_t>::type;
     const Idx groups = (Idx)S.base[n], step = (Idx)all;
-    const double ds = 4.0 * (double)all;
-    Idx g = (Idx)t;
-    for (int j = 0; g < groups; j++) {
-        const Idx end = (Idx)S.base[j + 1];
-        if (g >= end) continue;
-        const double coef = S.coef[j];
-        double s = fma(4.0, (double)(g - (Idx)S.base[j]), S.lo[j]);
+    if (groups < 2 * (uint64_t)n * all) {
+        // short sums: group after group whatever its sum, so that no lane waits for
+        // a sum that others have a part in (primes below 1e5: 72 us, 105 the
+        // other way)
+        int j = 0;
+        Idx end = (Idx)S.base[1];
+        double s0 = S.lo[0], coef = S.coef[0];
+        for (Idx g = (Idx)t; g < groups; g += step) {
+            if (g >= end) {
+                do end = (Idx)S.base[++j + 1];
+                while (g >= end);
+                s0 = fma(-4.0, (double)S.base[j], S.lo[j]);
+                coef = S.coef[j];
+            }
+            add_four<DEG>(fma(4.0, (double)g, s0), coef, c0, c1, m);
+        }
+    } else {
+        const double ds = 4.0 * (double)all;
+        Idx g = (Idx)t;
+        for (int j = 0; g < groups; j++) {
+            const Idx end = (Idx)S.base[j + 1];
+            if (g >= end) continue;
+            const double coef = S.coef[j];
+            double s = fma(4.0, (double)(g - (Idx)S.base[j]), S.lo[j]);
 #pragma unroll 2
-        for (; g < end; g += step, s += ds) add_four<DEG>(s, coef, c0, c1, m);
+            for (; g < end; g += step, s += ds) add_four<DEG>(s, coef, c0, c1, m);
+        }
     }
     for (uint64_t g = t; g < 3 * (uint64_t)n; g += all) {   // the up to three s beyond each sum's groups
         const int k = (int)(g / 3), r = (int)(g % 3);

@@ -683,7 +683,8 @@ __global__ void __launch_bounds__(256) k_irr_final(const IrrPrime *__restrict__ 
         if (at < pair_cap) pairs[at] = wv_irr_pair{p, (uint32_t)(2 * k), kind};
     };
     double c[R], w[R], pe[R];
-#pragma unroll(OUT ? R : 1)
+    constexpr int kUnroll = OUT ? R : 1;
+#pragma unroll kUnroll
     for (int r = 0; r < R; r++) {
         const uint64_t k = k1 + 64 * r;
         c[r] = w[r] = 1.0;

