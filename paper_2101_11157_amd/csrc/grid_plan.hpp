@@ -121,23 +121,29 @@ inline double grid_build_ops(int logl) {
     return ops;
 }
 
-// The least modelled work over the lengths and compiled congruences for primes
-// near p.  A length needs p >= 4 L^2: every
+// The compiled congruences of least modelled work for primes near p at one
+// length.
+inline GridClass grid_at_length(uint64_t p, int logl) {
+    GridClass c;
+    c.logl = logl;
+    double b = 1e300, e = 1e300;
+    for (int t = WV_TABLE_BB1; t <= WV_TABLE_EE33; t++) {
+        const double v = grid_side_ops(t, (double)p, logl);
+        if (kTables[t].deg == 3 && v < b) b = v, c.tb = t;
+        if (kTables[t].deg == 2 && v < e) e = v, c.te = t;
+    }
+    c.ops = b + e + grid_build_ops(logl);
+    return c;
+}
+
+// The least modelled work over the lengths, too.  A length needs p >= 4 L^2: every
 // difference of two points, at most p/2 + 2 K W, is then below p and nonzero.
 inline GridClass grid_search(uint64_t p, int max_log) {
     GridClass best;
     best.ops = 1e300;
     for (int logl = kNttMinLog; logl <= max_log; logl++) {
         if (p < (4ull << (2 * logl)) || (logl > kNttMaxLog && p >= kGridSplitMaxP)) break;
-        GridClass c;
-        c.logl = logl;
-        double b = 1e300, e = 1e300;
-        for (int t = WV_TABLE_BB1; t <= WV_TABLE_EE33; t++) {
-            const double v = grid_side_ops(t, (double)p, logl);
-            if (kTables[t].deg == 3 && v < b) b = v, c.tb = t;
-            if (kTables[t].deg == 2 && v < e) e = v, c.te = t;
-        }
-        c.ops = b + e + grid_build_ops(logl);
+        const GridClass c = grid_at_length(p, logl);
         if (c.ops < best.ops) best = c;
     }
     return best;
@@ -145,7 +151,7 @@ inline GridClass grid_search(uint64_t p, int max_log) {
 
 // The grid path's class for p: that of the least prime of its sixteenth of an
 // octave (so primes of one size share a class), searched once per process.
-inline const GridClass &grid_class(uint64_t p, int max_log = kGridMaxLog) {
+inline const GridClass &grid_class(uint64_t p) {
     struct Table {
         GridClass c[2][16 * 41];
         Table() {
@@ -157,22 +163,37 @@ inline const GridClass &grid_class(uint64_t p, int max_log = kGridMaxLog) {
     int i = std::min((int)(std::log2((double)p) * 16.0), 16 * 41 - 1);
     while (i > 0 && p < (uint64_t)std::ceil(std::exp2(i / 16.0))) i--;   // rounding of the logarithm
     // (the last prime of a sixteenth may lie beyond the split's range when its first does not)
-    const bool split = max_log > kNttMaxLog && p < kGridSplitMaxP;
-    return t.c[split ? 1 : 0][i];
+    return t.c[p < kGridSplitMaxP ? 1 : 0][i];
 }
 
-// The class a batch of n primes up to pmax of class g runs in.  Few primes: the
-// rounds of shifts the 256 CUs take, a split one 3.2 times as long as a whole one
-// (331 and 104 us), and one more doubling step (half a round): 7 primes at 1e11
-// take 1.28 ms split and 1.03 whole, 9 at 2e11 1.64 and 1.90.
-inline const GridClass &grid_batch_class(const GridClass &g, uint64_t n, uint64_t pmax) {
-    if (g.logl <= kNttMaxLog) return g;
-    const GridClass &whole = grid_class(pmax, kNttMaxLog);
-    auto rounds = [&](const GridClass &c) {
-        return std::ceil((double)n / 256.0 * (grid_shifts_est(c.tb, (double)pmax, c.logl) +
-                                              grid_shifts_est(c.te, (double)pmax, c.logl)));
+// The class a batch of n primes up to pmax, of class own, runs in.  Few primes do
+// not fill the chip: their time is the chain of doubling steps, longer with every
+// length, and the rounds in which the resident workgroups take the shifts (half
+// way between whole rounds and their fraction, the waves of a round finishing
+// apart).  Fitted to lists of 1 to 32 primes from 1e9 to 4e11, microseconds; of
+// the lengths from 2^12 to the batch's own, measured with the class of many primes
+// / this choice: 2 primes at 5e9 482 / 380, 1 at 2e10 488 / 403, 1 at 5e10 508 /
+// 467, 32 at 5e9 650 / 580, 7 at 1e11 1280 / 1030 (a split length's own).
+inline GridClass grid_batch_class(const GridClass &own, uint64_t n, uint64_t pmax) {
+    constexpr int kLow = 12;
+    static constexpr double chain[] = {330, 330, 400, 530}, round[] = {100, 112, 128, 360};
+    static constexpr double resident[] = {1024, 512, 256, 256};
+    static_assert(kLow + 3 == kGridMaxLog, "an entry per length");
+    if (own.logl <= kLow || n > 256) return own;
+    auto time = [&](const GridClass &c) {
+        const int k = c.logl - kLow;
+        const double r = (double)n / resident[k] *
+                         (grid_shifts_est(c.tb, (double)pmax, c.logl) + grid_shifts_est(c.te, (double)pmax, c.logl));
+        return chain[k] + round[k] * 0.5 * (r + std::ceil(r));
     };
-    return n < 256 && 3.2 * rounds(g) + 0.5 > rounds(whole) ? whole : g;
+    GridClass best = own;
+    double best_t = time(own);
+    for (int l = own.logl - 1; l >= kLow; l--) {
+        const GridClass c = grid_at_length(pmax, l);
+        const double v = time(c);
+        if (v < best_t) best_t = v, best = c;
+    }
+    return best;
 }
 
 // Operations per prime near p in class g.

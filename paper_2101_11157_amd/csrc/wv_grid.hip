@@ -970,7 +970,7 @@ bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g) {
 int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &own, const uint64_t *d_primes, uint32_t n,
                  uint64_t pmax, unsigned long long *terms, wv_result *d_out) {
     if (n == 0) return WV_OK;
-    const GridClass &g = grid_batch_class(own, n, pmax);
+    const GridClass g = grid_batch_class(own, n, pmax);
     for (int l = kNttMinLog; l <= std::min(g.logl, kNttMaxLog); l++) WV_TRY(ntt_tables(c, l));
     if (g.logl > kNttMaxLog) WV_TRY(split_table(c));
     WV_TRY(runs_table(c));
@@ -1008,7 +1008,7 @@ void grid_free(GridWork &b) {
 int grid_batch_sync(wv_ctx *c, const GridClass &own, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
                     wv_result *d_out) {
     if (n == 0) return WV_OK;
-    const GridClass &g = grid_batch_class(own, n, pmax);   // as grid_enqueue takes it
+    const GridClass g = grid_batch_class(own, n, pmax);   // as grid_enqueue takes it
     hipStream_t st = c->stream;
     auto *terms = as<unsigned long long>(c->scal);
     WV_HIP(hipEventRecord(c->ev[EV_PLAN0], st));

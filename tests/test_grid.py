@@ -192,7 +192,7 @@ def test_server_mixes_both_paths(grid, terms, step_terms, fault):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("lo,n", [(9 * 2 ** 23, 400), (10 ** 10, 40), (3 * 10 ** 10, 40), (10 ** 11 - 5000, 40),
-                                  (10 ** 11 - 8000, 300), (2 ** 39 - 700, 20), (2 ** 39 + 1, 12)])
+                                  (5 * 10 ** 9, 5), (2 * 10 ** 10, 9), (10 ** 11 - 8000, 300), (2 ** 39 - 700, 20), (2 ** 39 + 1, 12)])
 def test_ends_of_the_path_and_of_split_transforms(lo, n):
     """The first primes of the path, and batches large enough for transforms
     split into two, up to where they end."""
@@ -201,5 +201,5 @@ def test_ends_of_the_path_and_of_split_transforms(lo, n):
     with wv.Context(0) as grid, wv.Context(0) as sums:
         sums.set_block(28, 36)
         got = grid.eval_primes(ps)
-        assert grid.stats()["chunk_terms"] in ([16383] if (lo, n) in [(10 ** 11 - 8000, 300), (2 ** 39 - 700, 20)] else [1023, 2047, 8191, 16383, 4])
+        assert grid.stats()["chunk_terms"] in ([16383] if (lo, n) in [(10 ** 11 - 8000, 300), (2 ** 39 - 700, 20)] else [1023, 2047, 4095, 8191, 16383, 4])
         assert np.array_equal(got, sums.eval_primes(ps))
