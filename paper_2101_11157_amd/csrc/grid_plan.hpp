@@ -22,6 +22,7 @@ struct GridClass {
 // split into two of them (below 2^39, where its sums of 2^14 products stay
 // below a quarter of the moduli's product).
 constexpr int kGridMaxLog = kNttMaxLog + 1;
+constexpr int kGridMinLog = 11;   // the shortest the path's primes take
 constexpr uint64_t kGridSplitMaxP = 1ull << 39;
 
 constexpr uint64_t grid_k(int logl) { return (1ull << (logl - 1)) - 1; }
@@ -141,7 +142,7 @@ inline GridClass grid_at_length(uint64_t p, int logl) {
 inline GridClass grid_search(uint64_t p, int max_log) {
     GridClass best;
     best.ops = 1e300;
-    for (int logl = kNttMinLog; logl <= max_log; logl++) {
+    for (int logl = kGridMinLog; logl <= max_log; logl++) {
         if (p < (4ull << (2 * logl)) || (logl > kNttMaxLog && p >= kGridSplitMaxP)) break;
         const GridClass c = grid_at_length(p, logl);
         if (c.ops < best.ops) best = c;

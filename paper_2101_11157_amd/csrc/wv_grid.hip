@@ -864,8 +864,6 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
     const unsigned inv_grid = (unsigned)c->num_cus * 8;
     double *inv = at(y.inv);
     switch (logw) {
-    case 8: launch_inv<4>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
-    case 9: launch_inv<8>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
     case 10: launch_inv<16>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
     default: launch_inv<32>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
     }
@@ -929,8 +927,11 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
                            as<double>(c->ntt_split), at(y.half));
     else WV_TRY(with_shape(g.logl, [&](auto s) -> int {
         constexpr int LG = decltype(s)::value;
-        hipLaunchKernelGGL(k_grid_shift<LG>, dim3(grid_blocks(c, LG)), dim3(NttShape<LG>::T), 0, st, a);
-        return WV_OK;
+        if constexpr (LG >= kGridMinLog) {
+            hipLaunchKernelGGL(k_grid_shift<LG>, dim3(grid_blocks(c, LG)), dim3(NttShape<LG>::T), 0, st, a);
+            return WV_OK;
+        }
+        return WV_EINVAL;
     }));
     auto join = [&](auto nw) {
         constexpr int NW = decltype(nw)::value;
@@ -939,8 +940,8 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
                            at(y.vals), K, logw, as<Pair>(b.seg_pairs));
     };
     // a wave's reduction costs about what 50 of its terms or blocks do, so
-    // batches of many sums take few waves each (those of 4832 primes near 1e9
-    // 1.24 ms with eight, 0.5 with two), small ones enough to end soon
+    // batches of many sums take few waves each (those of 2416 primes near 1e9 1.24
+    // ms with eight, 0.75 with two), small ones enough to end soon
     if (nseg < 2048) join(std::integral_constant<int, 8>{});
     else if (K < 2047) join(std::integral_constant<int, 1>{});
     else if (K < 8191) join(std::integral_constant<int, 2>{});

@@ -97,10 +97,10 @@ static void classes() {
         if (k == 0) p = (1ull << 40) - 1;
         const GridClass c = grid_class(p);
         if (c.logl == 0) {
-            CHECK(p < (4ull << (2 * kNttMinLog)));
+            CHECK(p < (4ull << (2 * kGridMinLog)));
             continue;
         }
-        CHECK(c.logl >= kNttMinLog && c.logl <= kGridMaxLog && p >= (4ull << (2 * c.logl)));
+        CHECK(c.logl >= kGridMinLog && c.logl <= kGridMaxLog && p >= (4ull << (2 * c.logl)));
         CHECK(c.tb >= WV_TABLE_BB1 && c.tb <= WV_TABLE_BB30 && c.te >= WV_TABLE_EE3 && c.te <= WV_TABLE_EE33);
         const uint64_t K = grid_k(c.logl), W = grid_w(c.logl);
         CHECK(W == K + 1);
