@@ -881,40 +881,92 @@ constexpr double kDftMul = 16.0;       // a product and its share of the loads, 
 // per position.
 uint32_t dft_blocks(uint64_t h, int logl) { return (uint32_t)((h + (1ull << (logl - 1)) - 1) >> (logl - 1)); }
 
+// Modelled work of one prime's transforms: 6 A - 1 of them and the products of
+// its blocks, per modulus.
+double dft_work(uint32_t blocks, int logl, uint32_t nq) {
+    const double A = blocks, L = (double)(1ull << logl);
+    return nq * L * ((6.0 * A - 1.0) * (14.0 + 2.6 * logl) + 2.0 * A * A * kDftMul);
+}
+
 int dft_logl(uint64_t h) {
     int best = kNttMaxLog;
     double best_w = 1e300;
     for (int l = kNttMinLog; l <= kNttMaxLog; l++) {
-        const double A = dft_blocks(h, l), L = (double)(1ull << l);
-        const double w = L * ((6.0 * A - 1.0) * (14.0 + 2.6 * l) + 2.0 * A * A * kDftMul);
+        const double w = dft_work(dft_blocks(h, l), l, 1);
         if (w < best_w) best_w = w, best = l;
     }
     return best;
 }
 
-// The totals V of every prime by the transform, enqueued: primes ascending, in
-// groups of one length, number of blocks and number of moduli, each within the
-// workspace bound.  keep: the host data of the queued copies, until the stream
-// is waited for.
+// The totals V of every prime by the transform, enqueued in groups of one shape
+// (length, blocks, moduli), each within the workspace bound.  Primes are
+// ascending; the smaller ones join the shape of the larger while that costs less
+// than a group's launches (about 40 us; 1.5e13 modelled units a second), which is most
+// of the time of windows of small primes: [100, 8292) each in its own shape 0.83
+// ms, joined 0.67 ([500, 4596) 0.56 and 0.35).  keep: the host data of the queued copies, until the stream is
+// waited for.
+constexpr double kDftGroup = 6e8;
+constexpr double kDftSquares = 2.5e7;
+struct DftGroup {
+    size_t begin, end;
+    int logl;
+    uint32_t A, nq;
+};
+
+std::vector<DftGroup> dft_groups(const std::vector<IrrPrime> &prs) {
+    std::vector<DftGroup> out;
+    size_t end = prs.size();
+    uint64_t last_k = 0;
+    int last_l = 0;
+    while (end > 0) {
+        auto shape = [&](size_t i) {
+            // every block is a multiple of 256 values: so are the ends of the shapes' ranges
+            const uint64_t k = ((prs[i].p - 1) / 2 + 255) / 256;
+            if (k != last_k) {
+                last_k = k;
+                last_l = dft_logl(256 * k);
+            }
+            return DftGroup{i, end, last_l, dft_blocks(256 * k, last_l), prs[i].p < kIrrOneQ ? 1u : 2u};
+        };
+        DftGroup g = shape(end - 1);
+        const double mine = dft_work(g.A, g.logl, g.nq);
+        while (g.begin > 0) {
+            // the run of one shape before the group
+            const DftGroup o = shape(g.begin - 1);
+            size_t i = g.begin - 1;
+            while (i > 0) {
+                const DftGroup q = shape(i - 1);
+                if (q.logl != o.logl || q.A != o.A || q.nq != o.nq) break;
+                i--;
+            }
+            const bool same = o.logl == g.logl && o.A == g.A && o.nq == g.nq;
+            if (!same && (mine - dft_work(o.A, o.logl, o.nq)) * (double)(g.begin - i) > kDftGroup) break;
+            g.begin = i;
+        }
+        out.push_back(g);
+        end = g.begin;
+    }
+    return out;
+}
+
 constexpr uint64_t kDftDoubles = 1ull << 30;   // sequences and transforms held at once (8 GiB), unless one prime needs more
 
 int irr_dft(wv_ctx *c, const std::vector<IrrPrime> &prs, std::vector<std::vector<IrrNtt>> &keep) {
     hipStream_t st = c->stream;
-    size_t i = 0;
-    while (i < prs.size()) {
-        const uint64_t h0 = (prs[i].p - 1) / 2;
-        const int logl = dft_logl(h0);
+    const std::vector<DftGroup> groups = dft_groups(prs);
+    size_t i = groups.empty() ? 0 : groups[0].begin;
+    for (size_t k = 0; k < groups.size();) {
+        const DftGroup &gr = groups[k];
+        const int logl = gr.logl;
         const uint64_t L = 1ull << logl;
-        IrrShape sh{0, dft_blocks(h0, logl), (uint32_t)(L / 2), prs[i].p < kIrrOneQ ? 1u : 2u};
+        IrrShape sh{0, gr.A, (uint32_t)(L / 2), gr.nq};
         const uint64_t each = sh.seq_len() + sh.vecs() * sh.nq * L, wgs = sh.vecs() * sh.nq * std::max<uint64_t>(L / 256, 4);
         const uint64_t most = std::max<uint64_t>(1, std::min(kDftDoubles / each, kMaxWgs / wgs));
         keep.emplace_back();
         std::vector<IrrNtt> &g = keep.back();
-        for (; i < prs.size() && g.size() < most; i++) {
-            const uint64_t p = prs[i].p, h = (p - 1) / 2;
-            if (dft_logl(h) != logl || dft_blocks(h, logl) != sh.A || (p < kIrrOneQ) != (sh.nq == 1)) break;
-            g.push_back(IrrNtt{p, prs[i].vb, prs[i].ve, h});
-        }
+        for (; i < gr.end && g.size() < most; i++)
+            g.push_back(IrrNtt{prs[i].p, prs[i].vb, prs[i].ve, (prs[i].p - 1) / 2});
+        if (i == gr.end && ++k < groups.size()) i = groups[k].begin;   // gr's shape is in sh
         sh.n = (uint32_t)g.size();
         WV_TRY(ntt_tables(c, logl));
         WV_TRY(ensure(c, c->irr_dft, g.size() * sizeof(IrrNtt)));
@@ -965,8 +1017,14 @@ int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *d_b, uint64_
     uint64_t vn = 0, res = 0;
     double work = 0.0;
     const uint64_t kFin = d_b ? 8 : 16;   // indices per lane of k_irr_final
-    // path 2: the matrix cores while every partial sum stays exact
-    const bool mma = c->irr_path == 2 && *std::max_element(ps.begin(), ps.end()) < kIrrMmaMaxP;
+    // Path 0: transforms, but the matrix cores for a batch of so little work that the
+    // launches count (p^2 summed over the batch; one prime near 3000 130 us by the
+    // matrix cores, 139 by transforms, near 5000 both 140, near 8000 167 and 149).
+    // Path 2: the matrix cores while every partial sum stays exact.
+    double squares = 0.0;
+    for (uint64_t p : ps) squares += (double)p * (double)p;
+    const bool dft = c->irr_path == 0 && squares >= kDftSquares;
+    const bool mma = c->irr_path != 1 && !dft && *std::max_element(ps.begin(), ps.end()) < kIrrMmaMaxP;
     // exponents per row 16 ct: the least work over whole row blocks, each row
     // costing its N multiply-adds per s plus about 8 for building its A entry
     // (one modular product), ties to wider rows
@@ -987,7 +1045,6 @@ int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *d_b, uint64_
         }
         return (hi - lo + kIrrWaveS - 1) / kIrrWaveS * ((nt + kIrrUnitT - 1) / kIrrUnitT);
     };
-    const bool dft = c->irr_path == 0;   // transforms; the other paths take the sums one by one
     std::vector<std::vector<IrrNtt>> keep;
     auto task = [&](IrrTask t) {
         if (dft) return;

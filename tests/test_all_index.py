@@ -62,9 +62,10 @@ def test_transforms_equal_power_sums(ctx, part):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("lo,hi", [(5, 1500), (65000, 66200), (130900, 131300)])
+@pytest.mark.parametrize("lo,hi", [(5, 13), (5, 1500), (1000, 1030), (1500, 5600), (65000, 66200), (130900, 131300)])
 def test_census_by_transforms(ctx, lo, hi):
-    """Several lengths and both numbers of moduli within one window."""
+    """Several lengths and both numbers of moduli within one window, joined into
+    the larger ones; windows too small for transforms."""
     say(f"case: census by transforms, [{lo}, {hi})")
     got = ctx.irregular_pairs(lo, hi)
     ctx.set_irregular_path(1)
