@@ -287,7 +287,8 @@ int wv_bernoulli_euler_all(wv_ctx *ctx, uint64_t p, uint64_t *b, uint64_t *e);
 
 /* Method of wv_bernoulli_euler_all / wv_irregular_pairs:
  * 0 automatic (the power sums of all exponents as one discrete Fourier
- * transform per prime and side, by exact convolutions),
+ * transform per prime and side, by exact convolutions; the smallest batches
+ * as 2),
  * 1 power sums on the vector ALU, 2 power sums on the matrix cores for batches
  * with every p < 2^24 (where partial sums of up to 1024 products, reduced mod p
  * before they reach 2^53, stay exact f64 integers; vector ALU otherwise).
