@@ -177,17 +177,20 @@ BatchBufs ctx_bufs(wv_ctx *c) {
     return b;
 }
 
-int enqueue_plan(wv_ctx *c, const BatchBufs &b, const uint64_t *d_primes, const BatchShape &sh, hipStream_t st) {
+int enqueue_plan(wv_ctx *c, const BatchBufs &b, const uint64_t *d_primes, const BatchShape &sh, hipStream_t st,
+                 bool ready) {
     uint64_t *scal = b.scal;
     uint64_t *toff = b.off;   // prefix of terms, then of full chunks
     const uint64_t chunk_cfg = c->chunk_cfg ? c->chunk_cfg : c->chunk_auto;
-    WV_HIP(launch_set_u64(st, scal, 8, 0));
+    if (!ready) WV_HIP(launch_set_u64(st, scal, 8, 0));
     WV_HIP(launch_plan(st, d_primes, sh.n, sh.tb, sh.te, table_fallback(c, sh.tb), table_fallback(c, sh.te), sh.nB,
                        sh.nE, table_store(c), b.pr, b.segs, b.terms, b.coefs, b.lhsmod, 0));
     WV_HIP(launch_scan(st, b.terms, sh.nseg, toff, b.tiles));
     WV_HIP(launch_pick_chunk(st, toff + sh.nseg, sh.nseg, chunk_cfg, sum_lanes(c), sh.cap, scal + kScalLayout));
-    WV_HIP(launch_copy_u64(st, toff + sh.nseg, scal + kScalTerms, 1));
-    WV_HIP(launch_copy_u64(st, toff + (uint64_t)sh.n * sh.nB, scal + kScalTermsB, 1));
+    if (!ready) {
+        WV_HIP(launch_copy_u64(st, toff + sh.nseg, scal + kScalTerms, 1));
+        WV_HIP(launch_copy_u64(st, toff + (uint64_t)sh.n * sh.nB, scal + kScalTermsB, 1));
+    }
     WV_HIP(launch_chunk_layout(st, b.terms, sh.nseg, (uint64_t)sh.n * sh.nB, scal + kScalLayout, b.cnt, toff, b.tiles,
                                b.tail_hist, b.tails, scal + kScalChunks));
     return WV_OK;

@@ -195,7 +195,9 @@ BatchBufs ctx_bufs(wv_ctx *c);
 // The three stages of a batch, enqueued on st with buffers b (sized for sh);
 // nothing is allocated, every word that must start at zero is cleared by a
 // kernel, so the sequence can be captured in a graph.
-int enqueue_plan(wv_ctx *c, const BatchBufs &b, const uint64_t *d_primes, const BatchShape &sh, hipStream_t st);
+// ready: the scalars are cleared and the terms are not asked for
+int enqueue_plan(wv_ctx *c, const BatchBufs &b, const uint64_t *d_primes, const BatchShape &sh, hipStream_t st,
+                 bool ready = false);
 int enqueue_sum(wv_ctx *c, const BatchBufs &b, const BatchShape &sh, hipStream_t st, uint64_t begin, uint64_t end);
 int enqueue_finish(wv_ctx *c, const BatchBufs &b, const BatchShape &sh, hipStream_t st, wv_result *d_out);
 int run_batch_sync(wv_ctx *c, const uint64_t *d_primes, uint32_t n, uint64_t pmax, wv_result *d_out);
@@ -267,6 +269,19 @@ bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, DirectShape *d);
 int direct_reserve(wv_ctx *c, uint32_t n, const DirectShape &d);
 int direct_enqueue(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, uint32_t n, wv_result *d_out);
 int direct_batch_sync(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, uint32_t n, wv_result *d_out);
+// where only the device knows the primes: the choice, then (after the term sums of
+// the primes it left them) the run
+constexpr uint64_t kDirectParts = 1 << 14;   // fractions held
+struct DirectScratch {
+    uint64_t *gated;     // n primes for the term sums
+    double *part;        // 4 kDirectParts
+    uint32_t *ticket;    // n
+    uint32_t *mode;      // 2
+};
+int direct_device_pick(wv_ctx *c, const uint64_t *d_primes, uint32_t n, const DirectScratch &x, uint64_t *scal,
+                       hipStream_t st);
+int direct_device_run(wv_ctx *c, const uint64_t *d_primes, uint32_t n, const DirectScratch &x, wv_result *d_out,
+                      hipStream_t st);
 void direct_stats(wv_ctx *c, const DirectShape &d, uint64_t n, const uint64_t *scal);
 
 // The grid path (wv_grid.hip) takes primes from this size on when the context

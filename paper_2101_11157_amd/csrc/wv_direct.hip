@@ -174,21 +174,25 @@ WV_UNROLL
 // lane's terms, six wave steps and a Fermat inverse.  With G > 1 every
 // workgroup leaves its fraction in part and the one that draws the last ticket
 // (zeroed before the launch) adds them up.
+struct DirectLds {
+    Side side[2];
+    double red[kDirectWaves][4];
+    uint32_t last;
+};
+
 template <bool SMALL>
-__global__ void __launch_bounds__(64 * kDirectWaves) k_direct(TableStore ts, const uint64_t *__restrict__ primes, int tb,
-                                                              int te, int fb, int fe, uint32_t G, double *part,
-                                                              uint32_t *ticket, uint64_t *__restrict__ terms,
-                                                              wv_result *__restrict__ out) {
-    __shared__ Side side[2];
-    __shared__ double red[kDirectWaves][4];
-    __shared__ uint32_t last;
+__device__ void direct_prime(DirectLds &lds, const TableStore &ts, const uint64_t *__restrict__ primes, int tb, int te,
+                             int fb, int fe, uint32_t i, uint32_t g, uint32_t G, double *part, uint32_t *ticket,
+                             uint64_t *__restrict__ terms, wv_result *__restrict__ out) {
+    Side(&side)[2] = lds.side;
+    double(&red)[kDirectWaves][4] = lds.red;
+    uint32_t &last = lds.last;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
-    const uint32_t i = blockIdx.x / G, g = blockIdx.x % G;
     const uint64_t p = readfirst_u64(primes[i]);
     if (!(p >= 5 && p < WV_P_MAX && (p & 1))) {
         if (threadIdx.x == 0 && g == 0) {
             out[i] = wv_result{0, 0, 0, 0xFFFFFFFFu, 0};
-            terms[2 * (size_t)i] = terms[2 * (size_t)i + 1] = 0;
+            if (terms) terms[2 * (size_t)i] = terms[2 * (size_t)i + 1] = 0;
         }
         return;
     }
@@ -218,7 +222,7 @@ __global__ void __launch_bounds__(64 * kDirectWaves) k_direct(TableStore ts, con
         }
     }
     if (G > 1) {
-        double *mine = part + 4 * (size_t)blockIdx.x;
+        double *mine = part + 4 * ((size_t)i * G + g);
         if (threadIdx.x == 0) {
             const double v[4] = {b0, b1, e0, e1};
             for (int k = 0; k < 4; k++) __hip_atomic_store(mine + k, v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -251,9 +255,82 @@ __global__ void __launch_bounds__(64 * kDirectWaves) k_direct(TableStore ts, con
     const uint64_t re = __shfl((unsigned long long)r, 1, 64);
     if (lane == 0) {
         out[i] = wv_result{p, r, re, (r == 0 ? WV_FLAG_WOLSTENHOLME : 0u) | (re == 0 ? WV_FLAG_VANDIVER : 0u), 0};
-        terms[2 * (size_t)i] = side[0].terms;
-        terms[2 * (size_t)i + 1] = side[1].terms;
+        if (terms) {
+            terms[2 * (size_t)i] = side[0].terms;
+            terms[2 * (size_t)i + 1] = side[1].terms;
+        }
     }
+}
+
+template <bool SMALL>
+__global__ void __launch_bounds__(64 * kDirectWaves) k_direct(TableStore ts, const uint64_t *__restrict__ primes, int tb,
+                                                              int te, int fb, int fe, uint32_t G, double *part,
+                                                              uint32_t *ticket, uint64_t *__restrict__ terms,
+                                                              wv_result *__restrict__ out) {
+    __shared__ DirectLds lds;
+    direct_prime<SMALL>(lds, ts, primes, tb, te, fb, fe, blockIdx.x / G, blockIdx.x % G, G, part, ticket, terms, out);
+}
+
+// The same where only the device knows the primes: k_direct_pick has decided
+// (mode[0]: workgroups per prime, 0: the term sums; mode[1]: every p < 2^27), and a
+// fixed grid goes through the primes after the term sums have run, on primes
+// that were left out of them if they come this way.
+__global__ void __launch_bounds__(64 * kDirectWaves) k_direct_device(TableStore ts, const uint64_t *__restrict__ primes,
+                                                                     uint32_t n, int tb, int te, int fb, int fe,
+                                                                     const uint32_t *__restrict__ mode, double *part,
+                                                                     uint32_t *ticket, wv_result *__restrict__ out) {
+    __shared__ DirectLds lds;
+    const uint32_t G = __builtin_amdgcn_readfirstlane(mode[0]), small = __builtin_amdgcn_readfirstlane(mode[1]);
+    for (uint32_t w = blockIdx.x; w < n * G; w += gridDim.x) {
+        if (small) direct_prime<true>(lds, ts, primes, tb, te, fb, fe, w / G, w % G, G, part, ticket, nullptr, out);
+        else direct_prime<false>(lds, ts, primes, tb, te, fb, fe, w / G, w % G, G, part, ticket, nullptr, out);
+        __syncthreads();   // LDS free
+    }
+}
+
+// One workgroup: the batch's terms and largest prime, the choice of the path by
+// the rule of direct_takes, the primes for the term sums (all 0, which the
+// plan rejects, if they go the other way), cleared scalars and tickets.
+__global__ void __launch_bounds__(1024) k_direct_pick(const uint64_t *__restrict__ primes, uint32_t n, double cost,
+                                                      uint32_t threads, uint64_t *__restrict__ gated,
+                                                      uint64_t *__restrict__ scal, uint32_t *__restrict__ mode,
+                                                      uint32_t *__restrict__ ticket) {
+    __shared__ double sum[16];
+    __shared__ uint64_t top[16];
+    __shared__ uint32_t pick;
+    double s = 0.0;
+    uint64_t m = 0;
+    for (uint32_t i = threadIdx.x; i < n; i += 1024) {
+        const uint64_t p = primes[i];
+        if (p < WV_P_MAX) {
+            s += (double)p;
+            m = max(m, p);
+        }
+        ticket[i] = 0;
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        s += __shfl_xor(s, o, 64);
+        m = max(m, (uint64_t)__shfl_xor((unsigned long long)m, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0) sum[threadIdx.x >> 6] = s, top[threadIdx.x >> 6] = m;
+    if (threadIdx.x < 8) scal[threadIdx.x] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; w++) s += sum[w], m = max(m, top[w]);
+        const bool small = m < kDirectSmallP;
+        const double work = s * cost;
+        uint32_t G = 0;
+        if (small ? m < kDirectAllP || work <= kDirectSmallTerms : work <= kDirectTerms) {
+            const double lanes = min(kDirectLanes / n, work / n / kDirectLaneTerms);
+            for (G = 1; 2.0 * G * threads <= lanes && 2 * G * (uint64_t)n <= kDirectParts; G *= 2) {}
+        }
+        pick = G;
+        mode[0] = G;
+        mode[1] = small;
+    }
+    __syncthreads();
+    const bool sums = pick == 0;
+    for (uint32_t i = threadIdx.x; i < n; i += 1024) gated[i] = sums ? primes[i] : 0;
 }
 
 __global__ void __launch_bounds__(256) k_direct_zero(uint32_t *__restrict__ t, uint32_t n) {
@@ -321,6 +398,25 @@ int direct_enqueue(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, ui
                        as<double>(c->direct_part), as<uint32_t>(c->direct_ticket), as<uint64_t>(c->direct_terms), d_out);
     hipLaunchKernelGGL(k_direct_total, dim3(1), dim3(1024), 0, st, as<uint64_t>(c->direct_terms), n,
                        as<uint64_t>(c->scal));
+    WV_HIP(hipGetLastError());
+    return WV_OK;
+}
+
+static unsigned device_threads(uint32_t n) { return n > 4096 ? 64 : n > 512 ? 128 : 64 * kDirectWaves; }
+
+int direct_device_pick(wv_ctx *c, const uint64_t *d_primes, uint32_t n, const DirectScratch &x, uint64_t *scal,
+                       hipStream_t st) {
+    hipLaunchKernelGGL(k_direct_pick, dim3(1), dim3(1024), 0, st, d_primes, n, side_cost(c, c->tb) + side_cost(c, c->te),
+                       device_threads(n), x.gated, scal, x.mode, x.ticket);
+    WV_HIP(hipGetLastError());
+    return WV_OK;
+}
+
+int direct_device_run(wv_ctx *c, const uint64_t *d_primes, uint32_t n, const DirectScratch &x, wv_result *d_out,
+                      hipStream_t st) {
+    hipLaunchKernelGGL(k_direct_device, dim3((unsigned)c->num_cus * 8), dim3(device_threads(n)), 0, st, table_store(c),
+                       d_primes, n, c->tb, c->te, table_fallback(c, c->tb), table_fallback(c, c->te), x.mode, x.part,
+                       x.ticket, d_out);
     WV_HIP(hipGetLastError());
     return WV_OK;
 }

@@ -39,6 +39,12 @@ constexpr size_t kScratchBytes = align256(kOffHist + 2 * kTailClasses * sizeof(u
 static_assert(kScratchBytes <= WV_STATIC_SCRATCH_BYTES, "scratch layout exceeds the documented size");
 static_assert(WV_STATIC_MAX_CHUNKS >= 2 * WV_STATIC_MAX_SLOTS, "partial pairs must exceed twice the slots");
 
+// the direct path's: the mode behind the scalars, the rest within the partial pairs
+constexpr size_t kOffGatedEnd = align256(kOffPartials + WV_STATIC_MAX_PRIMES * sizeof(uint64_t));
+constexpr size_t kOffPartEnd = align256(kOffGatedEnd + 4 * kDirectParts * sizeof(double));
+static_assert(kOffPartEnd + WV_STATIC_MAX_PRIMES * sizeof(uint32_t) <= kOffSegPairs, "within the partial pairs");
+static_assert(kOffScal + 8 * sizeof(uint64_t) + 2 * sizeof(uint32_t) <= kOffPartials, "behind the scalars");
+
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
 void *g_addr[kMaxDevices] = {};   // device address of `scratch` on each device
@@ -60,6 +66,16 @@ BatchBufs carve(void *base) {
     r.tails = reinterpret_cast<uint32_t *>(b + kOffTails);
     r.tail_hist = reinterpret_cast<unsigned long long *>(b + kOffHist);
     return r;
+}
+
+DirectScratch carve_direct(void *base) {
+    char *b = static_cast<char *>(base);
+    DirectScratch x;
+    x.gated = reinterpret_cast<uint64_t *>(b + kOffPartials);
+    x.part = reinterpret_cast<double *>(b + kOffGatedEnd);
+    x.ticket = reinterpret_cast<uint32_t *>(b + kOffPartEnd);
+    x.mode = reinterpret_cast<uint32_t *>(b + kOffScal + 8 * sizeof(uint64_t));
+    return x;
 }
 
 }  // namespace
@@ -100,8 +116,21 @@ extern "C" int wv_eval_primes_static(wv_ctx *c, const uint64_t *d_primes, size_t
     sh.cap = WV_STATIC_MAX_CHUNKS;
     const BatchBufs b = carve(c->scratch);
     hipStream_t st = (hipStream_t)hip_stream;
-    WV_TRY(enqueue_plan(c, b, d_primes, sh, st));
+    if (!grid_allowed(c, c->tb, c->te)) {
+        WV_TRY(enqueue_plan(c, b, d_primes, sh, st));
+        WV_TRY(enqueue_sum(c, b, sh, st, 0, UINT64_MAX));
+        WV_TRY(enqueue_finish(c, b, sh, st, d_out));
+        return WV_OK;
+    }
+    // Little work goes the direct way, which the device decides: the term sums
+    // then get a batch without primes and their flagged results are overwritten.
+    // (A list of 500 primes near 1e5: 0.11 ms, by term sums 0.54.)  The direct path's
+    // buffers lie where the term sums keep the chunks' pairs, of which such a
+    // batch has none; the primes given to the plan are read before any is written.
+    const DirectScratch x = carve_direct(c->scratch);
+    WV_TRY(direct_device_pick(c, d_primes, (uint32_t)n, x, b.scal, st));
+    WV_TRY(enqueue_plan(c, b, x.gated, sh, st, true));
     WV_TRY(enqueue_sum(c, b, sh, st, 0, UINT64_MAX));
     WV_TRY(enqueue_finish(c, b, sh, st, d_out));
-    return WV_OK;
+    return direct_device_run(c, d_primes, (uint32_t)n, x, d_out, st);
 }

@@ -3,6 +3,7 @@ a forced shape) and the oracle, at the ends of its ranges, of its groups of four
 terms and of the workgroups per prime."""
 import numpy as np
 import pytest
+import torch   # before the library: it loads its own HIP runtime first
 
 import oracle
 import paper_2101_11157_amd as wv
@@ -75,3 +76,25 @@ def test_lists_hold_primes_only(ctxs):
         assert e.value.status == wv.WV_ENOTPRIME, n
     got = ctxs[0].eval_primes([13, 23, 41, 43, 1662803, 1093, 3511])
     assert [int(p) for p in got["p"]] == [13, 23, 41, 43, 1662803, 1093, 3511]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("at,n", [(5, 1), (5, 40), (10 ** 5, 1), (10 ** 5, 600), (10 ** 6, 4200), (1 << 27, 3), (10 ** 9, 2),
+                                  (3 * 10 ** 7, 700), (10 ** 8, 300)])
+def test_device_lists_equal_the_term_sums(ctxs, at, n):
+    """The call that leaves the choice to the device, on both sides of it, with
+    rejected entries among the primes."""
+    print(f"case: direct, device list of {n} at {at}", flush=True)
+    ps = oracle.primes(at, at + 40 * n + 2000)[:n]
+    ps[len(ps) // 2:len(ps) // 2] = [0, 4, 2 ** 40 + 15]
+    d = torch.tensor(ps, dtype=torch.int64, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    got = []
+    for c in ctxs:
+        o = torch.zeros((len(ps), 4), dtype=torch.int64, device="cuda")
+        for _ in range(2):
+            c.eval_primes_static(d.data_ptr(), len(ps), o.data_ptr(), st)
+        torch.cuda.synchronize()
+        got.append(o.cpu().numpy())
+    assert np.array_equal(got[0], got[1])
+    assert int(np.count_nonzero(got[0][:, 0] == 0)) == 3
