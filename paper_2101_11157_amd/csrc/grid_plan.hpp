@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <vector>
 
 #include "ntt.hpp"
 #include "wv_tables.hpp"
@@ -137,14 +138,18 @@ inline GridClass grid_at_length(uint64_t p, int logl) {
     return c;
 }
 
-// The least modelled work over the lengths, too.  A length needs p >= 4 L^2: every
-// difference of two points, at most p/2 + 2 K W, is then below p and nonzero.
-inline GridClass grid_search(uint64_t p, int max_log) {
+// Whether p can take a length: p >= 4 L^2, so that every difference of two
+// points, at most p/2 + 2 K W, is below p and nonzero.
+inline bool grid_fits(uint64_t p, int logl) { return p >= (4ull << (2 * logl)); }
+
+// The least modelled work for primes near hi over the lengths, too, that every
+// prime from lo on can take.
+inline GridClass grid_search(uint64_t lo, uint64_t hi, int max_log) {
     GridClass best;
     best.ops = 1e300;
     for (int logl = kGridMinLog; logl <= max_log; logl++) {
-        if (p < (4ull << (2 * logl)) || (logl > kNttMaxLog && p >= kGridSplitMaxP)) break;
-        const GridClass c = grid_at_length(p, logl);
+        if (!grid_fits(lo, logl) || (logl > kNttMaxLog && hi >= kGridSplitMaxP)) break;
+        const GridClass c = grid_at_length(hi, logl);
         if (c.ops < best.ops) best = c;
     }
     return best;
@@ -157,7 +162,10 @@ inline const GridClass &grid_class(uint64_t p) {
         GridClass c[2][16 * 41];
         Table() {
             for (int i = 0; i < 16 * 41; i++)
-                for (int k = 0; k < 2; k++) c[k][i] = grid_search((uint64_t)std::ceil(std::exp2(i / 16.0)), kNttMaxLog + k);
+                for (int k = 0; k < 2; k++) {
+                    const uint64_t p = (uint64_t)std::ceil(std::exp2(i / 16.0));
+                    c[k][i] = grid_search(p, p, kNttMaxLog + k);
+                }
         }
     };
     static const Table t;
@@ -209,9 +217,57 @@ inline double grid_ops(uint64_t p, const GridClass &g) {
 // measured for one prime; the path runs at about 1.7e13 operations/s).
 constexpr double kGridRate = 1.7e13, kGridBatchS = 3.5e-4;
 inline bool grid_joins(uint64_t p, double n, const GridClass &g) {
-    if (p < (4ull << (2 * g.logl))) return false;
+    if (!grid_fits(p, g.logl)) return false;
     const GridClass &own = grid_class(p);
     return own == g || (grid_ops(p, g) - own.ops) * n < kGridBatchS * kGridRate;
+}
+
+// n primes of [lo, hi], all of the path's sizes; at: where the caller has them.
+struct GridItem {
+    uint64_t lo, hi;
+    uint32_t n, at;
+};
+
+// Items [begin, end) of one batch: n primes of [lo, hi], evaluated in class g,
+// whose length every one of them can take.
+struct GridBatch {
+    GridClass g;
+    uint64_t lo, hi;
+    uint32_t n;
+    size_t begin, end;
+};
+
+// The batches of items, which are put in descending order of hi: an item joins the batch before
+// it where that is the cheaper way (grid_joins) and its least prime can take
+// the batch's length; else it starts one in its own class, of a length that its
+// own least prime can take.
+inline std::vector<GridBatch> grid_batches(std::vector<GridItem> &items) {
+    std::vector<GridBatch> out;
+    std::stable_sort(items.begin(), items.end(), [](const GridItem &a, const GridItem &b) { return a.hi > b.hi; });
+    for (size_t i = 0; i < items.size(); i++) {
+        const GridItem &t = items[i];
+        if (out.empty() || !grid_fits(t.lo, out.back().g.logl) || !grid_joins(t.hi, t.n, out.back().g)) {
+            const GridClass &own = grid_class(t.hi);
+            out.push_back(GridBatch{grid_fits(t.lo, own.logl) ? own : grid_search(t.lo, t.hi, kNttMaxLog), t.lo, t.hi, 0, i, i});
+        }
+        GridBatch &b = out.back();
+        b.lo = std::min(b.lo, t.lo);
+        b.n += t.n;
+        b.end = i + 1;
+    }
+    return out;
+}
+
+// Ascending primes p[0 .. n), the first of them at `at`, as items of one class
+// each, appended to out.
+inline void grid_items(const uint64_t *p, size_t n, uint32_t at, std::vector<GridItem> &out) {
+    for (size_t i = 0; i < n;) {
+        const GridClass &g = grid_class(p[i]);
+        size_t j = i + 1;
+        while (j < n && grid_class(p[j]) == g) j++;
+        out.push_back(GridItem{p[i], p[j - 1], (uint32_t)(j - i), at + (uint32_t)i});
+        i = j;
+    }
 }
 
 }  // namespace wv

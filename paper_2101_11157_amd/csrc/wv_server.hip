@@ -62,7 +62,8 @@ struct Request {
     uint64_t id = 0;
     bool is_range = false;
     uint64_t lo = 0, hi = 0;
-    std::vector<uint64_t> primes;
+    std::vector<uint64_t> primes;   // of a list, ascending
+    std::vector<uint32_t> order;    // each one's place in the caller's list (empty: that was ascending)
     double t_submit = 0, t_admit = 0, t_done = 0;
     int state = REQ_PENDING;
     int status = WV_OK;        // WV_OK, or the error that ended the request
@@ -382,7 +383,7 @@ int launch_step(wv_server *s, int sk, bool *launched) {
     // are finalized at its end
     std::vector<StepSpan> spans, gspans;
     std::vector<FinReq> fins, gfins;
-    std::vector<std::pair<uint64_t, size_t>> gcand;   // (largest prime, candidate) of the grid path's requests
+    std::vector<GridItem> gitems;   // of the grid path's requests
     ss.finishing.clear();
     ss.fin_out.clear();
     uint32_t q0 = 0, nres = 0, ngres = 0;
@@ -391,7 +392,8 @@ int launch_step(wv_server *s, int sk, bool *launched) {
         if (!give[k]) continue;
         Request *r = cand[k];
         if (r->grid) {
-            gcand.push_back({r->pmax, k});
+            if (r->is_range) gitems.push_back(GridItem{r->pmin, r->pmax, give[k], r->base + r->next});
+            else grid_items(r->primes.data() + r->next, give[k], r->base + r->next, gitems);
             continue;
         }
         spans.push_back(StepSpan{(uint64_t)r->base * s->NS, r->n, r->next, q0, give[k]});
@@ -404,31 +406,22 @@ int launch_step(wv_server *s, int sk, bool *launched) {
             nres += r->n;
         }
     }
-    // the grid path's requests: largest primes first, in batches of one class;
-    // a span's i0 is its first pool slot and its q0 counts within the step
-    struct Batch {
-        GridClass g;
-        uint64_t pmax;
-        uint32_t q0, n;
-    };
-    std::vector<Batch> batches;
-    std::sort(gcand.begin(), gcand.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+    // the grid path's requests, their results behind the others'
+    for (size_t k = 0; k < cand.size(); k++) {
+        Request *r = cand[k];
+        if (!give[k] || !r->grid || r->next + give[k] != r->n) continue;
+        gfins.push_back(FinReq{r->base, r->n, ngres, 0});
+        ss.finishing.push_back(r);
+        ss.fin_out.push_back(nres + ngres);
+        ngres += r->n;
+    }
+    // in batches, largest primes first (a span's i0 is its first pool slot and
+    // its q0 counts within the step)
+    const std::vector<GridBatch> batches = grid_batches(gitems);
     uint32_t gq = 0;
-    for (const auto &gk : gcand) {
-        Request *r = cand[gk.second];
-        const uint32_t m = give[gk.second];
-        const bool joins = !batches.empty() && r->pmin >= (4ull << (2 * batches.back().g.logl)) &&
-                           grid_joins(r->pmax, m, batches.back().g);
-        if (!joins) batches.push_back(Batch{grid_class(r->pmax), r->pmax, gq, 0});
-        batches.back().n += m;
-        gspans.push_back(StepSpan{0, r->n, r->base + r->next, gq, m});
-        gq += m;
-        if (r->next + m == r->n) {
-            gfins.push_back(FinReq{r->base, r->n, ngres, 0});
-            ss.finishing.push_back(r);
-            ss.fin_out.push_back(nres + ngres);
-            ngres += r->n;
-        }
+    for (const GridItem &t : gitems) {
+        gspans.push_back(StepSpan{0, 0, t.at, gq, t.n});
+        gq += t.n;
     }
     const uint64_t nq_terms = q0;
     const uint64_t nt = nq_terms * (uint64_t)s->NS, nbt = nq_terms * (uint64_t)s->nB;
@@ -512,9 +505,11 @@ int launch_step(wv_server *s, int sk, bool *launched) {
     if (gq) {
         WV_HIP(launch_pool_gather(st, as<StepSpan>(ss.gspans), (uint32_t)gspans.size(), gq, as<uint64_t>(s->plist),
                                   as<uint64_t>(ss.gprimes)));
-        for (const Batch &b : batches)
-            WV_TRY(grid_enqueue(c, ss.grid, st, b.g, as<uint64_t>(ss.gprimes) + b.q0, b.n, b.pmax,
-                                (unsigned long long *)(scal + kStepGridTerms), as<wv_result>(ss.gres) + b.q0));
+        for (const GridBatch &b : batches) {
+            const uint32_t g0 = gspans[b.begin].q0;
+            WV_TRY(grid_enqueue(c, ss.grid, st, b.g, as<uint64_t>(ss.gprimes) + g0, b.n, b.hi,
+                                (unsigned long long *)(scal + kStepGridTerms), as<wv_result>(ss.gres) + g0));
+        }
     }
     WV_HIP(hipEventRecord(ss.ev_sum, st));
     if (nt) {
@@ -591,6 +586,7 @@ int complete_step(wv_server *s, StepSet &ss) {
             continue;
         }
         r->results.assign(res, res + r->n);
+        for (size_t i = 0; i < r->order.size(); i++) r->results[r->order[i]] = res[i];
         pool_free(s, r->base, r->n);
         r->state = REQ_DONE;
         r->t_done = now_s();
@@ -771,6 +767,12 @@ int wv_server_submit_primes(wv_server *s, const uint64_t *primes, size_t n, uint
     if (!r) return WV_ENOMEM;
     r->id = s->next_id++;
     r->primes.assign(primes, primes + n);
+    if (!std::is_sorted(primes, primes + n)) {
+        r->order.resize(n);
+        for (size_t i = 0; i < n; i++) r->order[i] = (uint32_t)i;
+        std::stable_sort(r->order.begin(), r->order.end(), [&](uint32_t a, uint32_t b) { return primes[a] < primes[b]; });
+        for (size_t i = 0; i < n; i++) r->primes[i] = primes[r->order[i]];
+    }
     r->n_primes = n;
     r->pmin = pmin;
     r->pmax = pmax;
