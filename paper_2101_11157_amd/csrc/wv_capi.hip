@@ -454,13 +454,16 @@ int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector
         WV_TRY(compact(c, descs.data() + i, j - i, counts.data() + i, &got, nullptr, j - i <= kSieveLaunch));
         WV_HIP(hipEventRecord(c->ev[EV_SIEVE], st));
         WV_TRY(ensure(c, c->results, got * sizeof(wv_result)));
-        uint64_t pmax = 0;
-        for (size_t k = i; k < j; k++) pmax = std::max(pmax, std::min(descs[k].hi, descs[k].L + kSegSpan));
+        uint64_t pmin = UINT64_MAX, pmax = 0;
+        for (size_t k = i; k < j; k++) {
+            pmin = std::min(pmin, std::max(descs[k].L, descs[k].lo));
+            pmax = std::max(pmax, std::min(descs[k].hi, descs[k].L + kSegSpan));
+        }
         DirectShape ds;
         if (direct_takes(c, got, pmax, &ds))
             WV_TRY(direct_batch_sync(c, ds, as<uint64_t>(c->primes), (uint32_t)got, as<wv_result>(c->results)));
         else if (grid)
-            WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
+            WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes), (uint32_t)got, pmin, pmax, as<wv_result>(c->results)));
         else
             WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
         c->stats.ms_sieve += elapsed(c->ev[EV_START], c->ev[EV_SIEVE]);   // both recorded before its wait
@@ -1181,36 +1184,28 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
         WV_TRY(direct_batch_sync(c, ds, as<uint64_t>(c->primes), (uint32_t)n, as<wv_result>(c->results)));
         return results_to_host(c, as<wv_result>(c->results), n, out);
     }
-    // the primes of the grid path first, by class, the others (ascending
-    // too) after them; results go back to input order
-    std::vector<std::pair<uint64_t, size_t>> ord;
-    GridClass gc, gk;
+    // ascending: the primes of the grid path in its batches, those below its start
+    // by term sums; results go back to input order
+    GridClass gc;
     if (grid_takes(c, pmax, &gc)) {
-        ord.resize(n);
+        std::vector<std::pair<uint64_t, size_t>> ord(n);
         for (size_t i = 0; i < n; i++) ord[i] = {primes[i], i};
-        std::sort(ord.begin(), ord.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        std::sort(ord.begin(), ord.end());
         std::vector<uint64_t> sorted(n);
         for (size_t i = 0; i < n; i++) sorted[i] = ord[i].first;
         WV_HIP(hipMemcpyAsync(c->primes.ptr, sorted.data(), n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
-        size_t b = 0;
-        while (b < n && grid_takes(c, sorted[b], &gc)) {
-            // runs of smaller classes join while that is the cheaper way
-            size_t e = b;
-            while (e < n && grid_takes(c, sorted[e], &gk)) {
-                size_t r = e + 1;
-                while (r < n && sorted[r] >= kGridMinP && grid_class(sorted[r]) == gk) r++;
-                if (!grid_joins(sorted[e], (double)(r - e), gc)) break;
-                e = r;
-            }
-            WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes) + b, (uint32_t)(e - b), sorted[b],
-                                   as<wv_result>(c->results) + b));
-            b = e;
+        const size_t low = std::lower_bound(sorted.begin(), sorted.end(), kGridMinP) - sorted.begin();
+        std::vector<GridItem> items;
+        grid_items(sorted.data() + low, n - low, (uint32_t)low, items);
+        for (const GridBatch &b : grid_batches(items)) {
+            const size_t at = items[b.end - 1].at;   // descending, so this is the batch's first prime
+            WV_TRY(grid_batch_sync(c, b.g, as<uint64_t>(c->primes) + at, b.n, b.lo, b.hi, as<wv_result>(c->results) + at));
         }
         const uint64_t per = (uint64_t)side_slots(c, c->tb) + side_slots(c, c->te);
         const size_t step = (size_t)std::max<uint64_t>(1, kMaxBatchSlots / per);
-        for (; b < n; b += step) {
-            const size_t k = std::min(step, n - b);
-            WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes) + b, (uint32_t)k, sorted[b] + 1,
+        for (size_t b = 0; b < low; b += step) {
+            const size_t k = std::min(step, low - b);
+            WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes) + b, (uint32_t)k, sorted[b + k - 1] + 1,
                                   as<wv_result>(c->results) + b));
         }
         std::vector<wv_result> res(n);

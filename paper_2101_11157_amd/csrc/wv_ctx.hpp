@@ -293,14 +293,15 @@ void direct_stats(wv_ctx *c, const DirectShape &d, uint64_t n, const uint64_t *s
 constexpr uint64_t kGridMinP = 9ull << 23;
 bool grid_allowed(const wv_ctx *c, int tb, int te);   // with these tables configured
 bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g);
-// n primes in [4 * 4^logl, pmax] on the device -> d_out, enqueued on st with
-// buffers b; the terms covered are added to terms[0] (all) and terms[1] (s^-3)
+// n primes in [pmin, pmax] on the device -> d_out, enqueued on st with buffers b;
+// the terms covered are added to terms[0] (all) and terms[1] (s^-3).
+// WV_EINVAL if pmin cannot take the class's length (grid_fits).
 int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const uint64_t *d_primes, uint32_t n,
-                 uint64_t pmax, unsigned long long *terms, wv_result *d_out);
+                 uint64_t pmin, uint64_t pmax, unsigned long long *terms, wv_result *d_out);
 void grid_free(GridWork &b);
 // the same on the context's stream, waited for; fills c->stats
-int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
-                    wv_result *d_out);
+int grid_batch_sync(wv_ctx *c, const GridClass &g, const uint64_t *d_primes, uint32_t n, uint64_t pmin,
+                    uint64_t pmax, wv_result *d_out);
 // server: pool primes of a step's spans (i0: first pool slot) to out[q0 ..],
 // their results back, and the results of finished requests
 hipError_t launch_pool_gather(hipStream_t st, const StepSpan *sp, uint32_t nsp, uint32_t n, const uint64_t *plist,

@@ -969,9 +969,11 @@ bool grid_takes(const wv_ctx *c, uint64_t p, GridClass *g) {
 }
 
 int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &own, const uint64_t *d_primes, uint32_t n,
-                 uint64_t pmax, unsigned long long *terms, wv_result *d_out) {
+                 uint64_t pmin, uint64_t pmax, unsigned long long *terms, wv_result *d_out) {
     if (n == 0) return WV_OK;
-    const GridClass g = grid_batch_class(own, n, pmax);
+    // a difference of two points could be p, and its inverse and those found with it 0
+    if (!grid_fits(pmin, own.logl) || (own.logl > kNttMaxLog && pmax > kGridSplitMaxP)) return WV_EINVAL;
+    const GridClass g = grid_batch_class(own, n, pmax);   // no longer than own
     for (int l = kNttMinLog; l <= std::min(g.logl, kNttMaxLog); l++) WV_TRY(ntt_tables(c, l));
     if (g.logl > kNttMaxLog) WV_TRY(split_table(c));
     WV_TRY(runs_table(c));
@@ -1006,15 +1008,15 @@ void grid_free(GridWork &b) {
         if (x->ptr) (void)hipFree(x->ptr);
 }
 
-int grid_batch_sync(wv_ctx *c, const GridClass &own, const uint64_t *d_primes, uint32_t n, uint64_t pmax,
-                    wv_result *d_out) {
+int grid_batch_sync(wv_ctx *c, const GridClass &own, const uint64_t *d_primes, uint32_t n, uint64_t pmin,
+                    uint64_t pmax, wv_result *d_out) {
     if (n == 0) return WV_OK;
     const GridClass g = grid_batch_class(own, n, pmax);   // as grid_enqueue takes it
     hipStream_t st = c->stream;
     auto *terms = as<unsigned long long>(c->scal);
     WV_HIP(hipEventRecord(c->ev[EV_PLAN0], st));
     WV_HIP(launch_set_u64(st, as<uint64_t>(c->scal), 8, 0));
-    WV_TRY(grid_enqueue(c, c->grid, st, own, d_primes, n, pmax, terms, d_out));
+    WV_TRY(grid_enqueue(c, c->grid, st, own, d_primes, n, pmin, pmax, terms, d_out));
     WV_HIP(hipEventRecord(c->ev[EV_FINAL], st));
     uint64_t host[2];
     WV_HIP(hipMemcpyAsync(host, terms, sizeof(host), hipMemcpyDeviceToHost, st));

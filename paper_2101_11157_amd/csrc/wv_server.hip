@@ -507,7 +507,7 @@ int launch_step(wv_server *s, int sk, bool *launched) {
                                   as<uint64_t>(ss.gprimes)));
         for (const GridBatch &b : batches) {
             const uint32_t g0 = gspans[b.begin].q0;
-            WV_TRY(grid_enqueue(c, ss.grid, st, b.g, as<uint64_t>(ss.gprimes) + g0, b.n, b.hi,
+            WV_TRY(grid_enqueue(c, ss.grid, st, b.g, as<uint64_t>(ss.gprimes) + g0, b.n, b.lo, b.hi,
                                 (unsigned long long *)(scal + kStepGridTerms), as<wv_result>(ss.gres) + g0));
         }
     }

@@ -67,3 +67,17 @@ def test_server_lists_of_spread_primes(ctxs, step_terms):
     for ps, i in zip(lists, ids):
         print(f"case: server list of {len(ps)} primes from {min(ps)} to {max(ps)}", flush=True)
         assert np.array_equal(got[i], terms.eval_primes(ps))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ps", SPREAD + [near(113 * 10 ** 7, 2) + near(44 * 10 ** 8, 2) + near(5 * 10 ** 10, 20),
+                                         near(10 ** 6, 3) + near(9 * 2 ** 23 - 50, 8) + near(3 * 10 ** 9, 40)])
+def test_lists_of_spread_primes(ctxs, ps):
+    """One call for the whole list, as it stands and shuffled, with a repeat; among them
+    one of a class that serves two ranges of sizes beside a longer one's primes."""
+    c, terms = ctxs
+    print(f"case: list of {len(ps)} primes from {min(ps)} to {max(ps)}", flush=True)
+    for seed in (0, 1):
+        ps = ps + ps[:1]
+        assert np.array_equal(c.eval_primes(ps), terms.eval_primes(ps))
+        ps = random.Random(seed).sample(ps, len(ps))
