@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <vector>
 
+#include "direct_plan.hpp"
 #include "grid_plan.hpp"
 #include "wv_internal.hpp"
 #include "wv_tables.hpp"
@@ -241,29 +242,7 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
 // twiddle tables of transforms of length 2^logl (wv_grid.hip), uploaded once
 int ntt_tables(wv_ctx *c, int logl);
 
-// The direct path (wv_direct.hip): batches of little work, contexts as for the
-// grid path.  Measured on MI355X, ms a call, term sums (or grid path) / direct:
-//   n primes below 2^27, by their terms in all: 4e6 x 4096 (1.4e9 terms) 0.95 /
-//   0.80, 1e7 x 1024 (0.9e9) 0.70 / 0.46, x 4096 (3.6e9) 1.43 / 1.76, 2e7 x 1024
-//   (1.8e9) 0.86 / 0.80, 4e7 x 256 (0.9e9) 0.66 / 0.53, 8e7 x 256 (1.8e9) 0.88 /
-//   0.96, one prime at 1e8 0.53 / 0.08;
-//   every batch of small primes, whose (prime, sum) records cost more than the
-//   terms: 1e6 x 20000 1.97 / 1.01, 4e6 x 20000 2.83 / 2.83;
-//   from 2^27 on, where a product is six operations: 1.4e8 x 64 (0.8e9) 0.58 / 0.53,
-//   3e8 x 16 (0.4e9) 0.40 / 0.31, x 64 (1.7e9) 0.52 / 0.91, one prime at 3e9 (0.26e9)
-//   0.39 / 0.22, at 1e10 (0.9e9) 0.50 / 0.54.
-constexpr uint64_t kDirectSmallP = 1ull << 27;   // products exact in double precision below
-constexpr uint64_t kDirectAllP = 3ull << 20;
-constexpr double kDirectSmallTerms = 1.6e9, kDirectTerms = 5e8;
-// Lanes the primes of a batch share, and the least terms for one: 2^20 are 16
-// waves for each SIMD, rounds enough to even out the ends (2e7 x 1024: 0.80 ms,
-// with 2^19 0.98 ms).
-constexpr double kDirectLanes = 1048576.0, kDirectLaneTerms = 48.0;
-struct DirectShape {
-    bool small;              // p < kDirectSmallP
-    uint32_t G, threads;     // workgroups per prime and their threads
-    uint64_t key() const { return (uint64_t)G << 32 | threads << 1 | (small ? 1 : 0); }
-};
+// The direct path (wv_direct.hip, direct_plan.hpp).
 // whether a batch of n primes <= pmax goes this way
 bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, DirectShape *d);
 int direct_reserve(wv_ctx *c, uint32_t n, const DirectShape &d);
@@ -271,7 +250,6 @@ int direct_enqueue(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, ui
 int direct_batch_sync(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, uint32_t n, wv_result *d_out);
 // where only the device knows the primes: the choice, then (after the term sums of
 // the primes it left them) the run
-constexpr uint64_t kDirectParts = 1 << 14;   // fractions held
 struct DirectScratch {
     uint64_t *gated;     // n primes for the term sums
     double *part;        // 4 kDirectParts

@@ -29,7 +29,6 @@ namespace wv {
 namespace {
 
 constexpr int kDirectSums = 64;    // sums per side a workgroup stages
-constexpr int kDirectWaves = 4;
 
 // Arithmetic mod p: SMALL (p < 2^27): every product below is an integer below
 // 2^53, reduced to within p/2 (1 + 2^-24); else f_mulmod.
@@ -364,19 +363,7 @@ __global__ void __launch_bounds__(1024) k_direct_total(const uint64_t *__restric
 }  // namespace
 
 bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, DirectShape *d) {
-    if (n == 0 || !grid_allowed(c, c->tb, c->te)) return false;
-    const double per = (double)pmax * (side_cost(c, c->tb) + side_cost(c, c->te)), work = per * (double)n;
-    d->small = pmax <= kDirectSmallP;
-    if (!(d->small ? pmax <= kDirectAllP || work <= kDirectSmallTerms : work <= kDirectTerms)) return false;
-    // lanes per prime: the chip's, no more than leave a lane four groups
-    double lanes = std::min(kDirectLanes / (double)n, per / kDirectLaneTerms);
-    uint32_t w = 64;
-    while (2.0 * w <= lanes && w < 64 * kDirectWaves) w *= 2;
-    uint32_t G = 1;
-    while (2.0 * G * w <= lanes && G < 1024) G *= 2;
-    d->threads = w;
-    d->G = G;
-    return true;
+    return grid_allowed(c, c->tb, c->te) && direct_shape(n, pmax, side_cost(c, c->tb) + side_cost(c, c->te), d);
 }
 
 int direct_reserve(wv_ctx *c, uint32_t n, const DirectShape &d) {
@@ -393,9 +380,14 @@ int direct_enqueue(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, ui
     hipStream_t st = c->stream;
     if (d.G > 1)
         hipLaunchKernelGGL(k_direct_zero, dim3((n + 255) / 256), dim3(256), 0, st, as<uint32_t>(c->direct_ticket), n);
-    hipLaunchKernelGGL(d.small ? k_direct<true> : k_direct<false>, dim3(n * d.G), dim3(d.threads), 0, st, table_store(c),
-                       d_primes, c->tb, c->te, table_fallback(c, c->tb), table_fallback(c, c->te), d.G,
-                       as<double>(c->direct_part), as<uint32_t>(c->direct_ticket), as<uint64_t>(c->direct_terms), d_out);
+    const uint32_t most = direct_launch_primes(d);
+    for (uint64_t i = 0; i < n; i += most) {
+        const uint32_t k = (uint32_t)std::min<uint64_t>(most, n - i);
+        hipLaunchKernelGGL(d.small ? k_direct<true> : k_direct<false>, dim3(k * d.G), dim3(d.threads), 0, st,
+                           table_store(c), d_primes + i, c->tb, c->te, table_fallback(c, c->tb),
+                           table_fallback(c, c->te), d.G, as<double>(c->direct_part) + 4 * i * d.G,
+                           as<uint32_t>(c->direct_ticket) + i, as<uint64_t>(c->direct_terms) + 2 * i, d_out + i);
+    }
     hipLaunchKernelGGL(k_direct_total, dim3(1), dim3(1024), 0, st, as<uint64_t>(c->direct_terms), n,
                        as<uint64_t>(c->scal));
     WV_HIP(hipGetLastError());
