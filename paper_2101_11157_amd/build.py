@@ -10,7 +10,7 @@ PEAK_SRC = os.path.join(HERE, "csrc", "peak.hip")
 PEAK_LIB = os.path.join(HERE, "libwvpeak.so")
 DEPS = [os.path.join(HERE, "csrc", f) for f in ("mont.hpp", "sum_core.hpp", "wv_tables.hpp", "wv_internal.hpp",
                                                 "wv_ctx.hpp", "wave_ops.hpp", "ntt.hpp", "grid_plan.hpp",
-                                                "direct_plan.hpp", "step_share.hpp")] + [
+                                                "direct_plan.hpp", "list_plan.hpp", "step_share.hpp")] + [
     os.path.join(ROOT, "include", "wvprime.h")]
 LIB = os.path.join(HERE, "libwvprime.so")
 ARCH = os.environ.get("WV_OFFLOAD_ARCH", "gfx950")

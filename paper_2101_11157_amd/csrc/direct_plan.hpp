@@ -25,6 +25,11 @@ constexpr double kDirectSmallTerms = 1.6e9, kDirectTerms = 5e8;
 // waves for each SIMD, rounds enough to even out the ends (2e7 x 1024: 0.80 ms,
 // with 2^19 0.98 ms).
 constexpr double kDirectLanes = 1048576.0, kDirectLaneTerms = 48.0;
+// Every prime of a batch gets as many lanes, so the largest of a list of mixed
+// sizes ends last: terms a lane at most, n primes like the largest at kDirectLanes.
+// A lane takes 40 ns a term, 80 where the sums are short: 500 primes near 1e5 and
+// one near 4e9 (171,000 a lane) 6.5 ms, by term sums 0.58.
+constexpr double kDirectLaneMost = 2048.0;
 struct DirectShape {
     bool small;              // p < kDirectSmallP
     uint32_t G, threads;     // workgroups per prime and their threads
@@ -32,13 +37,15 @@ struct DirectShape {
 };
 constexpr uint64_t kDirectParts = 1 << 14;   // fractions held where only the device knows the primes
 
-// Whether a batch of n primes <= pmax, whose congruences hold cost p terms a
-// prime, goes this way.
-inline bool direct_shape(uint64_t n, uint64_t pmax, double cost, DirectShape *d) {
+// Whether a batch of n primes <= pmax, sum in all, whose congruences hold cost p
+// terms a prime, goes this way.
+inline bool direct_shape(uint64_t n, uint64_t pmax, double sum, double cost, DirectShape *d) {
     if (n == 0) return false;
-    const double per = (double)pmax * cost, work = per * (double)n;
+    const double per = (double)pmax * cost;
     d->small = pmax <= kDirectSmallP;
-    if (!(d->small ? pmax <= kDirectAllP || work <= kDirectSmallTerms : work <= kDirectTerms)) return false;
+    if (!(pmax <= kDirectAllP || (sum * cost <= (d->small ? kDirectSmallTerms : kDirectTerms) &&
+                                  per * (double)n <= kDirectLaneMost * kDirectLanes)))
+        return false;
     // lanes per prime: the chip's, and kDirectLaneTerms (about twelve groups of four) for each at least
     const double lanes = std::min(kDirectLanes / (double)n, per / kDirectLaneTerms);
     uint32_t w = 64;

@@ -183,23 +183,24 @@ inline const GridClass &grid_class(uint64_t p) {
 // the lengths from 2^12 to the batch's own, measured with the class of many primes
 // / this choice: 2 primes at 5e9 482 / 380, 1 at 2e10 488 / 403, 1 at 5e10 508 /
 // 467, 32 at 5e9 650 / 580, 7 at 1e11 1280 / 1030 (a split length's own).
-inline GridClass grid_batch_class(const GridClass &own, uint64_t n, uint64_t pmax) {
-    constexpr int kLow = 12;
+constexpr int kGridFewLog = 12;     // the shortest length measured
+constexpr uint64_t kGridFew = 256;  // primes at most
+inline double grid_few_us(const GridClass &c, uint64_t n, double p) {
     static constexpr double chain[] = {330, 330, 400, 530}, round[] = {100, 112, 128, 360};
     static constexpr double resident[] = {1024, 512, 256, 256};
-    static_assert(kLow + 3 == kGridMaxLog, "an entry per length");
-    if (own.logl <= kLow || n > 256) return own;
-    auto time = [&](const GridClass &c) {
-        const int k = c.logl - kLow;
-        const double r = (double)n / resident[k] *
-                         (grid_shifts_est(c.tb, (double)pmax, c.logl) + grid_shifts_est(c.te, (double)pmax, c.logl));
-        return chain[k] + round[k] * 0.5 * (r + std::ceil(r));
-    };
+    static_assert(kGridFewLog + 3 == kGridMaxLog, "an entry per length");
+    const int k = c.logl - kGridFewLog;
+    const double r = (double)n / resident[k] * (grid_shifts_est(c.tb, p, c.logl) + grid_shifts_est(c.te, p, c.logl));
+    return chain[k] + round[k] * 0.5 * (r + std::ceil(r));
+}
+
+inline GridClass grid_batch_class(const GridClass &own, uint64_t n, uint64_t pmax) {
+    if (own.logl <= kGridFewLog || n > kGridFew) return own;
     GridClass best = own;
-    double best_t = time(own);
-    for (int l = own.logl - 1; l >= kLow; l--) {
+    double best_t = grid_few_us(own, n, (double)pmax);
+    for (int l = own.logl - 1; l >= kGridFewLog; l--) {
         const GridClass c = grid_at_length(pmax, l);
-        const double v = time(c);
+        const double v = grid_few_us(c, n, (double)pmax);
         if (v < best_t) best_t = v, best = c;
     }
     return best;

@@ -460,7 +460,7 @@ int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector
             pmax = std::max(pmax, std::min(descs[k].hi, descs[k].L + kSegSpan));
         }
         DirectShape ds;
-        if (direct_takes(c, got, pmax, &ds))
+        if (direct_takes(c, got, pmax, (double)got * (double)pmax, &ds))
             WV_TRY(direct_batch_sync(c, ds, as<uint64_t>(c->primes), (uint32_t)got, as<wv_result>(c->results)));
         else if (grid)
             WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes), (uint32_t)got, pmin, pmax, as<wv_result>(c->results)));
@@ -703,7 +703,7 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
     const uint64_t n_pad = (n_bound + 1023) & ~1023ull;
     BatchShape sh{};
     DirectShape ds;
-    const bool direct = direct_takes(c, n_est, pmax, &ds);
+    const bool direct = direct_takes(c, n_est, pmax, (double)n_est * (double)pmax, &ds);
     if (direct) {
         WV_TRY(direct_reserve(c, (uint32_t)n_pad, ds));
     } else {
@@ -1055,7 +1055,7 @@ int wv_search_windows(wv_ctx *c, const uint64_t *lo, const uint64_t *hi, size_t 
         const uint64_t est = std::min<uint64_t>(bound, 16 + (uint64_t)(1.1 * (double)(hi[0] - lo[0]) / std::log(mid)));
         DirectShape ds;
         if (bound <= cap && bound <= kMaxBatchPrimes && work <= kGraphSearchTerms &&
-            (!desc_grid(c, d[0], &gc) || direct_takes(c, est, pmax + 1, &ds))) {
+            (!desc_grid(c, d[0], &gc) || direct_takes(c, est, pmax + 1, (double)est * (double)pmax, &ds))) {
             c->stats = wv_stats{};
             pick_tuned(c, pmax);
             size_t n = 0;
@@ -1168,10 +1168,12 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
     if (!primes || !out) return WV_EINVAL;
     if (n > 0xFFFFFFFFull) return WV_EINVAL;
     uint64_t pmax = 0;
+    double sum = 0;
     for (size_t i = 0; i < n; i++) {
         if (primes[i] < 5 || primes[i] >= WV_P_MAX) return WV_EDOMAIN;
         if (!is_prime_u64(primes[i])) return WV_ENOTPRIME;
         pmax = std::max(pmax, primes[i]);
+        sum += (double)primes[i];
     }
     WV_TRY(check_device(c));
     c->stats = wv_stats{};
@@ -1180,12 +1182,14 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
     WV_TRY(ensure(c, c->results, n * sizeof(wv_result)));
     WV_HIP(hipMemcpyAsync(c->primes.ptr, primes, n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
     DirectShape ds;
-    if (direct_takes(c, n, pmax, &ds)) {
+    if (direct_takes(c, n, pmax, sum, &ds)) {
         WV_TRY(direct_batch_sync(c, ds, as<uint64_t>(c->primes), (uint32_t)n, as<wv_result>(c->results)));
         return results_to_host(c, as<wv_result>(c->results), n, out);
     }
-    // ascending: the primes of the grid path in its batches, those below its start
-    // by term sums; results go back to input order
+    const uint64_t per = (uint64_t)side_slots(c, c->tb) + side_slots(c, c->te);
+    const size_t step = (size_t)std::max<uint64_t>(1, kMaxBatchSlots / per);
+    // primes of the grid path: the list ascending, in parts; results go back to
+    // input order
     GridClass gc;
     if (grid_takes(c, pmax, &gc)) {
         std::vector<std::pair<uint64_t, size_t>> ord(n);
@@ -1193,29 +1197,27 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
         std::sort(ord.begin(), ord.end());
         std::vector<uint64_t> sorted(n);
         for (size_t i = 0; i < n; i++) sorted[i] = ord[i].first;
-        WV_HIP(hipMemcpyAsync(c->primes.ptr, sorted.data(), n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
-        const size_t low = std::lower_bound(sorted.begin(), sorted.end(), kGridMinP) - sorted.begin();
-        std::vector<GridItem> items;
-        grid_items(sorted.data() + low, n - low, (uint32_t)low, items);
-        for (const GridBatch &b : grid_batches(items)) {
-            const size_t at = items[b.end - 1].at;   // descending, so this is the batch's first prime
-            WV_TRY(grid_batch_sync(c, b.g, as<uint64_t>(c->primes) + at, b.n, b.lo, b.hi, as<wv_result>(c->results) + at));
+        const std::vector<ListPart> parts = list_parts(sorted.data(), n, kGridMinP, side_cost(c, c->tb) + side_cost(c, c->te));
+        if (!parts.empty()) {
+            uint64_t *dp = as<uint64_t>(c->primes);
+            wv_result *dr = as<wv_result>(c->results);
+            WV_HIP(hipMemcpyAsync(dp, sorted.data(), n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
+            for (const ListPart &t : parts) {
+                if (t.path == kListDirect) WV_TRY(direct_batch_sync(c, t.d, dp + t.at, t.n, dr + t.at));
+                else if (t.path == kListGrid) WV_TRY(grid_batch_sync(c, t.g, dp + t.at, t.n, t.lo, t.hi, dr + t.at));
+                else
+                    for (size_t b = t.at; b < t.at + t.n; b += step) {
+                        const size_t k = std::min(step, t.at + t.n - b);
+                        WV_TRY(run_batch_sync(c, dp + b, (uint32_t)k, sorted[b + k - 1] + 1, dr + b));
+                    }
+            }
+            std::vector<wv_result> res(n);
+            WV_TRY(results_to_host(c, dr, n, res.data()));
+            for (size_t i = 0; i < n; i++) out[ord[i].second] = res[i];
+            return WV_OK;
         }
-        const uint64_t per = (uint64_t)side_slots(c, c->tb) + side_slots(c, c->te);
-        const size_t step = (size_t)std::max<uint64_t>(1, kMaxBatchSlots / per);
-        for (size_t b = 0; b < low; b += step) {
-            const size_t k = std::min(step, low - b);
-            WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes) + b, (uint32_t)k, sorted[b + k - 1] + 1,
-                                  as<wv_result>(c->results) + b));
-        }
-        std::vector<wv_result> res(n);
-        WV_TRY(results_to_host(c, as<wv_result>(c->results), n, res.data()));
-        for (size_t i = 0; i < n; i++) out[ord[i].second] = res[i];
-        return WV_OK;
     }
     // batches of at most kMaxBatchSlots (prime, sum) slots, in input order
-    const uint64_t per = (uint64_t)side_slots(c, c->tb) + side_slots(c, c->te);
-    const size_t step = (size_t)std::max<uint64_t>(1, kMaxBatchSlots / per);
     for (size_t b = 0; b < n; b += step) {
         const size_t k = std::min(step, n - b);
         WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes) + b, (uint32_t)k, pmax + 1, as<wv_result>(c->results) + b));

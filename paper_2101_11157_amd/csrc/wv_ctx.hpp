@@ -9,8 +9,7 @@
 #include <cstdlib>
 #include <vector>
 
-#include "direct_plan.hpp"
-#include "grid_plan.hpp"
+#include "list_plan.hpp"
 #include "wv_internal.hpp"
 #include "wv_tables.hpp"
 #include "wvprime.h"
@@ -243,8 +242,8 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
 int ntt_tables(wv_ctx *c, int logl);
 
 // The direct path (wv_direct.hip, direct_plan.hpp).
-// whether a batch of n primes <= pmax goes this way
-bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, DirectShape *d);
+// whether a batch of n primes <= pmax, sum in all, goes this way
+bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, double sum, DirectShape *d);
 int direct_reserve(wv_ctx *c, uint32_t n, const DirectShape &d);
 int direct_enqueue(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, uint32_t n, wv_result *d_out);
 int direct_batch_sync(wv_ctx *c, const DirectShape &d, const uint64_t *d_primes, uint32_t n, wv_result *d_out);

@@ -362,8 +362,8 @@ __global__ void __launch_bounds__(1024) k_direct_total(const uint64_t *__restric
 
 }  // namespace
 
-bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, DirectShape *d) {
-    return grid_allowed(c, c->tb, c->te) && direct_shape(n, pmax, side_cost(c, c->tb) + side_cost(c, c->te), d);
+bool direct_takes(const wv_ctx *c, uint64_t n, uint64_t pmax, double sum, DirectShape *d) {
+    return grid_allowed(c, c->tb, c->te) && direct_shape(n, pmax, sum, side_cost(c, c->tb) + side_cost(c, c->te), d);
 }
 
 int direct_reserve(wv_ctx *c, uint32_t n, const DirectShape &d) {

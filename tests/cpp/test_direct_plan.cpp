@@ -21,7 +21,7 @@ int main() {
         for (double q = 2.4; q <= 36.0; q += 0.2) {
             const uint64_t n = std::min<uint64_t>((uint64_t)std::exp2(e), 0xFFFFFFFFull), pmax = (uint64_t)std::exp2(q);
             DirectShape d;
-            if (!direct_shape(n, pmax, 0.0878, &d)) continue;
+            if (!direct_shape(n, pmax, (double)n * (double)pmax, 0.0878, &d)) continue;
             taken++;
             CHECK(d.G >= 1 && d.G <= 1024 && d.threads >= 64 && d.threads <= 64 * kDirectWaves);
             CHECK(d.small == (pmax <= kDirectSmallP));

@@ -1,4 +1,5 @@
-"""Little work: the direct path's rule on the CPU, its longest lists on the GPU."""
+"""Little work and lists of mixed sizes: the rules on the CPU, lists on the GPU
+against a context held to the term sums."""
 import os
 import subprocess
 
@@ -7,15 +8,17 @@ import pytest
 
 import oracle
 import paper_2101_11157_amd as wv
+from paper_2101_11157_amd.workloads import next_prime
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_rule_on_host(tmp_path):
-    exe = tmp_path / "test_direct_plan"
+@pytest.mark.parametrize("name", ["test_direct_plan", "test_list_plan"])
+def test_rules_on_host(tmp_path, name):
+    exe = tmp_path / name
     subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
                     os.path.join(ROOT, "paper_2101_11157_amd", "csrc"), "-o", str(exe),
-                    os.path.join(ROOT, "tests", "cpp", "test_direct_plan.cpp")], check=True)
+                    os.path.join(ROOT, "tests", "cpp", name + ".cpp")], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
 
@@ -34,3 +37,32 @@ def test_list_longer_than_a_launch():
     whole = n // len(few) * len(few)
     assert bool((got[:whole].reshape(-1, len(few)) == want).all())
     assert np.array_equal(got[whole:], want[:n - whole])
+
+
+def near(lo, n):
+    out, x = [], lo
+    while len(out) < n:
+        x = next_prime(x)
+        out.append(x)
+        x += 1
+    return out
+
+
+# the paths a list takes by chunk_terms of its last part: a grid block, 4 (direct), or a chunk of term sums
+MIXED = [("grid, little work below it", near(10 ** 4, 100) + near(2 * 10 ** 10, 2), 4),
+         ("grid, term sums below it", near(5 * 10 ** 7, 3000) + near(10 ** 9, 30), None),
+         ("direct, of sizes 1e5 to 2e9", near(10 ** 5, 5) + near(10 ** 7, 3) + near(2 * 10 ** 9, 1), 4),
+         ("term sums: a chain each would be longer", near(15 * 10 ** 7, 60) + near(7 * 10 ** 9, 1), None)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what, ps, chunk", MIXED, ids=[m[0] for m in MIXED])
+def test_lists_of_mixed_sizes(what, ps, chunk):
+    print(f"case: {what}", flush=True)
+    ps = ps[1::2] + ps[::2]
+    with wv.Context(0) as c, wv.Context(0) as terms:
+        terms.set_block(28, 36)
+        got = c.eval_primes(ps)
+        s = c.stats()
+        assert s["n_primes"] == len(ps) and (s["chunk_terms"] == chunk if chunk else s["n_chunks"] > 0)
+        assert np.array_equal(got, terms.eval_primes(ps))
