@@ -4,6 +4,8 @@
 #include <algorithm>
 #include <cstdint>
 
+#include "mont.hpp"
+
 namespace wv {
 
 // The direct path (wv_direct.hip): batches of little work, contexts as for the
@@ -38,16 +40,24 @@ struct DirectShape {
 constexpr uint64_t kDirectParts = 1 << 14;   // fractions held where only the device knows the primes
 
 // Whether a batch of n primes <= pmax, sum in all, whose congruences hold cost p
-// terms a prime, goes this way.
+// terms a prime, goes this way; the host's rule and the device's.
+__host__ __device__ inline bool direct_rule(double n, uint64_t pmax, double sum, double cost) {
+    return pmax <= kDirectAllP || (sum * cost <= (pmax <= kDirectSmallP ? kDirectSmallTerms : kDirectTerms) &&
+                                   (double)pmax * cost * n <= kDirectLaneMost * kDirectLanes);
+}
+
+// Lanes of each prime: the chip's, and kDirectLaneTerms (about twelve groups of
+// four) for each at least.
+__host__ __device__ inline double direct_lanes(double n, uint64_t pmax, double cost) {
+    const double share = kDirectLanes / n, own = (double)pmax * cost / kDirectLaneTerms;
+    return share < own ? share : own;
+}
+
 inline bool direct_shape(uint64_t n, uint64_t pmax, double sum, double cost, DirectShape *d) {
     if (n == 0) return false;
-    const double per = (double)pmax * cost;
     d->small = pmax <= kDirectSmallP;
-    if (!(pmax <= kDirectAllP || (sum * cost <= (d->small ? kDirectSmallTerms : kDirectTerms) &&
-                                  per * (double)n <= kDirectLaneMost * kDirectLanes)))
-        return false;
-    // lanes per prime: the chip's, and kDirectLaneTerms (about twelve groups of four) for each at least
-    const double lanes = std::min(kDirectLanes / (double)n, per / kDirectLaneTerms);
+    if (!direct_rule((double)n, pmax, sum, cost)) return false;
+    const double lanes = direct_lanes((double)n, pmax, cost);
     uint32_t w = 64;
     while (2.0 * w <= lanes && w < 64 * kDirectWaves) w *= 2;
     uint32_t G = 1;

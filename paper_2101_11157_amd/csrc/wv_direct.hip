@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(64 * kDirectWaves) k_direct_device(TableStore 
 }
 
 // One workgroup: the batch's terms and largest prime, the choice of the path by
-// the rule of direct_takes, the primes for the term sums (all 0, which the
+// direct_rule, the primes for the term sums (all 0, which the
 // plan rejects, if they go the other way), cleared scalars and tickets.
 __global__ void __launch_bounds__(1024) k_direct_pick(const uint64_t *__restrict__ primes, uint32_t n, double cost,
                                                       uint32_t threads, uint64_t *__restrict__ gated,
@@ -316,16 +316,14 @@ __global__ void __launch_bounds__(1024) k_direct_pick(const uint64_t *__restrict
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 16; w++) s += sum[w], m = max(m, top[w]);
-        const bool small = m < kDirectSmallP;
-        const double work = s * cost;
         uint32_t G = 0;
-        if (small ? m < kDirectAllP || work <= kDirectSmallTerms : work <= kDirectTerms) {
-            const double lanes = min(kDirectLanes / n, work / n / kDirectLaneTerms);
+        if (direct_rule(n, m, s, cost)) {
+            const double lanes = direct_lanes(n, m, cost);
             for (G = 1; 2.0 * G * threads <= lanes && 2 * G * (uint64_t)n <= kDirectParts; G *= 2) {}
         }
         pick = G;
         mode[0] = G;
-        mode[1] = small;
+        mode[1] = m <= kDirectSmallP;
     }
     __syncthreads();
     const bool sums = pick == 0;

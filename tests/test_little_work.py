@@ -5,6 +5,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch   # before the library: it loads its own HIP runtime first
 
 import oracle
 import paper_2101_11157_amd as wv
@@ -66,3 +67,34 @@ def test_lists_of_mixed_sizes(what, ps, chunk):
         s = c.stats()
         assert s["n_primes"] == len(ps) and (s["chunk_terms"] == chunk if chunk else s["n_chunks"] > 0)
         assert np.array_equal(got, terms.eval_primes(ps))
+
+
+# a list in device memory: one large prime among many small ones would leave its few lanes
+# with most of the work, so such lists stay with the term sums
+@pytest.mark.gpu
+@pytest.mark.parametrize("n, lo, m, hi", [(500, 10 ** 5, 1, 4 * 10 ** 9), (5000, 10 ** 4, 1, 10 ** 9), (8, 10 ** 5, 1, 2 * 10 ** 9),
+                                          (1, 7, 1, 5 * 10 ** 9), (300, 10 ** 6, 2, 5 * 10 ** 7), (99, 10 ** 4, 1, 2 * 10 ** 8)])
+def test_device_lists_of_mixed_sizes(n, lo, m, hi):
+    print(f"case: device list, {n} primes at {lo} and {m} at {hi}", flush=True)
+    ps = near(lo, n) + near(hi, m)
+    ps = ps[1::2] + ps[::2]
+    d = torch.tensor(ps, dtype=torch.int64, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    got, ms = [], []
+    with wv.Context(0) as c, wv.Context(0) as terms:
+        terms.set_block(28, 36)
+        for x in (c, terms):
+            o = torch.zeros((n + m, 4), dtype=torch.int64, device="cuda")
+            t = []
+            for _ in range(5):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                x.eval_primes_static(d.data_ptr(), n + m, o.data_ptr(), st)
+                b.record()
+                torch.cuda.synchronize()
+                t.append(a.elapsed_time(b))
+            got.append(o.cpu().numpy())
+            ms.append(min(t))
+    assert np.array_equal(got[0], got[1])
+    # (0.1 to 0.6 ms by term sums; 6.5 and 25 ms when the first two went direct)
+    assert ms[0] < 2.0 * ms[1]
