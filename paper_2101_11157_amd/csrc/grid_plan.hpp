@@ -223,10 +223,12 @@ inline bool grid_joins(uint64_t p, double n, const GridClass &g) {
     return own == g || (grid_ops(p, g) - own.ops) * n < kGridBatchS * kGridRate;
 }
 
-// n primes of [lo, hi], all of the path's sizes; at: where the caller has them.
+// n primes of [lo, hi], sum in all (or more), all of the path's sizes; at: where
+// the caller has them.
 struct GridItem {
     uint64_t lo, hi;
     uint32_t n, at;
+    double sum;
 };
 
 // Items [begin, end) of one batch: n primes of [lo, hi], evaluated in class g,
@@ -264,9 +266,10 @@ inline std::vector<GridBatch> grid_batches(std::vector<GridItem> &items) {
 inline void grid_items(const uint64_t *p, size_t n, uint32_t at, std::vector<GridItem> &out) {
     for (size_t i = 0; i < n;) {
         const GridClass &g = grid_class(p[i]);
-        size_t j = i + 1;
-        while (j < n && grid_class(p[j]) == g) j++;
-        out.push_back(GridItem{p[i], p[j - 1], (uint32_t)(j - i), at + (uint32_t)i});
+        size_t j = i;
+        double sum = 0;
+        while (j < n && grid_class(p[j]) == g) sum += (double)p[j++];
+        out.push_back(GridItem{p[i], p[j - 1], (uint32_t)(j - i), at + (uint32_t)i, sum});
         i = j;
     }
 }

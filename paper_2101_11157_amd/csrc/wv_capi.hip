@@ -329,7 +329,7 @@ int sieve_count(wv_ctx *c, const SegDesc *descs, size_t ns, bool keep_bits, uint
 
 // Primes of descs[0..ns) (bitmaps already in c->seg_bits) into c->primes.
 int compact(wv_ctx *c, const SegDesc *descs, size_t ns, const uint32_t *counts, uint64_t *np_out, hipStream_t st,
-            bool descs_ready) {
+            bool descs_ready, size_t at) {
     if (!st) st = c->stream;
     std::vector<uint64_t> offs(ns + 1, 0);
     for (size_t i = 0; i < ns; i++) offs[i + 1] = offs[i] + counts[i];
@@ -338,9 +338,9 @@ int compact(wv_ctx *c, const SegDesc *descs, size_t ns, const uint32_t *counts, 
     WV_TRY(ensure(c, c->seg_off, (ns + 1) * sizeof(uint64_t)));
     WV_TRY(ensure(c, c->primes, offs[ns] * sizeof(uint64_t)));
     if (!descs_ready)
-        WV_HIP(hipMemcpyAsync(c->seg_desc.ptr, descs, ns * sizeof(SegDesc), hipMemcpyHostToDevice, st));
+        WV_HIP(hipMemcpyAsync(as<SegDesc>(c->seg_desc) + at, descs, ns * sizeof(SegDesc), hipMemcpyHostToDevice, st));
     WV_HIP(hipMemcpyAsync(c->seg_off.ptr, offs.data(), (ns + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, st));
-    WV_HIP(launch_seg_compact(st, as<SegDesc>(c->seg_desc), (unsigned)ns, as<uint32_t>(c->seg_bits),
+    WV_HIP(launch_seg_compact(st, as<SegDesc>(c->seg_desc) + at, (unsigned)ns, as<uint32_t>(c->seg_bits) + at * kSegWords,
                               as<uint64_t>(c->seg_off), as<uint64_t>(c->primes), offs[ns]));
     return WV_OK;
 }
@@ -386,93 +386,91 @@ int words_to_host(wv_ctx *c, const uint64_t *d0, uint64_t *out0, const uint64_t 
     return WV_OK;
 }
 
-// Whether every prime of a segment goes through the grid path, and its class
-// (that of the largest).
-static bool desc_grid(const wv_ctx *c, const SegDesc &d, GridClass *g) {
-    return std::max(d.L, d.lo) >= kGridMinP && grid_takes(c, std::min(d.hi, d.L + kSegSpan) - 1, g);
+// The largest prime a segment can hold.
+static uint64_t desc_top(const SegDesc &d) { return std::min(d.hi, d.L + kSegSpan) - 1; }
+
+// Whether every prime of a segment goes through the grid path.
+static bool desc_grid(const wv_ctx *c, const SegDesc &d) {
+    GridClass g;
+    return std::max(d.L, d.lo) >= kGridMinP && grid_takes(c, desc_top(d), &g);
 }
 
-// All primes of the descriptor list (in order) and their residues into out.
+// Segments [i, j) as items (empty ones left out), at their places; ends that
+// overlapping windows put out of order are raised to the largest before them.
+static std::vector<GridItem> desc_items(const std::vector<SegDesc> &descs, const std::vector<uint32_t> &counts, size_t i,
+                                        size_t j) {
+    std::vector<GridItem> items;
+    uint64_t top = 0;
+    for (; i < j; i++) {
+        if (!counts[i]) continue;
+        top = std::max(top, desc_top(descs[i]));
+        items.push_back(GridItem{std::max(descs[i].L, descs[i].lo), top, counts[i], (uint32_t)i, (double)counts[i] * (double)top});
+    }
+    return items;
+}
+
+// Whether windows of little work in all (the time of their sums is that of a few
+// batches) go as one batch: direct, or by term sums where the parts, each with a
+// chain and waits of its own (about 60 us), would take longer together.
+static bool descs_whole(const wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector<uint32_t> &counts) {
+    if (descs.size() > kMaxBatchSegs || !grid_allowed(c, c->tb, c->te)) return false;
+    const double cost = side_cost(c, c->tb) + side_cost(c, c->te);
+    const std::vector<GridItem> items = desc_items(descs, counts, 0, descs.size());
+    double n = 0, sum = 0;
+    size_t low = 0;
+    for (const GridItem &t : items) {
+        n += t.n;
+        sum += t.sum;
+        if (!desc_grid(c, descs[t.at])) low++;   // ascending: the first ones
+    }
+    if (low == items.size() || n > (double)kMaxBatchPrimes || sum * cost > kGraphSearchTerms) return false;
+    DirectShape d;
+    if (direct_takes(c, (uint64_t)n, items.back().hi, sum, &d)) return true;
+    const ListPlan plan = plan_items(items, low, cost);
+    return plan.time + 6e-5 * (double)(plan.parts.size() - 1) > plan.sums;
+}
+
+// All primes of the descriptor list (ascending in L) and their residues into out.
 // Descriptors are grouped into batches of at most kMaxBatchSegs segments and
 // about kMaxBatchPrimes primes; each batch is one plan and one persistent
-// term-sum launch (or one split launch sequence under a progress callback).
+// term-sum launch (or one split launch sequence under a progress callback), or,
+// where the grid path takes all of it, that path's batches.
 int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector<uint32_t> &counts, wv_result *out,
                  StatsSink *sink, const uint64_t *dest, bool bits_ready) {
     std::vector<wv_result> staging;
     hipStream_t st = c->stream;
-    size_t i = 0, written = 0;
-    while (i < descs.size()) {
-        // a batch ends at kMaxBatchSegs segments, kMaxBatchPrimes primes or
-        // about kMaxBatchTerms terms (bounded by count * largest p * cost):
-        // with the partial pairs capped, a bigger batch would force chunks
-        // longer than its sums
-        // (slots per prime: those of the tables a batch up to its largest
-        // prime can pick; work: each piece at the cost of the table serving
-        // its top)
-        // Segments that the grid path takes form batches of their own, one
-        // class each (it bounds its own workspace).
-        GridClass gc, gj;
-        const bool grid = desc_grid(c, descs[i], &gc);
-        size_t j = i;
-        uint64_t np = 0, pm = 0;
-        double est = 0.0;
-        while (j < descs.size() && j - i < kMaxBatchSegs) {
-            const uint64_t top = std::min(descs[j].hi, descs[j].L + kSegSpan);
-            if (desc_grid(c, descs[j], &gj) != grid || (grid && !(gj == gc))) break;
-            if (grid) {
-                if (np > 0 && np + counts[j] > kMaxBatchPrimes) break;
-                np += counts[j++];
-                pm = std::max(pm, top);
-                continue;
-            }
-            const uint64_t pm_j = std::max(pm, top);
-            const uint64_t per = (uint64_t)side_slots(c, batch_table(c, c->tb, pm_j)) +
-                                 side_slots(c, batch_table(c, c->te, pm_j));
-            const uint64_t max_np = std::min<uint64_t>(kMaxBatchPrimes, kMaxBatchSlots / per);
-            const double e = (double)counts[j] * (double)top * (prime_cost(c, c->tb, top) + prime_cost(c, c->te, top));
-            if (np > 0 && (np + counts[j] > max_np || est + e > kMaxBatchTerms)) break;
-            np += counts[j++];
-            est += e;
-            pm = pm_j;
-        }
-        if (np == 0) {
-            i = j;
-            continue;
-        }
-        WV_HIP(hipEventRecord(c->ev[EV_START], st));
-        const bool whole = bits_ready && i == 0 && j == descs.size();
-        if (!whole) {
-            // the bitmaps of this batch's segments (the counting pass kept none)
-            std::vector<uint32_t> again(j - i);
-            WV_TRY(sieve_count(c, descs.data() + i, j - i, true, again.data()));
-            for (size_t k = 0; k < again.size(); k++)
-                if (again[k] != counts[i + k]) return WV_EHIP;   // the sieve is deterministic
-        }
-        uint64_t got = 0;
-        // the counting pass (or the re-sieve just above) left these
-        // descriptors in c->seg_desc when they fit one launch
-        WV_TRY(compact(c, descs.data() + i, j - i, counts.data() + i, &got, nullptr, j - i <= kSieveLaunch));
+    const double cost = side_cost(c, c->tb) + side_cost(c, c->te);
+    const bool whole = descs_whole(c, descs, counts);
+    // segments [a, b), their bitmaps from number `at` on: as the grid path's part, or
+    // (none) by the direct path where it takes them, else by term sums
+    auto run = [&](size_t a, size_t b, size_t at, const ListPart *part) -> int {
+        uint64_t got = 0, pmin = UINT64_MAX, pmax = 0;
+        double sum = 0;
+        WV_TRY(compact(c, descs.data() + a, b - a, counts.data() + a, &got, nullptr, b - a <= kSieveLaunch, at));
         WV_HIP(hipEventRecord(c->ev[EV_SIEVE], st));
         WV_TRY(ensure(c, c->results, got * sizeof(wv_result)));
-        uint64_t pmin = UINT64_MAX, pmax = 0;
-        for (size_t k = i; k < j; k++) {
+        for (size_t k = a; k < b; k++) {
+            if (!counts[k]) continue;
+            const uint64_t top = desc_top(descs[k]) + 1;
             pmin = std::min(pmin, std::max(descs[k].L, descs[k].lo));
-            pmax = std::max(pmax, std::min(descs[k].hi, descs[k].L + kSegSpan));
+            pmax = std::max(pmax, top);
+            sum += (double)counts[k] * (double)top;
         }
         DirectShape ds;
-        if (direct_takes(c, got, pmax, (double)got * (double)pmax, &ds))
-            WV_TRY(direct_batch_sync(c, ds, as<uint64_t>(c->primes), (uint32_t)got, as<wv_result>(c->results)));
-        else if (grid)
-            WV_TRY(grid_batch_sync(c, gc, as<uint64_t>(c->primes), (uint32_t)got, pmin, pmax, as<wv_result>(c->results)));
+        if (part && part->path == kListGrid)
+            WV_TRY(grid_batch_sync(c, part->g, as<uint64_t>(c->primes), (uint32_t)got, pmin, pmax,
+                                   as<wv_result>(c->results)));
+        else if (part || direct_takes(c, got, pmax, sum, &ds))
+            WV_TRY(direct_batch_sync(c, part ? part->d : ds, as<uint64_t>(c->primes), (uint32_t)got,
+                                     as<wv_result>(c->results)));
         else
             WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes), (uint32_t)got, pmax, as<wv_result>(c->results)));
         c->stats.ms_sieve += elapsed(c->ev[EV_START], c->ev[EV_SIEVE]);   // both recorded before its wait
-        if (out && !dest) WV_TRY(results_to_host(c, as<wv_result>(c->results), got, out + written));
-        if (out && dest) {
+        if (out) {
             staging.resize(got);
             WV_TRY(results_to_host(c, as<wv_result>(c->results), got, staging.data()));
             uint64_t o = 0;
-            for (size_t k = i; k < j; k++) {
+            for (size_t k = a; k < b; k++) {
                 std::memcpy(out + dest[k], staging.data() + o, counts[k] * sizeof(wv_result));
                 o += counts[k];
             }
@@ -496,7 +494,62 @@ int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector
                                       st));
         }
         WV_HIP(hipStreamSynchronize(st));
-        written += got;
+        WV_HIP(hipEventRecord(c->ev[EV_START], st));   // of the next part
+        return WV_OK;
+    };
+    size_t i = 0;
+    while (i < descs.size()) {
+        // a batch ends at kMaxBatchSegs segments, kMaxBatchPrimes primes or
+        // about kMaxBatchTerms terms (bounded by count * largest p * cost):
+        // with the partial pairs capped, a bigger batch would force chunks
+        // longer than its sums
+        // (slots per prime: those of the tables a batch up to its largest
+        // prime can pick; work: each piece at the cost of the table serving
+        // its top)
+        // Segments that the grid path takes form batches of their own (it
+        // bounds its own workspace).
+        const bool grid = !whole && desc_grid(c, descs[i]);
+        size_t j = i;
+        uint64_t np = 0, pm = 0;
+        double est = 0.0;
+        while (j < descs.size() && j - i < kMaxBatchSegs) {
+            const uint64_t top = desc_top(descs[j]) + 1;
+            if ((!whole && desc_grid(c, descs[j])) != grid) break;
+            if (grid) {
+                if (np > 0 && np + counts[j] > kMaxBatchPrimes) break;
+                np += counts[j++];
+                continue;
+            }
+            const uint64_t pm_j = std::max(pm, top);
+            const uint64_t per = (uint64_t)side_slots(c, batch_table(c, c->tb, pm_j)) +
+                                 side_slots(c, batch_table(c, c->te, pm_j));
+            const uint64_t max_np = std::min<uint64_t>(kMaxBatchPrimes, kMaxBatchSlots / per);
+            const double e = (double)counts[j] * (double)top * (prime_cost(c, c->tb, top) + prime_cost(c, c->te, top));
+            if (np > 0 && (np + counts[j] > max_np || est + e > kMaxBatchTerms)) break;
+            np += counts[j++];
+            est += e;
+            pm = pm_j;
+        }
+        if (np == 0) {
+            i = j;
+            continue;
+        }
+        WV_HIP(hipEventRecord(c->ev[EV_START], st));
+        if (!bits_ready) {
+            // the bitmaps of this batch's segments (the counting pass kept none)
+            std::vector<uint32_t> again(j - i);
+            WV_TRY(sieve_count(c, descs.data() + i, j - i, true, again.data()));
+            for (size_t k = 0; k < again.size(); k++)
+                if (again[k] != counts[i + k]) return WV_EHIP;   // the sieve is deterministic
+        }
+        const size_t first = bits_ready ? 0 : i;   // whose bitmap is number 0
+        if (grid) {
+            const std::vector<GridItem> items = desc_items(descs, counts, i, j);
+            for (const ListPart &t : plan_items(items, 0, cost).parts)
+                WV_TRY(run(items[t.begin].at, items[t.end - 1].at + 1, items[t.begin].at - first, &t));
+        } else {
+            WV_TRY(run(i, j, i - first, nullptr));
+        }
         i = j;
     }
     return WV_OK;
@@ -1045,7 +1098,6 @@ int wv_search_windows(wv_ctx *c, const uint64_t *lo, const uint64_t *hi, size_t 
     }
     first[nwin] = d.size();
     // a small single-window search: one graph, sized by the prime-count bound
-    GridClass gc;
     if (nwin == 1 && out && !d.empty() && d.size() <= kMaxBatchSegs && !c->progress) {
         const uint64_t bound = prime_count_bound(std::max<uint64_t>(lo[0], 5), hi[0]);
         const double work = (double)bound * (double)pmax * (side_cost(c, c->tb) + side_cost(c, c->te));
@@ -1055,7 +1107,7 @@ int wv_search_windows(wv_ctx *c, const uint64_t *lo, const uint64_t *hi, size_t 
         const uint64_t est = std::min<uint64_t>(bound, 16 + (uint64_t)(1.1 * (double)(hi[0] - lo[0]) / std::log(mid)));
         DirectShape ds;
         if (bound <= cap && bound <= kMaxBatchPrimes && work <= kGraphSearchTerms &&
-            (!desc_grid(c, d[0], &gc) || direct_takes(c, est, pmax + 1, (double)est * (double)pmax, &ds))) {
+            (!desc_grid(c, d[0]) || direct_takes(c, est, pmax + 1, (double)est * (double)pmax, &ds))) {
             c->stats = wv_stats{};
             pick_tuned(c, pmax);
             size_t n = 0;
@@ -1071,14 +1123,28 @@ int wv_search_windows(wv_ctx *c, const uint64_t *lo, const uint64_t *hi, size_t 
             }
         }
     }
-    std::vector<uint32_t> counts(d.size());
+    // Segments in ascending position, so that a batch holds primes of one size
+    // (chunk sizes then fit every sum of the batch); each one's primes go to its
+    // window's offset.
+    std::vector<size_t> ord(d.size());
+    for (size_t k = 0; k < ord.size(); k++) ord[k] = k;
+    std::stable_sort(ord.begin(), ord.end(), [&](size_t a, size_t b) { return d[a].L < d[b].L; });
+    std::vector<SegDesc> ds(d.size());
+    for (size_t k = 0; k < ord.size(); k++) ds[k] = d[ord[k]];
+    std::vector<uint32_t> cs(d.size());
     // a single batch's worth of segments keeps its bitmaps from this count
     const bool keep = d.size() <= kMaxBatchSegs;
-    if (!d.empty()) WV_TRY(sieve_count(c, d.data(), d.size(), keep, counts.data()));
+    if (!d.empty()) WV_TRY(sieve_count(c, ds.data(), ds.size(), keep, cs.data()));
+    std::vector<uint32_t> counts(d.size());
+    for (size_t k = 0; k < ord.size(); k++) counts[ord[k]] = cs[k];
+    std::vector<uint64_t> dest(d.size());
     uint64_t total = 0;
     for (size_t w = 0; w < nwin; w++) {
         if (win_off) win_off[w] = (size_t)total;
-        for (size_t k = first[w]; k < first[w + 1]; k++) total += counts[k];
+        for (size_t k = first[w]; k < first[w + 1]; k++) {
+            dest[k] = total;
+            total += counts[k];
+        }
     }
     if (win_off) win_off[nwin] = (size_t)total;
     *n_out = (size_t)total;
@@ -1087,29 +1153,9 @@ int wv_search_windows(wv_ctx *c, const uint64_t *lo, const uint64_t *hi, size_t 
     c->stats = wv_stats{};
     if (total == 0) return WV_OK;
     pick_tuned(c, pmax);
-    // Batch the segments in ascending position, so that a batch holds primes of
-    // one size (chunk sizes then fit every sum of the batch), and place each
-    // segment's primes at its window's offset.
-    std::vector<uint64_t> dest(d.size());
-    uint64_t o = 0;
-    for (size_t k = 0; k < d.size(); k++) {
-        dest[k] = o;
-        o += counts[k];
-    }
-    std::vector<size_t> ord(d.size());
-    for (size_t k = 0; k < ord.size(); k++) ord[k] = k;
-    std::stable_sort(ord.begin(), ord.end(), [&](size_t a, size_t b) { return d[a].L < d[b].L; });
-    std::vector<SegDesc> ds(d.size());
-    std::vector<uint32_t> cs(d.size());
     std::vector<uint64_t> dst(d.size());
-    bool same_order = true;
-    for (size_t k = 0; k < ord.size(); k++) {
-        ds[k] = d[ord[k]];
-        cs[k] = counts[ord[k]];
-        dst[k] = dest[ord[k]];
-        same_order &= ord[k] == k;
-    }
-    return search_descs(c, ds, cs, out, nullptr, dst.data(), keep && same_order);
+    for (size_t k = 0; k < ord.size(); k++) dst[k] = dest[ord[k]];
+    return search_descs(c, ds, cs, out, nullptr, dst.data(), keep);
 }
 
 int wv_range_stats(wv_ctx *c, uint64_t lo, uint64_t hi, uint32_t bins, uint64_t near_bound, uint64_t *hist_b,

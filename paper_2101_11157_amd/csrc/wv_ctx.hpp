@@ -210,13 +210,13 @@ uint64_t window_piece(const wv_ctx *c, uint64_t hi);
 // (compact leaves the compaction enqueued on st)
 int sieve_count(wv_ctx *c, const SegDesc *descs, size_t ns, bool keep_bits, uint32_t *counts,
                 hipStream_t st = nullptr);
-// descs_ready: c->seg_desc already holds descs[0..ns) (the sieve uploaded them)
+// descs_ready: c->seg_desc already holds descs[0..ns) (the sieve uploaded them);
+// at: where they and their bitmaps start
 int compact(wv_ctx *c, const SegDesc *descs, size_t ns, const uint32_t *counts, uint64_t *np_out,
-            hipStream_t st = nullptr, bool descs_ready = false);
-// out: host results (may be NULL when sink is set), written contiguously in
-// desc order, or, with dest, the primes of descs[k] at out + dest[k];
-// sink: device statistics; bits_ready: the counting pass kept the bitmaps of
-// every descriptor, in this order, in c->seg_bits
+            hipStream_t st = nullptr, bool descs_ready = false, size_t at = 0);
+// out: host results (may be NULL when sink is set), the primes of descs[k] at
+// out + dest[k]; sink: device statistics; bits_ready: the counting pass kept the
+// bitmaps of every descriptor, in this order, in c->seg_bits
 int search_descs(wv_ctx *c, const std::vector<SegDesc> &descs, const std::vector<uint32_t> &counts,
                  wv_result *out, StatsSink *sink = nullptr, const uint64_t *dest = nullptr, bool bits_ready = false);
 void pick_tuned(wv_ctx *c, uint64_t pmax);

@@ -392,7 +392,7 @@ int launch_step(wv_server *s, int sk, bool *launched) {
         if (!give[k]) continue;
         Request *r = cand[k];
         if (r->grid) {
-            if (r->is_range) gitems.push_back(GridItem{r->pmin, r->pmax, give[k], r->base + r->next});
+            if (r->is_range) gitems.push_back(GridItem{r->pmin, r->pmax, give[k], r->base + r->next, 0.0});
             else grid_items(r->primes.data() + r->next, give[k], r->base + r->next, gitems);
             continue;
         }

@@ -107,11 +107,11 @@ int main() {
         CHECK(items.empty());
         for (uint64_t x : p) {
             const uint64_t hi = std::min<uint64_t>(1ull << 40, x + (rnd() >> (38 + rnd() % 26)));
-            items.push_back(GridItem{x, hi, 1 + (uint32_t)(rnd() % 1000), 0});
+            items.push_back(GridItem{x, hi, 1 + (uint32_t)(rnd() % 1000), 0, 0.0});
         }
         check(items);
         // a range of any width
-        check({GridItem{p[0], std::max(p[0], p.back()), 5, 0}});
+        check({GridItem{p[0], std::max(p[0], p.back()), 5, 0, 0.0}});
     }
     if (fails) return printf("%d failed\n", fails), 1;
     printf("ok\n");

@@ -51,7 +51,35 @@ static std::vector<uint64_t> log_uniform(double a, double b, int n) {
     return p;
 }
 
+// windows: items of ranges in ascending order, the first `low` below the path's start
+static void check_windows(int n) {
+    std::vector<GridItem> items;
+    uint64_t at = (uint64_t)std::exp2(10.0 + (double)(rnd() % 200) / 10.0);
+    size_t low = 0;
+    for (int k = 0; k < n && at < (1ull << 39); k++) {
+        const uint64_t top = at + rnd() % (1 << 20);
+        const uint32_t m = 1 + (uint32_t)(rnd() % 2000);
+        if (at < kMinP) low++;
+        items.push_back(GridItem{at, top, m, (uint32_t)(2 * k), (double)m * (double)top});
+        at = top + (rnd() % 3 ? rnd() % (at / 2) : 0);
+    }
+    const ListPlan plan = plan_items(items, low, kCost);
+    size_t next = 0;
+    for (const ListPart &t : plan.parts) {
+        CHECK(t.begin == next && t.end > t.begin && t.at == items[t.begin].at);
+        CHECK(t.lo == items[t.begin].lo && t.hi == items[t.end - 1].hi);
+        uint32_t m = 0;
+        for (size_t i = t.begin; i < t.end; i++) m += items[i].n;
+        CHECK(m == t.n);
+        CHECK(t.begin >= low || (t.begin == 0 && t.end == low && t.path != kListGrid));
+        if (t.path == kListGrid) CHECK(grid_fits(t.lo, t.g.logl));
+        next = t.end;
+    }
+    CHECK(next == items.size());
+}
+
 int main() {
+    for (int k = 0; k < 2000; k++) check_windows(1 + (int)(rnd() % 64));
     for (int k = 0; k < 4000; k++) {
         const double a = 3.0 + (double)(rnd() % 300) / 10.0, b = std::max(a, 27.0) + (double)(rnd() % 120) / 10.0;
         check(log_uniform(a, std::min(b, 40.0), 1 + (int)(rnd() % (k % 4 ? 20 : 500))));

@@ -98,3 +98,31 @@ def test_device_lists_of_mixed_sizes(n, lo, m, hi):
     assert np.array_equal(got[0], got[1])
     # (0.1 to 0.6 ms by term sums; 6.5 and 25 ms when the first two went direct)
     assert ms[0] < 2.0 * ms[1]
+
+
+# windows that form several parts, that go as one batch, and that overlap, in any order
+WINDOWS = [[(10 ** 6, 400), (3 * 10 ** 7, 400), (8 * 10 ** 7, 400), (2 * 10 ** 8, 400), (10 ** 9, 400), (9 * 10 ** 9, 200)],
+           [(9 * 2 ** 23 - 300, 300), (9 * 2 ** 23, 300), (9 * 2 ** 23 - 100, 200)],
+           [(2 * 10 ** 9, 3000), (2 * 10 ** 9 + 1, 2999), (2 * 10 ** 9 + 1000, 50), (5, 100), (2 * 10 ** 9 - 64, 9000)],
+           [(10 ** 8 + 7 * 10 ** 6 * k, 1500) for k in range(12)] + [(10 ** 10, 30), (2 * 10 ** 7, 3000)],
+           [(24, 5), (10 ** 10, 40), (90, 7), (4 * 10 ** 9, 700), (113 * 10 ** 7, 700)]]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", range(len(WINDOWS)))
+def test_windows_of_mixed_sizes(k):
+    """Each window of a call, whatever parts its primes run in, is what the term sums give."""
+    los = [lo for lo, _ in WINDOWS[k]]
+    his = [lo + w for lo, w in WINDOWS[k]]
+    print(f"case: windows {WINDOWS[k]}", flush=True)
+    with wv.Context(0) as c, wv.Context(0) as terms:
+        terms.set_block(28, 36)
+        want = terms.search_windows(los, his)
+        for order in (list(range(len(los))), list(range(len(los)))[::-1], list(range(1, len(los), 2)) + list(range(0, len(los), 2))):
+            got = c.search_windows([los[i] for i in order], [his[i] for i in order])
+            for i, g in zip(order, got):
+                assert [int(p) for p in g["p"]] == oracle.primes(los[i], his[i])
+                assert np.array_equal(g, want[i])
+        lo, hi = min(los), max(his)
+        if hi - lo < 10 ** 5:
+            assert c.range_stats(lo, hi, bins=10, near=0)[3] == len(oracle.primes(lo, hi))
