@@ -71,4 +71,15 @@ inline bool direct_shape(uint64_t n, uint64_t pmax, double sum, double cost, Dir
 // list (of small primes, with repeats) may be longer.
 inline uint32_t direct_launch_primes(const DirectShape &d) { return (1u << 31) / (d.G * d.threads); }
 
+// Slots of a captured search of at most n_bound primes: every one has its
+// workgroups, G of them, whether it holds a prime or not, and 2^18 that hold none
+// take 0.25 ms.  Up to 1024 a power of two (few captures), then a multiple of 1024:
+// windows of 2 integers near 1e9, 1024 slots / these, 0.34 / 0.09 ms (term sums
+// 0.32), of 20 near 8e7 0.16 / 0.08.
+inline uint64_t direct_pad(uint64_t n_bound) {
+    uint64_t n = 16;
+    while (n < n_bound && n < 1024) n *= 2;
+    return n < n_bound ? (n_bound + 1023) & ~1023ull : n;
+}
+
 }  // namespace wv

@@ -744,8 +744,9 @@ uint64_t prime_count_bound(uint64_t lo, uint64_t hi) {
 
 // A single-batch search replayed from one captured graph: sieve -> segment
 // offsets -> compaction -> plan -> term sums -> reduce -> finalize, sized by
-// an upper bound on the prime count (rounded up to a multiple of 1024; the
-// padding slots hold 0, which the plan rejects and which cost no term work).
+// an upper bound on the prime count (rounded up to a multiple of 1024, or as
+// direct_pad has it; the padding slots hold 0, which the plan rejects and which
+// cost no term work).
 // The device counts the primes; the count, the batch's scalars and the
 // results come back after the call's one wait.  d: the segments (at most
 // kMaxBatchSegs), in ascending order, so the compacted primes ascend.
@@ -753,10 +754,10 @@ int search_graph(wv_ctx *c, const std::vector<SegDesc> &d, uint64_t n_bound, uin
                  size_t *n_out) {
     hipStream_t st = c->stream;
     const uint64_t ns = d.size();
-    const uint64_t n_pad = (n_bound + 1023) & ~1023ull;
     BatchShape sh{};
     DirectShape ds;
     const bool direct = direct_takes(c, n_est, pmax, (double)n_est * (double)pmax, &ds);
+    const uint64_t n_pad = direct ? direct_pad(n_bound) : (n_bound + 1023) & ~1023ull;
     if (direct) {
         WV_TRY(direct_reserve(c, (uint32_t)n_pad, ds));
     } else {

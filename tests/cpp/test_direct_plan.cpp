@@ -33,6 +33,13 @@ int main() {
             CHECK(held == n && (launches == 1 || n > most));
         }
     CHECK(taken > 1000);
+    // slots for every prime a narrow window may hold, and few without one
+    uint64_t last = 0;
+    for (uint64_t n = 0; n < 5000; n++) {
+        const uint64_t pad = direct_pad(n);
+        CHECK(pad >= n && pad >= last && pad <= std::max<uint64_t>(16, n <= 1024 ? 2 * n : n + 1023));
+        last = pad;
+    }
     if (fails) return printf("%d failed\n", fails), 1;
     printf("ok\n");
     return 0;

@@ -126,3 +126,22 @@ def test_windows_of_mixed_sizes(k):
         lo, hi = min(los), max(his)
         if hi - lo < 10 ** 5:
             assert c.range_stats(lo, hi, bins=10, near=0)[3] == len(oracle.primes(lo, hi))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lo, width", [(9 * 2 ** 23 + 1, 1), (3 * 10 ** 8, 2), (10 ** 9 + 6, 2), (10 ** 9, 20), (10 ** 8, 33),
+                                       (10 ** 9 + 1, 64), (10 ** 7, 300), (10 ** 6, 7000), (10 ** 6, 9000)])
+def test_narrow_windows(lo, width):
+    """One window with as many slots as it may hold primes, or 16: three captured
+    replays each, between other calls."""
+    print(f"case: direct, window [{lo}, {lo + width})", flush=True)
+    with wv.Context(0) as c, wv.Context(0) as terms:
+        terms.set_block(28, 36)
+        for a in (lo, lo + 12, lo + 2):
+            got, _ = c.search_range(a, a + width)
+            ps = oracle.primes(a, a + width)
+            assert [int(p) for p in got["p"]] == ps
+            if ps:
+                assert c.stats()["chunk_terms"] == 4 and c.stats()["n_primes"] == len(ps)
+                assert np.array_equal(got, terms.eval_primes(ps))
+            c.count_primes(5, 3000)
