@@ -650,7 +650,9 @@ WV_UNROLL
 // wanted) one Fermat inverse serves the lane's 2 R left sides, about 10 products
 // an index instead of 70 with its own powers and 130 with its own inverses.
 // Bound by the serial steps: 16 indices a lane take 48 us over the 390 primes of
-// a window near 2^15, 32 take 59 us (half the waves).
+// a window near 2^15, 32 take 59 us (half the waves).  The indices of one prime that
+// hardly fill the chip go one to a lane (with eight / with one: p = 5003 18 / 7 us,
+// 300007 22 / 15, 1000003 23 / 34).
 template <bool OUT, int R>
 __global__ void __launch_bounds__(256) k_irr_final(const IrrPrime *__restrict__ pr, const uint64_t *__restrict__ off,
                                                    uint32_t np, const double *__restrict__ V,
@@ -670,7 +672,13 @@ __global__ void __launch_bounds__(256) k_irr_final(const IrrPrime *__restrict__ 
         return a;
     };
     // steps of 64 in k
-    const double s2 = sq((double)((p + 1) / 2), 7), s3 = sq(3.0, 7), s3i = sq(f_pow_u(3.0, p - 2, f), 7), s16 = sq(16.0, 6);
+    double s2 = 0.0, s3 = 0.0, s3i = 0.0, s16 = 0.0;
+    if constexpr (R > 1) {
+        s2 = sq((double)((p + 1) / 2), 7);
+        s3 = sq(3.0, 7);
+        s3i = sq(f_pow_u(3.0, p - 2, f), 7);
+        s16 = sq(16.0, 6);
+    }
     double x = 0.0, y = 0.0, z = 0.0, p4 = 0.0;
     if (k1 <= P.nt) {
         x = fpow_e(2.0, p - 2 * k1, f);
@@ -709,10 +717,12 @@ __global__ void __launch_bounds__(256) k_irr_final(const IrrPrime *__restrict__ 
                 pe[r] = f_mulmod(p4, z, f);
             }
         }
-        x = f_mulmod(x, s2, f);
-        y = f_mulmod(y, s3i, f);
-        z = f_mulmod(z, s3, f);
-        if (OUT) p4 = f_mulmod(p4, s16, f);
+        if constexpr (R > 1) {
+            x = f_mulmod(x, s2, f);
+            y = f_mulmod(y, s3i, f);
+            z = f_mulmod(z, s3, f);
+            if (OUT) p4 = f_mulmod(p4, s16, f);
+        }
     }
     if constexpr (OUT) {
         double pre[2 * R], acc = 1.0;
@@ -766,6 +776,7 @@ constexpr uint64_t kIrrMaxB = 64;
 static_assert(kIrrMaxB - 4 < 64, "one candidate b per lane");
 constexpr int kFixThreads = 512;
 constexpr uint64_t kFixGrid = 1024;       // workgroups: the chip twice over
+constexpr uint64_t kIrrOneFin = 1u << 19; // one prime below: an index a lane in k_irr_final
 constexpr uint64_t kFixShared = kFixGrid / 2;   // queue lengths up to here are shared; a total and a ticket each
 constexpr uint64_t kFixMaxShare = 16;
 constexpr uint64_t kFixWords = 4 + 2 * kFixShared;   // the counters, totals and tickets
@@ -1004,19 +1015,21 @@ int irr_dft(wv_ctx *c, const std::vector<IrrPrime> &prs, std::vector<std::vector
     return WV_OK;
 }
 
-// One batch of primes (all in [5, WV_IRR_P_MAX)): residues into the device
-// arrays b_out / e_out (may be null) at each prime's res offset, zero pairs
-// appended to the device list.  Returns the counters {fixups, pairs, unresolved}.
-int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *d_b, uint64_t *d_e, uint64_t pair_cap,
+// One batch of primes (all in [5, WV_IRR_P_MAX)): with b and e (host arrays), the
+// residues of every index, prime by prime; else zero pairs appended to the device
+// list and the counters {fixups, pairs, unresolved}.
+int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *b, uint64_t *e, uint64_t pair_cap,
               uint64_t counts_out[3], float *ms_sum, double *pairs_done) {
     hipStream_t st = c->stream;
+    uint64_t *d_b = b ? as<uint64_t>(c->irr_b) : nullptr, *d_e = b ? as<uint64_t>(c->irr_e) : nullptr;
     std::vector<IrrTask> tasks;
     std::vector<uint64_t> units(1, 0);
     std::vector<IrrPrime> prs;
     std::vector<uint64_t> roff(1, 0);
     uint64_t vn = 0, res = 0;
     double work = 0.0;
-    const uint64_t kFin = d_b ? 8 : 16;   // indices per lane of k_irr_final
+    // indices per lane of k_irr_final
+    const uint64_t kFin = !d_b ? 16 : ps.size() == 1 && ps[0] < kIrrOneFin ? 1 : 8;
     // Path 0: transforms, but the matrix cores for a batch of so little work that the
     // launches count (p^2 summed over the batch; one prime near 3000 130 us by the
     // matrix cores, 139 by transforms, near 5000 both 140, near 8000 167 and 149).
@@ -1110,27 +1123,28 @@ int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *d_b, uint64_
     auto *counts = as<unsigned long long>(c->irr_counts);
     IrrFix *fix_b = as<IrrFix>(c->irr_fix), *fix_e = fix_b + std::max<uint64_t>(res, 1);
     const unsigned fgrid = grid_for(roff.back(), 4);
-    if (d_b)
-        hipLaunchKernelGGL((k_irr_final<true, 8>), dim3(fgrid), dim3(256), 0, st, as<IrrPrime>(c->irr_primes),
-                           as<uint64_t>(c->irr_roff), np, as<double>(c->irr_v), d_b, d_e, fix_b, fix_e, counts,
-                           as<wv_irr_pair>(c->irr_pairs), pair_cap);
-    else
-        hipLaunchKernelGGL((k_irr_final<false, 16>), dim3(fgrid), dim3(256), 0, st, as<IrrPrime>(c->irr_primes),
-                           as<uint64_t>(c->irr_roff), np, as<double>(c->irr_v), d_b, d_e, fix_b, fix_e, counts,
-                           as<wv_irr_pair>(c->irr_pairs), pair_cap);
+    hipLaunchKernelGGL((kFin == 16  ? k_irr_final<false, 16>
+                        : kFin == 8 ? k_irr_final<true, 8>
+                                    : k_irr_final<true, 1>),
+                       dim3(fgrid), dim3(256), 0, st, as<IrrPrime>(c->irr_primes), as<uint64_t>(c->irr_roff), np,
+                       as<double>(c->irr_v), d_b, d_e, fix_b, fix_e, counts, as<wv_irr_pair>(c->irr_pairs), pair_cap);
     WV_HIP(hipGetLastError());
     // the queues' lengths stay on the device: a fixed grid goes through them
     hipLaunchKernelGGL(k_irr_fix, dim3((unsigned)kFixGrid), dim3(kFixThreads), 0, st, as<IrrPrime>(c->irr_primes), fix_b,
                        fix_e, counts, d_b, d_e, as<wv_irr_pair>(c->irr_pairs), pair_cap);
     WV_HIP(hipGetLastError());
-    unsigned long long host[4];
-    WV_HIP(hipMemcpyAsync(host, counts, sizeof(host), hipMemcpyDeviceToHost, st));
-    WV_HIP(hipStreamSynchronize(st));
+    if (b) {
+        WV_TRY(words_to_host(c, d_b, b, d_e, e, res));   // waits
+    } else {
+        unsigned long long host[4];
+        WV_HIP(hipMemcpyAsync(host, counts, sizeof(host), hipMemcpyDeviceToHost, st));
+        WV_HIP(hipStreamSynchronize(st));
+        for (int q = 0; q < 3; q++) counts_out[q] = host[q];
+    }
     float ms = 0.f;
     (void)hipEventElapsedTime(&ms, c->ev[EV_SUM0], c->ev[EV_SUM]);
     *ms_sum += ms;
     *pairs_done += work;
-    for (int q = 0; q < 3; q++) counts_out[q] = host[q];
     return WV_OK;
 }
 
@@ -1178,12 +1192,9 @@ int wv_bernoulli_euler_all(wv_ctx *c, uint64_t p, uint64_t *b, uint64_t *e) {
     WV_TRY(ensure(c, c->irr_b, nt * sizeof(uint64_t)));
     WV_TRY(ensure(c, c->irr_e, nt * sizeof(uint64_t)));
     WV_TRY(ensure(c, c->irr_pairs, 64 * sizeof(wv_irr_pair)));
-    uint64_t counts[3];
     float ms = 0.f;
     double work = 0.0;
-    WV_TRY(irr_batch(c, std::vector<uint64_t>{p}, as<uint64_t>(c->irr_b), as<uint64_t>(c->irr_e), 0, counts, &ms,
-                     &work));
-    WV_TRY(words_to_host(c, as<uint64_t>(c->irr_b), b, as<uint64_t>(c->irr_e), e, nt));
+    WV_TRY(irr_batch(c, std::vector<uint64_t>{p}, b, e, 0, nullptr, &ms, &work));
     c->stats.n_primes = 1;
     c->stats.n_terms = (uint64_t)work;
     c->stats.ms_sum = ms;
