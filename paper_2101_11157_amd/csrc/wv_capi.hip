@@ -42,7 +42,12 @@ int ensure(wv_ctx *c, DevBuf &b, size_t bytes) {
         (void)hipGetLastError();
         b.ptr = nullptr;
         want = need;
-        WV_HIP(hipMalloc(&b.ptr, want));
+        const hipError_t e = hipMalloc(&b.ptr, want);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();   // the caller may go on with less
+            b.ptr = nullptr;
+            return e == hipErrorOutOfMemory ? WV_ENOMEM : WV_EHIP;
+        }
     }
     b.cap = want;
     c->gen++;   // captured graphs hold the old address

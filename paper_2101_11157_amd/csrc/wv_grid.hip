@@ -977,26 +977,35 @@ int grid_enqueue(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &own, c
     for (int l = kNttMinLog; l <= std::min(g.logl, kNttMaxLog); l++) WV_TRY(ntt_tables(c, l));
     if (g.logl > kNttMaxLog) WV_TRY(split_table(c));
     WV_TRY(runs_table(c));
-    // sub-batches within the workspace bound
+    // sub-batches within the workspace bound, or within what the device has left
     const unsigned blocks = grid_blocks(c, g.logl);
     const size_t one = grid_layout(g, 64, pmax, 0).total / 64 + 1;
     uint32_t step = (uint32_t)std::min<uint64_t>(n, std::max<uint64_t>(1, kGridBytes / one));
     step = std::min<uint32_t>(step, 1u << 16);
-    const uint32_t parts = (n + step - 1) / step;
-    step = (n + parts - 1) / parts;
-    const GridLayout y = grid_layout(g, step, pmax, blocks);
-    const uint64_t nseg = (uint64_t)step * (kTables[g.tb].n + kTables[g.te].n);
-    WV_TRY(ensure(c, b.pr, step * sizeof(PrimeRec)));
-    WV_TRY(ensure(c, b.segs, nseg * sizeof(SegRec)));
-    WV_TRY(ensure(c, b.runs, nseg * sizeof(SegRec)));   // no more runs than sums
-    WV_TRY(ensure(c, b.terms, nseg * sizeof(uint64_t)));
-    WV_TRY(ensure(c, b.cnt, nseg * sizeof(uint64_t)));
-    WV_TRY(ensure(c, b.off, (nseg + 1) * sizeof(uint64_t)));
-    WV_TRY(ensure(c, b.tiles, ((nseg + kScanTile - 1) / kScanTile + 1) * sizeof(uint64_t)));
-    WV_TRY(ensure(c, b.seg_pairs, nseg * sizeof(Pair)));
-    WV_TRY(ensure(c, b.coefs, nseg * sizeof(uint64_t)));
-    WV_TRY(ensure(c, b.lhsmod, 2 * (size_t)step * sizeof(uint64_t)));
-    WV_TRY(ensure(c, b.ws, y.total));
+    GridLayout y;
+    auto reserve = [&]() -> int {
+        y = grid_layout(g, step, pmax, blocks);
+        const uint64_t nseg = (uint64_t)step * (kTables[g.tb].n + kTables[g.te].n);
+        WV_TRY(ensure(c, b.pr, step * sizeof(PrimeRec)));
+        WV_TRY(ensure(c, b.segs, nseg * sizeof(SegRec)));
+        WV_TRY(ensure(c, b.runs, nseg * sizeof(SegRec)));   // no more runs than sums
+        WV_TRY(ensure(c, b.terms, nseg * sizeof(uint64_t)));
+        WV_TRY(ensure(c, b.cnt, nseg * sizeof(uint64_t)));
+        WV_TRY(ensure(c, b.off, (nseg + 1) * sizeof(uint64_t)));
+        WV_TRY(ensure(c, b.tiles, ((nseg + kScanTile - 1) / kScanTile + 1) * sizeof(uint64_t)));
+        WV_TRY(ensure(c, b.seg_pairs, nseg * sizeof(Pair)));
+        WV_TRY(ensure(c, b.coefs, nseg * sizeof(uint64_t)));
+        WV_TRY(ensure(c, b.lhsmod, 2 * (size_t)step * sizeof(uint64_t)));
+        return ensure(c, b.ws, y.total);
+    };
+    for (;;) {
+        const uint32_t parts = (n + step - 1) / step;
+        step = (n + parts - 1) / parts;
+        const int rc = reserve();
+        if (rc == WV_OK) break;
+        if (rc != WV_ENOMEM || step == 1) return rc;
+        step = (step + 1) / 2;
+    }
     for (uint32_t i = 0; i < n; i += step)
         WV_TRY(grid_sub(c, b, st, g, y, d_primes + i, std::min(step, n - i), terms, d_out + i));
     return WV_OK;

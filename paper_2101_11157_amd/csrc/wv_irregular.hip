@@ -966,24 +966,30 @@ int irr_dft(wv_ctx *c, const std::vector<IrrPrime> &prs, std::vector<std::vector
     hipStream_t st = c->stream;
     const std::vector<DftGroup> groups = dft_groups(prs);
     size_t i = groups.empty() ? 0 : groups[0].begin;
+    uint64_t held = kDftDoubles;
     for (size_t k = 0; k < groups.size();) {
         const DftGroup &gr = groups[k];
         const int logl = gr.logl;
         const uint64_t L = 1ull << logl;
         IrrShape sh{0, gr.A, (uint32_t)(L / 2), gr.nq};
         const uint64_t each = sh.seq_len() + sh.vecs() * sh.nq * L, wgs = sh.vecs() * sh.nq * std::max<uint64_t>(L / 256, 4);
-        const uint64_t most = std::max<uint64_t>(1, std::min(kDftDoubles / each, kMaxWgs / wgs));
+        // as many primes as the bound allows, or what the device has left
+        for (;;) {
+            const uint64_t most = std::max<uint64_t>(1, std::min(held / each, kMaxWgs / wgs));
+            sh.n = (uint32_t)std::min<uint64_t>(most, gr.end - i);
+            int rc = ensure(c, c->irr_seq, sh.n * sh.seq_len() * sizeof(double));
+            if (rc == WV_OK) rc = ensure(c, c->irr_hat, sh.n * sh.vecs() * sh.nq * L * sizeof(double));
+            if (rc == WV_OK) break;
+            if (rc != WV_ENOMEM || sh.n == 1) return rc;
+            held = sh.n / 2 * each;
+        }
         keep.emplace_back();
         std::vector<IrrNtt> &g = keep.back();
-        for (; i < gr.end && g.size() < most; i++)
-            g.push_back(IrrNtt{prs[i].p, prs[i].vb, prs[i].ve, (prs[i].p - 1) / 2});
+        for (; g.size() < sh.n; i++) g.push_back(IrrNtt{prs[i].p, prs[i].vb, prs[i].ve, (prs[i].p - 1) / 2});
         if (i == gr.end && ++k < groups.size()) i = groups[k].begin;   // gr's shape is in sh
-        sh.n = (uint32_t)g.size();
         WV_TRY(ntt_tables(c, logl));
         WV_TRY(ensure(c, c->irr_dft, g.size() * sizeof(IrrNtt)));
         WV_TRY(ensure(c, c->irr_root, g.size() * sizeof(double)));
-        WV_TRY(ensure(c, c->irr_seq, sh.n * sh.seq_len() * sizeof(double)));
-        WV_TRY(ensure(c, c->irr_hat, sh.n * sh.vecs() * sh.nq * L * sizeof(double)));
         WV_HIP(hipMemcpyAsync(c->irr_dft.ptr, g.data(), g.size() * sizeof(IrrNtt), hipMemcpyHostToDevice, st));
         const IrrNtt *pr = as<IrrNtt>(c->irr_dft);
         double *seq = as<double>(c->irr_seq), *hat = as<double>(c->irr_hat);
@@ -1019,7 +1025,7 @@ int irr_dft(wv_ctx *c, const std::vector<IrrPrime> &prs, std::vector<std::vector
 // residues of every index, prime by prime; else zero pairs appended to the device
 // list and the counters {fixups, pairs, unresolved}.
 int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *b, uint64_t *e, uint64_t pair_cap,
-              uint64_t counts_out[3], float *ms_sum, double *pairs_done) {
+              uint64_t counts_out[3], float *ms_sum, double *pairs_done, bool transforms = true) {
     hipStream_t st = c->stream;
     uint64_t *d_b = b ? as<uint64_t>(c->irr_b) : nullptr, *d_e = b ? as<uint64_t>(c->irr_e) : nullptr;
     std::vector<IrrTask> tasks;
@@ -1036,7 +1042,7 @@ int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *b, uint64_t 
     // Path 2: the matrix cores while every partial sum stays exact.
     double squares = 0.0;
     for (uint64_t p : ps) squares += (double)p * (double)p;
-    const bool dft = c->irr_path == 0 && squares >= kDftSquares;
+    const bool dft = c->irr_path == 0 && transforms && squares >= kDftSquares;
     const bool mma = c->irr_path != 1 && !dft && *std::max_element(ps.begin(), ps.end()) < kIrrMmaMaxP;
     // exponents per row 16 ct: the least work over whole row blocks, each row
     // costing its N multiply-adds per s plus about 8 for building its A entry
@@ -1106,7 +1112,18 @@ int irr_batch(wv_ctx *c, const std::vector<uint64_t> &ps, uint64_t *b, uint64_t 
     }
     WV_HIP(hipEventRecord(c->ev[EV_SUM0], st));
     if (dft) {
-        WV_TRY(irr_dft(c, prs, keep));
+        const int rc = irr_dft(c, prs, keep);
+        if (rc == WV_ENOMEM) {
+            // a prime's transforms (120 bytes times p) need more than there is: the
+            // power sums, which need a tenth of that
+            WV_HIP(hipStreamSynchronize(st));
+            for (DevBuf *x : {&c->irr_seq, &c->irr_hat}) {
+                if (x->ptr) WV_HIP(hipFree(x->ptr));
+                *x = DevBuf{};
+            }
+            return irr_batch(c, ps, b, e, pair_cap, counts_out, ms_sum, pairs_done, false);
+        }
+        WV_TRY(rc);
     } else if (mma) {
         // one workgroup per unit, in launches of fewer than 2^32 work-items
         for (uint64_t u0 = 0; u0 < nunits; u0 += kMmaMaxGrid) {
