@@ -700,11 +700,13 @@ uint32_t bitrev(uint32_t v, int bits) {
     return r;
 }
 
-template <class F>
+// fn(integral_constant<int, c>), c a power of two from MIN on
+template <int MIN, class F>
 int with_chunks(int c, F &&fn) {
     switch (c) {
-    case 1: return fn(std::integral_constant<int, 1>{});
-    case 2: return fn(std::integral_constant<int, 2>{});
+    case 2:
+        if constexpr (MIN <= 2) return fn(std::integral_constant<int, 2>{});
+        return WV_EINVAL;
     case 4: return fn(std::integral_constant<int, 4>{});
     case 8: return fn(std::integral_constant<int, 8>{});
     case 16: return fn(std::integral_constant<int, 16>{});
@@ -867,7 +869,7 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
     case 10: launch_inv<16>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
     default: launch_inv<32>(st, inv_grid, runs, off, nruns, pr, K, logw, inv); break;
     }
-    WV_TRY(with_chunks((int)(K + 1) / 256, [&](auto c) -> int {
+    WV_TRY(with_chunks<(1 << kGridMinLog) / 512>((int)(K + 1) / 256, [&](auto c) -> int {
         hipLaunchKernelGGL(k_grid_fact<decltype(c)::value>, dim3(n), dim3(256), 0, st, pr, at(y.fact));
         return WV_OK;
     }));
@@ -883,7 +885,7 @@ int grid_sub(wv_ctx *c, GridWork &b, hipStream_t st, const GridClass &g, const G
     };
     for (int l = kNttMinLog; l < g.logl; l++) {
         const uint32_t k = (uint32_t)grid_k(l);
-        WV_TRY(with_chunks((1 << l) / 256, [&](auto c) -> int {
+        WV_TRY(with_chunks<(1 << kNttMinLog) / 256>((1 << l) / 256, [&](auto c) -> int {
             hipLaunchKernelGGL(k_grid_level<decltype(c)::value>, dim3(3 * n), dim3(256), 0, st, pr, K, at(y.beta),
                                at(y.pi), at(y.cst));
             return WV_OK;
