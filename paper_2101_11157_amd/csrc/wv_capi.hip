@@ -1214,22 +1214,17 @@ int wv_search_range(wv_ctx *c, uint64_t lo, uint64_t hi, wv_result *out, size_t 
     return WV_OK;
 }
 
-int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) {
-    if (!c) return WV_EINVAL;
-    if (n == 0) return WV_OK;
-    if (!primes || !out) return WV_EINVAL;
-    if (n > 0xFFFFFFFFull) return WV_EINVAL;
+// Primes of a list taken at once: the buffers, the host's copies and the kernels'
+// 32-bit counters are sized for these.
+static constexpr size_t kListSlice = 1 << 26;
+
+static int eval_list(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) {
     uint64_t pmax = 0;
     double sum = 0;
     for (size_t i = 0; i < n; i++) {
-        if (primes[i] < 5 || primes[i] >= WV_P_MAX) return WV_EDOMAIN;
-        if (!is_prime_u64(primes[i])) return WV_ENOTPRIME;
         pmax = std::max(pmax, primes[i]);
         sum += (double)primes[i];
     }
-    WV_TRY(check_device(c));
-    c->stats = wv_stats{};
-    pick_tuned(c, pmax);
     WV_TRY(ensure(c, c->primes, n * sizeof(uint64_t)));
     WV_TRY(ensure(c, c->results, n * sizeof(wv_result)));
     WV_HIP(hipMemcpyAsync(c->primes.ptr, primes, n * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
@@ -1275,6 +1270,25 @@ int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) 
         WV_TRY(run_batch_sync(c, as<uint64_t>(c->primes) + b, (uint32_t)k, pmax + 1, as<wv_result>(c->results) + b));
     }
     return results_to_host(c, as<wv_result>(c->results), n, out);
+}
+
+int wv_eval_primes(wv_ctx *c, const uint64_t *primes, size_t n, wv_result *out) {
+    if (!c) return WV_EINVAL;
+    if (n == 0) return WV_OK;
+    if (!primes || !out) return WV_EINVAL;
+    if (n > 0xFFFFFFFFull) return WV_EINVAL;
+    uint64_t pmax = 0;
+    for (size_t i = 0; i < n; i++) {
+        if (primes[i] < 5 || primes[i] >= WV_P_MAX) return WV_EDOMAIN;
+        if (!is_prime_u64(primes[i])) return WV_ENOTPRIME;
+        pmax = std::max(pmax, primes[i]);
+    }
+    WV_TRY(check_device(c));
+    c->stats = wv_stats{};
+    pick_tuned(c, pmax);
+    for (size_t at = 0; at < n; at += kListSlice)
+        WV_TRY(eval_list(c, primes + at, std::min(kListSlice, n - at), out + at));
+    return WV_OK;
 }
 
 int wv_eval_sums(wv_ctx *c, const uint64_t *primes, size_t n, uint64_t *out_b, uint64_t *out_e) {
