@@ -88,9 +88,11 @@ typedef struct wv_ctx wv_ctx;
 
 /* Timings (milliseconds, HIP events on the context stream) and sizes of the
  * most recent wv_search_range / wv_eval_primes call.  Primes evaluated along
- * progressions (see wv_set_tables) count the sums and terms of the
- * congruences used for them, their device time under ms_sum, no chunks, and
- * the terms per block as chunk_terms. */
+ * progressions or directly (see wv_set_tables) count the sums and terms of the
+ * congruences used for them, their device time under ms_sum and no chunks;
+ * chunk_terms is the terms per block of the progressions (2^k - 1), or 4 for
+ * primes evaluated directly.  A call of several batches adds them up; chunk_terms
+ * and grid are those of its last one. */
 typedef struct {
     double ms_total;     /* first to last event of the call (device time)        */
     double ms_sieve;     /* segmented sieve and prime compaction (search only)   */
@@ -122,10 +124,13 @@ int wv_destroy(wv_ctx *ctx);
  * or a defined Euler table.  Default: WV_TABLE_BB30 and WV_TABLE_EE33 (the
  * cheapest printed ones, cost 227p/6480 and 27p/512).  Every valid choice gives
  * identical residues; only the work changes.  With the default choice (and no
- * forced block shape, chunk size or progress callback) the synchronous calls
- * evaluate primes from 2^27 on by fast evaluation along arithmetic
- * progressions instead of term by term, from whichever printed congruences
- * cost it least at their size.  Errors: WV_EINVAL. */
+ * forced block shape, chunk size or progress callback) the synchronous calls and
+ * the request server evaluate primes from 9*2^23 on by fast evaluation along
+ * arithmetic progressions instead of term by term, from whichever printed
+ * congruences cost it least at their size; the synchronous calls and
+ * wv_eval_primes_static evaluate batches of little work (up to 1.6e9 terms below
+ * 2^27, 5e8 from there on, and every batch of primes up to 3*2^20) directly, in
+ * one launch from the primes to the residues.  Errors: WV_EINVAL. */
 int wv_set_tables(wv_ctx *ctx, int b_table, int e_table);
 
 /* Define a congruence at run time (for instance one derived from eqnVandiver
@@ -162,7 +167,8 @@ int wv_set_table_below(wv_ctx *ctx, int id, int below);
  * which balances the set-up of each chunk against lanes idling when the last
  * chunks finish).  Each sum is cut into chunks of exactly this many terms plus
  * one shorter tail; the tails of all sums run after the full chunks, longest
- * first.  Must be a multiple of 64 when nonzero.  Results do not depend on it. */
+ * first.  Must be a multiple of 64 when nonzero.  Nonzero: every prime goes through
+ * the term sums.  Results do not depend on it. */
 int wv_set_chunk_terms(wv_ctx *ctx, uint64_t chunk_terms);
 
 /* Choose the block shape of the term-sum kernel: kb terms per block on the
@@ -172,7 +178,8 @@ int wv_set_chunk_terms(wv_ctx *ctx, uint64_t chunk_terms);
  * eqnCombinePairs, whose two members come from the Taylor coefficients of
  * prod_j (x + j) stepped by finite differences.  Results do not depend on the
  * shape.
- * kb = ke = 0 returns to the default / autotuned choice.
+ * A forced shape sends every prime through the term sums; kb = ke = 0 returns to
+ * the default / autotuned choice.
  * Errors: WV_EINVAL for a shape that is not compiled. */
 int wv_set_block(wv_ctx *ctx, int kb, int ke);
 
@@ -187,8 +194,8 @@ int wv_set_progress(wv_ctx *ctx, wv_progress_fn fn, void *user, uint64_t terms_p
 /* Autotuner: times every compiled block shape with chunk sizes 2^16, 2^18 and
  * automatic (reported as 0) on sample primes just above p_hint (n_sample of them, 0: 16) and
  * keeps the fastest for primes in [2^k, 2^(k+1)), k = floor(log2 p_hint).
- * Synchronous calls on primes in a tuned range then use the tuned shape and
- * chunk unless wv_set_block / wv_set_chunk_terms force others.  The measured
+ * The term sums of synchronous calls on primes in a tuned range then use the
+ * tuned shape and chunk unless wv_set_block / wv_set_chunk_terms force others.  The measured
  * rates go to rates[v*3 + j] (terms/s) when rates is non-NULL (room for
  * 3 x the number of compiled shapes).  Returns the chosen shape and chunk. */
 int wv_autotune(wv_ctx *ctx, uint64_t p_hint, int n_sample, int *kb, int *ke, uint64_t *chunk_terms,
@@ -268,7 +275,8 @@ int wv_range_stats(wv_ctx *ctx, uint64_t lo, uint64_t hi, uint32_t bins, uint64_
  * eqnEMac2 (Section 4: (-1)^k' 4^(k'-1) (9^k' + 1) E_t == 2^t (S_t(0, 1/12)
  * - S_t(5/12, 1/2)), k' = (p - 1 - t)/2) and, where 9^k' == -1 (mod p), from
  * eqnE1 with the sign read as (-1)^k'.  The power sums of every exponent run
- * on the device: about p^2 / 8 terms per prime. */
+ * on the device: as one discrete Fourier transform per side, or the about p^2 / 8
+ * terms per prime one by one (wv_set_irregular_path; wv_stats counts those). */
 #define WV_IRR_P_MAX (1ULL << 27)
 
 typedef struct {
@@ -306,11 +314,13 @@ int wv_irregular_pairs(wv_ctx *ctx, uint64_t lo, uint64_t hi, wv_irr_pair *out, 
                        uint64_t *n_primes, uint64_t *n_unresolved);
 
 /* Batched search over nwin windows [lo[w], hi[w]) (may differ in size and
- * position): all windows are sieved together and all their primes go through
- * one plan and one persistent term-sum launch per batch (at most 2^19 primes,
- * 2^27 (prime, sum) slots and about 2^44 terms; a wide window at large p is
- * cut into sub-ranges that fall into several batches), with work split by
- * cost (equal-size chunks of the flat term space).  out
+ * position): all windows are sieved together.  Primes of the term sums go through
+ * one plan and one persistent launch per batch (at most 2^19 primes, 2^27
+ * (prime, sum) slots and about 2^44 terms; a wide window at large p is cut into
+ * sub-ranges that fall into several batches), with work split by cost
+ * (equal-size chunks of the flat term space); those evaluated along progressions
+ * in batches of like sizes; windows of little work in all as one batch where that
+ * is the quicker way.  out
  * receives the results window by window, ascending p within a window;
  * win_off (nwin + 1 entries, may be NULL) receives each window's first index
  * and the total.  Short buffer: WV_ETRUNC with *n_out set, nothing written.
@@ -320,7 +330,8 @@ int wv_search_windows(wv_ctx *ctx, const uint64_t *lo, const uint64_t *hi, size_
 
 /* Residues for n given primes (host memory), results in input order: the
  * same computation as wv_search_range (Sections 3 and 5, eqnDefnS,
- * eqnComputeS, eqnCombinePairs) for a caller-chosen list.  Each
+ * eqnComputeS, eqnCombinePairs) for a caller-chosen list, of primes of any sizes
+ * in any order, with or without repeats.  Each
  * p must satisfy 5 <= p < WV_P_MAX (else WV_EDOMAIN) and be prime (checked on
  * the host by deterministic Miller-Rabin; else WV_ENOTPRIME).  n == 0 is a
  * no-op. */
@@ -349,7 +360,9 @@ int wv_eval_primes_async(wv_ctx *ctx, const uint64_t *d_primes, size_t n,
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * computation and the same arguments and results as wv_eval_primes_async, but
- * the call allocates nothing, captures no graph and never synchronises.
+ * the call allocates nothing, captures no graph and never synchronises.  The
+ * device chooses between the term sums and, with the default congruences, the
+ * direct evaluation of lists of little work.
  * Every intermediate buffer lives in one fixed device array of
  * WV_STATIC_SCRATCH_BYTES that the library holds on each GPU it runs on until
  * the process ends (looked up by wv_create); ctx contributes only its
@@ -388,7 +401,9 @@ int wv_eval_sums(wv_ctx *ctx, const uint64_t *primes, size_t n, uint64_t *out_b,
  * requests, about `step_terms` terms in all (an even share per request, the
  * rest to the smallest remaining work first, at least one prime), runs every
  * sum of those primes through the term-sum kernels and folds it into its
- * pair with eqnCombinePairs (Section 3).  Requests that arrive while others
+ * pair with eqnCombinePairs (Section 3).  Requests whose primes all lie from
+ * 9*2^23 on are evaluated along progressions where the synchronous calls do so
+ * (wv_set_tables), a step's primes of them in batches of like sizes.  Requests that arrive while others
  * run join at the next step; results do not depend on the interleaving (exact
  * arithmetic, associative product).  All device work goes on the context's
  * stream in call order (admission between steps); the host keeps no per-sum
@@ -435,8 +450,10 @@ int wv_server_submit_primes(wv_server *srv, const uint64_t *primes, size_t n, ui
  * its results become available in the call that completes that step
  * (wv_server_result says WV_EBUSY until then).  A step holds about
  * step_terms terms (default 2^38, about 45 ms of the whole GPU at p ~ 1e11)
- * and at most 2^23 sums (2^22 while a request with at most an eighth of
- * step_terms left is active, so that it completes in a short step).
+ * and at most 2^23 sums of the congruences set at creation (2^22 while a request
+ * with at most an eighth of step_terms left is active).  With the thousands of
+ * sums of the derived ladders that cap lets such a request complete in a short
+ * step; with the 63 of the printed congruences the terms set the step.
  * Admission takes requests pending for 2 s or more in
  * arrival order, then the smallest first (by number of primes), and plans at
  * most 2^24 sums per call; a request that does not fit in the pool waits

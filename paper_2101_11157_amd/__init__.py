@@ -425,8 +425,8 @@ class Context:
 
     def set_irregular_path(self, path):
         """Method of the irregular-pair calls: 0 automatic (one transform per
-        prime), 1 power sums on the vector ALU, 2 on the matrix cores where
-        exact (p < 2^24)."""
+        prime and side; the smallest batches as 2), 1 power sums on the vector
+        ALU, 2 on the matrix cores where exact (p < 2^24)."""
         _check(lib().wv_set_irregular_path(self._h, int(path)), "wv_set_irregular_path")
 
     def bernoulli_euler_all(self, p):
